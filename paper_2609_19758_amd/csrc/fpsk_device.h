@@ -48,22 +48,6 @@ __device__ __forceinline__ uint32_t absmax2(uint32_t mx, uint32_t w) {
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(a, b));
 }
 
-// 8 halfs of a row starting at column col (zero beyond n).
-__device__ __forceinline__ u32x4 load8h(const uint16_t* row, int64_t col, int64_t n, bool vec) {
-  if (vec && col + 8 <= n) {
-    return __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(row + col));
-  }
-  u32x4 r = {0u, 0u, 0u, 0u};
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    if (col + e < n) {
-      const uint32_t h = row[col + e];
-      r[e >> 1] |= h << (16 * (e & 1));
-    }
-  }
-  return r;
-}
-
 // Branch-free 16-byte loads for the vector path: an invalid row or lane reads the zero buffer
 // instead of branching, so a group of loads issues back to back.
 __device__ __forceinline__ u32x4 load8h_sel(const uint16_t* p, bool ok, const void* zero) {
@@ -78,18 +62,98 @@ __device__ __forceinline__ void load8f_sel(const float* p, bool ok, const void* 
   v1 = __builtin_nontemporal_load(q + 1);
 }
 
-// 8 floats of a row starting at column col (zero beyond n).
-__device__ __forceinline__ void load8f(const float* row, int64_t col, int64_t n, bool vec,
-                                       f32x4& v0, f32x4& v1) {
-  if (vec && col + 8 <= n) {
-    v0 = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + col));
-    v1 = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(row + col + 4));
-    return;
+// Ragged rows: a row length that is no multiple of 8 or a base off a 16-byte boundary.  gfx950
+// takes 16-byte global loads at any element alignment, so ragged rows keep the vector path's
+// loads (8 elements a lane, all issued back to back) instead of 8 element loads under branches:
+// 2047 x 8191 x 8191 BF16 at m = 64, stream kernel 152.5 -> 50.9 us (3947 GB/s of A, B and C; the
+// aligned 2048 x 8192 x 8192 takes 43 us); 1531 x 4096 x 32003 FP16 at m = 279, call 493 -> 231
+// us.  Three things keep them right:
+//   - `last` is the matrix's element count less 8.  A lane whose 8 elements would pass the end of
+//     the matrix (in its last row or rows) loads the final 8 instead and rag_shift moves them
+//     down.  (A matrix of fewer than 8 elements comes in a copy padded to 8, with last = 0.)
+//   - elements past the row's end are the next row's and are masked off (rag_keep).
+//   - rag_near says, uniformly for a wave, whether any lane of a row needs the shift.
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+
+__device__ __forceinline__ int64_t rag_last(int64_t rows, int64_t n) {
+  const int64_t l = rows * n - 8;
+  return l > 0 ? l : 0;
+}
+
+// Element offset, from the tile's first element `base` in the matrix, that a lane at offset
+// `off` loads from.
+__device__ __forceinline__ int rag_off(int64_t base, int off, int64_t last) {
+  const int64_t rem = last - base;
+  const int lim = rem < -(1 << 30) ? -(1 << 30) : (rem > (1 << 30) ? (1 << 30) : static_cast<int>(rem));
+  return off < lim ? off : lim;
+}
+
+__device__ __forceinline__ bool rag_near(int64_t base, int max_off, int64_t last) {
+  return base + max_off > last;
+}
+
+__device__ __forceinline__ u32x4 load8h_rag(const uint16_t* X, int64_t base, int off,
+                                            int64_t last, bool ok, const void* zero) {
+  const uint16_t* p = X + base + rag_off(base, off, last);
+  const u32x4_a2* q = ok ? reinterpret_cast<const u32x4_a2*>(p)
+                                      : static_cast<const u32x4_a2*>(zero);
+  return __builtin_nontemporal_load(q);
+}
+
+__device__ __forceinline__ void load8f_rag(const float* X, int64_t base, int off, int64_t last,
+                                           bool ok, const void* zero, f32x4& v0, f32x4& v1) {
+  const float* p = X + base + rag_off(base, off, last);
+  const f32x4_a4* q = ok ? reinterpret_cast<const f32x4_a4*>(p)
+                                      : static_cast<const f32x4_a4*>(zero);
+  v0 = __builtin_nontemporal_load(q);
+  v1 = __builtin_nontemporal_load(q + 1);
+}
+
+// The rows rag_near picks: the final 8 elements of the matrix moved down to the lane's own
+// (zeros beyond the end), or the element loads of a matrix of fewer than 8.
+__device__ __forceinline__ void rag_shift(u32x4& v, int64_t base, int off, int64_t last, bool ok) {
+  const int s = ok ? off - rag_off(base, off, last) : 0;    // 0 .. 7 elements
+  if (s & 1) {
+    v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16),
+              (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
   }
+  if (s & 2) v = u32x4{v[1], v[2], v[3], 0u};
+  if (s & 4) v = u32x4{v[2], v[3], 0u, 0u};
+}
+
+__device__ __forceinline__ void rag_shift(f32x4& v0, f32x4& v1, int64_t base, int off,
+                                          int64_t last, bool ok) {
+  const int s = ok ? off - rag_off(base, off, last) : 0;    // 0 .. 7 elements
+  if (s & 1) {
+    v0 = f32x4{v0[1], v0[2], v0[3], v1[0]};
+    v1 = f32x4{v1[1], v1[2], v1[3], 0.0f};
+  }
+  if (s & 2) {
+    v0 = f32x4{v0[2], v0[3], v1[0], v1[1]};
+    v1 = f32x4{v1[2], v1[3], 0.0f, 0.0f};
+  }
+  if (s & 4) {
+    v0 = v1;
+    v1 = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+}
+
+// Masks of the elements col .. col + 7 that lie in a row of n.
+__device__ __forceinline__ u32x4 rag_keep(int64_t col, int64_t n) {
+  u32x4 k;
+#pragma unroll
+  for (int h = 0; h < 4; ++h) {
+    k[h] = (col + 2 * h < n ? 0xffffu : 0u) | (col + 2 * h + 1 < n ? 0xffff0000u : 0u);
+  }
+  return k;
+}
+
+__device__ __forceinline__ void rag_mask(f32x4& v0, f32x4& v1, int64_t col, int64_t n) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    v0[e] = (col + e < n) ? row[col + e] : 0.0f;
-    v1[e] = (col + 4 + e < n) ? row[col + 4 + e] : 0.0f;
+    if (col + e >= n) v0[e] = 0.0f;
+    if (col + 4 + e >= n) v1[e] = 0.0f;
   }
 }
 

@@ -469,13 +469,13 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
   // m = 400: 82.5 -> 59.2 us).  The 512-entry tile lists of m > 256 let one 16-byte load per
   // thread stage all four; m <= 1024 keeps the fold's segment starts (8 G) in registers.
   d.wt_c = m > 256 && m <= 1024 && n1 <= 32 * static_cast<int64_t>(m) && d.tg >= 4;
-  // The same at 48 < m <= 192 for the probe with B as stored and whole 16-byte rows (the
-  // instance with 4-row B work-groups; its unaligned form would spill): column groups of 4 tiles
+  // The same at 48 < m <= 192 for the probe with B as stored (the
+  // instance with 4-row B work-groups): column groups of 4 tiles
   // instead of about 1024 / m groups, the padded 8-entry lists staged after the column sums
   // (2048 x 4096 x 12288 at m = 80: stream pass 43.3 -> 41.5 us; 2048 x 8192 x 8192 at m = 64:
-  // 45.3 -> 43.8 us).
+  // 45.3 -> 43.8 us; ragged rows, 2047 x 8191 x 8191 at m = 64: 54.9 -> 50.9 us).
   if (!mom && !transb && m > 48 && m <= 192 && n1 <= 32 * static_cast<int64_t>(m) &&
-      d.TC >= 4 && n2 % 8 == 0 && n3 % 8 == 0) {
+      d.TC >= 4) {
     d.wt_c = true;
     d.npc = (d.TC + 3) / 4;
     d.tg = (d.TC + d.npc - 1) / d.npc;
@@ -714,6 +714,7 @@ struct fpsketch_ctx {
   Workspace probe_ws;
   DevBuf stats;       // 8 doubles
   DevBuf zero;        // 64 bytes of zeros
+  DevBuf tiny;        // three 32-byte slots: A, B, C of fewer than 8 elements, zero-padded
   DevBuf sigma_acc;   // 2 doubles
   // localize / diagnostic workspaces
   DevRound aux_round;
@@ -844,7 +845,7 @@ fpsketch_status pass_args(fpsketch_ctx* c, const DevRound& R, Workspace& W, cons
   // B as stored: rows of n3; transposed: rows of W, n2 long
   s.vec_b = ((c->transb ? c->n2 : c->n3) % 8 == 0) && aligned16(B);
   s.vec_c = (c->n3 % 4 == 0) && aligned16(Cm);
-  // the vector path loads whole 8-element groups: every row length must be a multiple of 8
+  // the aligned instances load whole 8-element groups: every row length must be a multiple of 8
   if (c->n2 % 8 != 0 || c->n3 % 8 != 0) s.vec_a = s.vec_b = s.vec_c = 0;
   s.zero = c->zero.p;
   if (R.cwb != d.cwb || R.m != d.m || R.mom != mom || (c->transb && R.perm2.p == nullptr)) {
@@ -920,6 +921,32 @@ fpsketch_status pass_args(fpsketch_ctx* c, const DevRound& R, Workspace& W, cons
   return FPSK_OK;
 }
 
+// Operands of fewer than 8 elements go to the stream pass in the context's padded copies.
+fpsketch_status pad_tiny(fpsketch_ctx* c, fpsk::StreamArgs& s, hipStream_t st) {
+  fpsk::PadTinyArgs a{};
+  a.dst = as<uint16_t>(c->tiny);
+  const int64_t na = c->n1 * c->n2, nb = c->n2 * c->n3, nc = c->n1 * c->n3;
+  if (s.nA > 0 && na < 8) {
+    a.src[0] = s.A;
+    a.halfwords[0] = static_cast<int>(na);
+    s.A = a.dst;
+  }
+  if (s.nB > 0 && nb < 8) {
+    a.src[1] = s.B;
+    a.halfwords[1] = static_cast<int>(nb);
+    s.B = a.dst + 16;
+  }
+  if (s.nC > 0 && nc < 8) {
+    a.src[2] = reinterpret_cast<const uint16_t*>(s.C);
+    a.halfwords[2] = static_cast<int>(2 * nc);
+    s.C = reinterpret_cast<const float*>(a.dst + 32);
+  }
+  if (a.halfwords[0] + a.halfwords[1] + a.halfwords[2] > 0) {
+    FPSK_HIP(fpsk::launch_pad_tiny(a, st));
+  }
+  return FPSK_OK;
+}
+
 // One sketch pass (stream + product) on `st`.
 fpsketch_status run_pass(fpsketch_ctx* c, const DevRound& R, Workspace& W, const void* A,
                          const void* B, const float* Cm, bool mom, int mode, int32_t* d_dirty,
@@ -932,6 +959,7 @@ fpsketch_status run_pass(fpsketch_ctx* c, const DevRound& R, Workspace& W, const
   fpsk::ProductArgs a;
   FPSK_TRY(pass_args(c, R, W, A, B, Cm, mom, mode, d_dirty, prow, pcol, pval, stats_out,
                      sigma_acc_out, bside, s, a));
+  FPSK_TRY(pad_tiny(c, s, st));
   if (bside == BSide::kFillCache) {
     FPSK_HIP(fpsk::launch_stream(s, c->dt == FPSK_BF16 ? 1 : 0, false, d.rb, d.g, d.ng,
                                  d.lds_stream, st));
@@ -1314,6 +1342,7 @@ fpsketch_status fpsketch_create(int64_t n1, int64_t n2, int64_t n3, fpsketch_dty
   fpsketch_status s = dev_alloc(c->stats, 8 * sizeof(double));
   if (s == FPSK_OK) s = dev_alloc(c->sigma_acc, 2 * sizeof(double));
   if (s == FPSK_OK) s = dev_alloc(c->zero, 64);
+  if (s == FPSK_OK) s = dev_alloc_zero(c->tiny, 96);
   if (s == FPSK_OK) {
     hipError_t e = hipMemset(c->stats.p, 0, 8 * sizeof(double));
     if (e == hipSuccess) e = hipMemset(c->zero.p, 0, 64);
@@ -1341,7 +1370,7 @@ void fpsketch_destroy(fpsketch_ctx* c) {
   free_round(c->aux_round);
   free_workspace(c->aux_ws);
   for (Workspace& w : c->pipe_ws) free_workspace(w);
-  for (DevBuf* b : {&c->stats, &c->sigma_acc, &c->zero, &c->scan_counts, &c->scan_rows, &c->scan_base,
+  for (DevBuf* b : {&c->stats, &c->sigma_acc, &c->zero, &c->tiny, &c->scan_counts, &c->scan_rows, &c->scan_base,
                     &c->scan_out, &c->samples, &c->patch_rowptr, &c->patch_col, &c->patch_val,
                     &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->rc_c, &c->sel_state,
                     &c->sel_hist, &c->peel_list, &c->cands, &c->cand_count, &c->apply_list,
@@ -1484,6 +1513,7 @@ fpsketch_status deferred_probe(fpsketch_ctx* c, const void* A, const void* B, co
   fpsk::ProductArgs a;
   FPSK_TRY(pass_args(c, c->probe_round, W, A, B, C, false, 1, d_dirty, nullptr, nullptr, nullptr,
                      nullptr, nullptr, bside, s, a));
+  FPSK_TRY(pad_tiny(c, s, st));
   const size_t lds = std::max(d.lds_stream, fpsk::probe_pipe_lds(d.xb));
   FPSK_HIP(fpsk::launch_probe_pipe(s, c->pipe_prod, c->pipe_dec,
                                    c->pipe_has_prod ? c->pipe_nprod : 0,

@@ -86,7 +86,7 @@ struct StreamArgs {
   // (row block mod TB) and wrap (n3 a whole number of chunks, TB > 1)
   int rot_b;
   double inv_l1, inv_l3;      // 1 / 2^ceil(log2 n1), 1 / 2^ceil(log2 n3)
-  int vec_a, vec_b, vec_c;    // 16-byte vector loads allowed
+  int vec_a, vec_b, vec_c;    // rows are whole aligned 16-byte groups
   const void* zero;           // >= 64 bytes of zeros (read in place of invalid rows or lanes)
 };
 
@@ -196,6 +196,14 @@ struct ApplyEntry {    // one record of the apply step: C[o] <- d, or C[o] + d
   int32_t absolute;
   int32_t pad;
 };
+// Matrices of fewer than 8 elements, copied into zero-padded slots of 16 halfwords so that the
+// stream pass's 8-element loads stay inside: halfwords[b] (0: not copied) of src[b] to slot b.
+struct PadTinyArgs {
+  const uint16_t* src[3];
+  int halfwords[3];
+  uint16_t* dst;
+};
+hipError_t launch_pad_tiny(const PadTinyArgs& a, hipStream_t st);
 hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st);
 // Zeroes columns [c0, c1) of rows x ld FP32 rows (c1 <= ld).
 hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipStream_t st);

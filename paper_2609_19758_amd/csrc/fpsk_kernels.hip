@@ -963,6 +963,18 @@ hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipSt
   return hipGetLastError();
 }
 
+// Copies of matrices of fewer than 8 elements into 32-byte slots (zero past them): thread t of
+// block b copies halfword t of matrix b.
+__global__ __launch_bounds__(64) void pad_tiny_kernel(PadTinyArgs a) {
+  const int b = blockIdx.x, t = threadIdx.x;
+  if (t < a.halfwords[b]) a.dst[16 * b + t] = a.src[b][t];
+}
+
+hipError_t launch_pad_tiny(const PadTinyArgs& a, hipStream_t st) {
+  hipLaunchKernelGGL(pad_tiny_kernel, dim3(3), dim3(64), 0, st, a);
+  return hipGetLastError();
+}
+
 hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(apply_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, st, C,

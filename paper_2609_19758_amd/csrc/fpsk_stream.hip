@@ -34,6 +34,7 @@ __device__ __forceinline__ int32_t row_entry(int32_t pe, int r) {
 // the rows j of W with h2, v2, w_j give Q = (B H2^T)^T and Qw directly, in the same layout.
 struct RowSide {
   const uint16_t* X;       // rows x n2 half bits
+  int64_t last;            // rag_last of X (ragged rows)
   const int32_t* perm;     // bucket lists (row | sign << 31), cap entries each
   int cap;
   double inv_l;            // 1 / 2^ceil(log2 rows)
@@ -43,11 +44,34 @@ struct RowSide {
 };
 
 __device__ __forceinline__ RowSide a_side(const StreamArgs& s) {
-  return RowSide{s.A, s.perm, s.cap, s.inv_l1, s.P, s.Pw, s.maxpart};
+  return RowSide{s.A, rag_last(s.n1, s.n2), s.perm, s.cap, s.inv_l1, s.P, s.Pw, s.maxpart};
 }
 
 __device__ __forceinline__ RowSide w_side(const StreamArgs& s) {
-  return RowSide{s.B, s.perm2, s.cap2, s.inv_l3, s.Q, s.Qw, s.maxpart + s.nA};
+  return RowSide{s.B, rag_last(s.n3, s.n2), s.perm2, s.cap2, s.inv_l3, s.Q, s.Qw, s.maxpart + s.nA};
+}
+
+// Ragged rows: the group's rows at the end of the matrix shifted, then the row ends masked.
+template <int U>
+__device__ __forceinline__ void rag_rows(const RowSide& rs, int64_t n, int64_t tcol, int lane,
+                                         bool lane_ok, int32_t pe, int r0, int nr,
+                                         const u32x4& keep, u32x4 (&v)[U]) {
+  bool near = false;
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const int64_t row = row_entry(pe, r0 + q < nr ? r0 + q : 0) & 0x7fffffff;
+    near |= rag_near(row * n + tcol, kColTile - 8, rs.last);
+  }
+  if (near) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const bool ok = r0 + q < nr;
+      const int64_t row = row_entry(pe, ok ? r0 + q : 0) & 0x7fffffff;
+      rag_shift(v[q], row * n + tcol, lane * 8, rs.last, ok && lane_ok);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < U; ++q) v[q] &= keep;
 }
 
 // Row-bucket work-group: bucket a, column tile t.  out[a, tile] = sum over the bucket's rows of
@@ -60,8 +84,10 @@ __device__ void a_unit(const StreamArgs& s, const RowSide& rs, int u, double* ld
   constexpr int U = 8;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int a = u / s.TA, t = u - a * s.TA;
-  const int64_t col = static_cast<int64_t>(t) * kColTile + lane * 8;
+  const int64_t tcol = static_cast<int64_t>(t) * kColTile;
+  const int64_t col = tcol + lane * 8;
   const bool lane_ok = col < s.n2;
+  const u32x4 keep = rag_keep(col, s.n2);
   const int32_t* prow = rs.perm + static_cast<int64_t>(a) * rs.cap;
   double acc[8], accw[8];
 #pragma unroll
@@ -87,9 +113,10 @@ __device__ void a_unit(const StreamArgs& s, const RowSide& rs, int u, double* ld
         if (VEC) {
           v[q] = load8h_sel(rs.X + row * s.n2 + col, ok && lane_ok, s.zero);
         } else {
-          v[q] = ok ? load8h(rs.X + row * s.n2, col, s.n2, false) : u32x4{0u, 0u, 0u, 0u};
+          v[q] = load8h_rag(rs.X, row * s.n2 + tcol, lane * 8, rs.last, ok && lane_ok, s.zero);
         }
       }
+      if (!VEC) rag_rows<U>(rs, s.n2, tcol, lane, lane_ok, pe, r0, nr, keep, v);
       float g32[8], gw32[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -153,8 +180,10 @@ __device__ void a_unit_wt(const StreamArgs& s, const RowSide& rs, int u, uint32_
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int tq = (s.TA + 3) / 4;
   const int a = u / tq, t = 4 * (u - a * tq) + w;
-  const int64_t col = static_cast<int64_t>(t) * kColTile + lane * 8;
+  const int64_t tcol = static_cast<int64_t>(t) * kColTile;
+  const int64_t col = tcol + lane * 8;
   const bool lane_ok = t < s.TA && col < s.n2;
+  const u32x4 keep = rag_keep(col, s.n2);
   const int32_t* prow = rs.perm + static_cast<int64_t>(a) * rs.cap;
   double acc[8], accw[8];
 #pragma unroll
@@ -180,10 +209,10 @@ __device__ void a_unit_wt(const StreamArgs& s, const RowSide& rs, int u, uint32_
         if (VEC) {
           v[q] = load8h_sel(rs.X + row * s.n2 + col, ok && lane_ok, s.zero);
         } else {
-          v[q] = ok && lane_ok ? load8h(rs.X + row * s.n2, col, s.n2, false)
-                               : u32x4{0u, 0u, 0u, 0u};
+          v[q] = load8h_rag(rs.X, row * s.n2 + tcol, lane * 8, rs.last, ok && lane_ok, s.zero);
         }
       }
+      if (!VEC) rag_rows<U>(rs, s.n2, tcol, lane, lane_ok, pe, r0, nr, keep, v);
       float g32[8], gw32[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
@@ -348,6 +377,32 @@ __device__ __forceinline__ int b_block(int u, int nB) {
   return (u & ~63) | ((u & 7) << 3) | ((u >> 3) & 7);
 }
 
+// Ragged rows of a loaded chunk (rows k0 .., columns from cbase): the rows at the end of the
+// matrix shifted, then the row ends masked (both only where the chunk has them).
+template <int RB, int NI, int CW>
+__device__ __forceinline__ void rag_chunk(const StreamArgs& s, int64_t k0, int64_t cbase,
+                                          int64_t last, u32x4* v) {
+  if (rag_near((k0 + RB - 1) * s.n3 + cbase, CW - 8, last)) {
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      const int g8 = threadIdx.x + kThreads * it;
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const bool ok = k0 + r < s.n2 && cbase + g8 * 8 < s.n3;
+        rag_shift(v[it * RB + r], (k0 + r) * s.n3 + cbase, g8 * 8, last, ok);
+      }
+    }
+  }
+  if (cbase + CW > s.n3) {
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      const u32x4 keep = rag_keep(cbase + (threadIdx.x + kThreads * it) * 8, s.n3);
+#pragma unroll
+      for (int r = 0; r < RB; ++r) v[it * RB + r] &= keep;
+    }
+  }
+}
+
 template <int DT, bool MOM, int RB, int G, int NG, bool VEC>
 __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, uint32_t* ldsu) {
   constexpr int CW = kBChunkHalfs / RB;      // columns per chunk
@@ -371,6 +426,7 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
   const int stride = s.btab_stride;
   const int rg = threadIdx.x / SLOTS, bslot = threadIdx.x - rg * SLOTS;
   const int64_t k0 = static_cast<int64_t>(b_block<RB>(u, s.nB)) * RB;
+  const int64_t last = rag_last(s.n2, s.n3);      // ragged rows
   double acc[G][RBG], accw[G][RBG];
 #pragma unroll
   for (int g = 0; g < G; ++g) {
@@ -397,8 +453,7 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
         if (VEC) {
           ch.v[it * RB + r] = load8h_sel(s.B + (k0 + r) * s.n3 + col, ok, s.zero);
         } else {
-          ch.v[it * RB + r] = ok ? load8h(s.B + (k0 + r) * s.n3, col, s.n3, false)
-                                 : u32x4{0u, 0u, 0u, 0u};
+          ch.v[it * RB + r] = load8h_rag(s.B, (k0 + r) * s.n3 + cbase, g8 * 8, last, ok, s.zero);
         }
       }
       const uint8_t* sp = live ? s.bsign + cbase / 8 + g8 : static_cast<const uint8_t*>(s.zero);
@@ -433,7 +488,11 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
   };
 
   // Stage chunk c: signs v2(j) applied to the halves, columns and the sorted list into LDS.
-  auto stage = [&](Chunk& ch) {
+  auto stage = [&](Chunk& ch, int c) {
+    if (!VEC) {
+      const int64_t cbase = static_cast<int64_t>(c) * CW;
+      rag_chunk<RB, NI, CW>(s, k0, cbase, last, ch.v);
+    }
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const int g8 = threadIdx.x + kThreads * it;
@@ -608,7 +667,7 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
     Chunk ch;
     issue(ch, 0);
     for (int c = 0; c < s.TB; ++c) {
-      stage(ch);
+      stage(ch, c);
       int qb[G], qe[G];
 #pragma unroll
       for (int g = 0; g < G; ++g) {
@@ -623,7 +682,7 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
     for (int c = 0; c < s.TB; ++c) {
       Chunk ch;
       issue(ch, c);
-      stage(ch);
+      stage(ch, c);
       fold(c, ch.qb, ch.qe);
       __syncthreads();
     }
@@ -703,6 +762,7 @@ __device__ void b_unit_probe4(const StreamArgs& s, int u, uint16_t* L, uint32_t*
   const int t = threadIdx.x;
   const int rbk = b_block<RB>(u, s.nB);
   const int64_t k0 = static_cast<int64_t>(rbk) * RB;
+  const int64_t last = rag_last(s.n2, s.n3);          // ragged rows
   int32_t* boffL = reinterpret_cast<int32_t*>(L + CW * RB + 8);   // after the zero column
   float* PL = reinterpret_cast<float*>(L);       // group partials, over the staged data
   if (t < RB) L[CW * RB + t] = 0;                // zero sentinel column (slot CW)
@@ -730,8 +790,7 @@ __device__ void b_unit_probe4(const StreamArgs& s, int u, uint16_t* L, uint32_t*
         if (VEC) {
           v[it][r] = load8h_sel(s.B + (k0 + r) * s.n3 + col, ok, s.zero);
         } else {
-          v[it][r] = ok ? load8h(s.B + (k0 + r) * s.n3, col, s.n3, false)
-                        : u32x4{0u, 0u, 0u, 0u};
+          v[it][r] = load8h_rag(s.B, (k0 + r) * s.n3 + cbase, g8 * 8, last, ok, s.zero);
         }
       }
       sb[it] = s.bsign[cbase / 8 + g8];          // the sign bits cover whole chunks
@@ -748,6 +807,7 @@ __device__ void b_unit_probe4(const StreamArgs& s, int u, uint16_t* L, uint32_t*
       const int b = t + kThreads * j;
       bo[j] = b <= m ? s.boff[static_cast<int64_t>(c) * (m + 1) + b] : 0;
     }
+    if (!VEC) rag_chunk<RB, NI, CW>(s, k0, cbase, last, &v[0][0]);
 #pragma unroll
     for (int it = 0; it < NI; ++it) {
       const int g8 = t + kThreads * it;
@@ -837,6 +897,27 @@ __device__ void b_unit_probe4(const StreamArgs& s, int u, uint16_t* L, uint32_t*
 // (staged in LDS with the row loads): S_C[a, b] += sum v2(j) colsum[j] (T_C with w_j, R_C from
 // the row-weighted sums).  One partial per tile group.
 
+// Ragged rows of C: as rag_rows, for the group's rows rows[q].
+template <int U>
+__device__ __forceinline__ void rag_rows_c(const StreamArgs& s, const int64_t (&rows)[U],
+                                           int64_t tcol, int lane, bool lane_ok, int r0, int nr,
+                                           int64_t last, f32x4 (&v0)[U], f32x4 (&v1)[U]) {
+  bool near = false;
+#pragma unroll
+  for (int q = 0; q < U; ++q) near |= rag_near(rows[q] * s.n3 + tcol, kColTile - 8, last);
+  if (near) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      rag_shift(v0[q], v1[q], rows[q] * s.n3 + tcol, lane * 8, last,
+                r0 + q < nr && lane_ok);
+    }
+  }
+  if (tcol + kColTile > s.n3) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) rag_mask(v0[q], v1[q], tcol + lane * 8, s.n3);
+  }
+}
+
 template <bool MOM, int G, bool VEC>
 __device__ void c_unit(const StreamArgs& s, int u, double* lds, uint16_t* tabL) {
   // rows in flight per wave: 4 at m > 2048 (a few rows per bucket, and the fold's 16 buckets
@@ -849,6 +930,7 @@ __device__ void c_unit(const StreamArgs& s, int u, double* lds, uint16_t* tabL) 
   const int t1 = (t0 + s.tg < s.TC) ? t0 + s.tg : s.TC;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int32_t* prow = s.perm + static_cast<int64_t>(a) * s.cap;
+  const int64_t last = rag_last(s.n1, s.n3);        // ragged rows
   const bool patched = s.patch_rowptr != nullptr;
   double* comb = lds;                          // [2][4][8][64]
   double* cs = lds + (MOM ? 4096 : 2048);      // column sums [513] (+ weighted at 520)
@@ -860,7 +942,8 @@ __device__ void c_unit(const StreamArgs& s, int u, double* lds, uint16_t* tabL) 
     fT[g] = 0.0;
   }
   for (int t = t0; t < t1; ++t) {
-    const int64_t col = static_cast<int64_t>(t) * kColTile + lane * 8;
+    const int64_t tcol = static_cast<int64_t>(t) * kColTile;
+    const int64_t col = tcol + lane * 8;
     const bool lane_ok = col < s.n3;
     // fold tables of this tile, loaded with the first rows
     const int stride = s.ctab_stride;
@@ -908,13 +991,12 @@ __device__ void c_unit(const StreamArgs& s, int u, double* lds, uint16_t* tabL) 
           sw[q] = MOM ? sg[q] * static_cast<double>(row + 1) * s.inv_l1 : 0.0;
           if (VEC) {
             load8f_sel(s.C + row * s.n3 + col, ok && lane_ok, s.zero, v0[q], v1[q]);
-          } else if (ok) {
-            load8f(s.C + row * s.n3, col, s.n3, false, v0[q], v1[q]);
           } else {
-            v0[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-            v1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+            load8f_rag(s.C, row * s.n3 + tcol, lane * 8, last, ok && lane_ok, s.zero, v0[q],
+                       v1[q]);
           }
         }
+        if (!VEC) rag_rows_c<U>(s, rows, tcol, lane, lane_ok, r0, nr, last, v0, v1);
         if (patched) {
 #pragma unroll
           for (int q = 0; q < U; ++q) {
@@ -1023,6 +1105,7 @@ __device__ void c_unit_wt(const StreamArgs& s, int u, double* lds, uint16_t* tab
   const int t1 = (t0 + s.tg < s.TC) ? t0 + s.tg : s.TC;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int32_t* prow = s.perm + static_cast<int64_t>(a) * s.cap;
+  const int64_t last = rag_last(s.n1, s.n3);        // ragged rows
   const bool patched = s.patch_rowptr != nullptr;
   double* cs = lds;                    // [4][520]: the four tiles' column sums and sentinels
   double* csw = lds + 4 * 520;         // [4][520]: row-weighted column sums (moments)
@@ -1039,7 +1122,8 @@ __device__ void c_unit_wt(const StreamArgs& s, int u, double* lds, uint16_t* tab
   for (int tq = t0; tq < t1; tq += 4) {
     const int t = tq + w;
     const bool tok = t < t1;
-    const int64_t col = static_cast<int64_t>(t) * kColTile + lane * 8;
+    const int64_t tcol = static_cast<int64_t>(t) * kColTile;
+    const int64_t col = tcol + lane * 8;
     const bool lane_ok = tok && col < s.n3;
     // this wave's tile list (512 entries, 8 per lane), loaded with the first rows
     u32x4 tv = {0u, 0u, 0u, 0u};
@@ -1071,13 +1155,12 @@ __device__ void c_unit_wt(const StreamArgs& s, int u, double* lds, uint16_t* tab
             sw[q] = MOM ? sg[q] * static_cast<double>(row + 1) * s.inv_l1 : 0.0;
             if (VEC) {
               load8f_sel(s.C + row * s.n3 + col, ok && lane_ok, s.zero, v0[q], v1[q]);
-            } else if (ok && lane_ok) {
-              load8f(s.C + row * s.n3, col, s.n3, false, v0[q], v1[q]);
             } else {
-              v0[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-              v1[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+              load8f_rag(s.C, row * s.n3 + tcol, lane * 8, last, ok && lane_ok, s.zero, v0[q],
+                         v1[q]);
             }
           }
+          if (!VEC) rag_rows_c<U>(s, rows, tcol, lane, lane_ok, r0, nr, last, v0, v1);
           if (patched) {
 #pragma unroll
             for (int q = 0; q < U; ++q) {
@@ -1317,23 +1400,17 @@ hipError_t launch_probe_pipe(const StreamArgs& s, const ProductArgs& prod, const
                              int nprod, int has_dec, int dt, int xb, size_t lds_bytes,
                              hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   const bool vec = s.vec_a && s.vec_b && s.vec_c;
-  // (one-tile-per-wave C work-groups only with whole 16-byte rows, as in the stream kernel)
-  if (vec && s.wt_c) {
-    return dt == 1 ? pipe_dispatch<1, true, true>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st,
-                                                  e0, e1)
-                   : pipe_dispatch<0, true, true>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st,
-                                                  e0, e1);
-  }
+  // the C work-groups' form follows the stream kernel's: deferred and ordinary probes agree bit
+  // for bit
+#define FPSK_PIPE(DT_, VEC_, WTC_) \
+  pipe_dispatch<DT_, VEC_, WTC_>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st, e0, e1)
   if (dt == 1) {
-    return vec ? pipe_dispatch<1, true, false>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st, e0,
-                                               e1)
-               : pipe_dispatch<1, false, false>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st,
-                                                e0, e1);
+    if (s.wt_c) return vec ? FPSK_PIPE(1, true, true) : FPSK_PIPE(1, false, true);
+    return vec ? FPSK_PIPE(1, true, false) : FPSK_PIPE(1, false, false);
   }
-  return vec ? pipe_dispatch<0, true, false>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st, e0,
-                                             e1)
-             : pipe_dispatch<0, false, false>(s, prod, dec, nprod, has_dec, xb, lds_bytes, st, e0,
-                                              e1);
+  if (s.wt_c) return vec ? FPSK_PIPE(0, true, true) : FPSK_PIPE(0, false, true);
+  return vec ? FPSK_PIPE(0, true, false) : FPSK_PIPE(0, false, false);
+#undef FPSK_PIPE
 }
 
 // ----------------------------------------------------------------------------------------
@@ -1345,8 +1422,8 @@ static hipError_t stream_dispatch(const StreamArgs& s, int rb, int g, int ng, si
   const int grid = s.nA + s.nB + s.nC;
   if (grid <= 0) return hipSuccess;
   const bool vec = s.vec_a && s.vec_b && s.vec_c;
-  // one-tile-per-wave C work-groups: their own instances (at G = 1 only the probe's aligned one)
-  const bool wtc = s.wt_c && !(g == 1 && (MOM || !vec));
+  // one-tile-per-wave C work-groups: their own instances (at G = 1 only the probe's)
+  const bool wtc = s.wt_c && !(g == 1 && MOM);
 #define FPSK_STREAM_LAUNCH(RB_, G_, NG_, VEC_, WTC_)                                          \
   launch_k(stream_kernel<DT, MOM, RB_, G_, NG_, VEC_, WTC_>, dim3(grid), dim3(kThreads), lds, st, \
            e0, e1, s)
@@ -1369,10 +1446,7 @@ static hipError_t stream_dispatch(const StreamArgs& s, int rb, int g, int ng, si
     return hipGetLastError();                                                                 \
   }
   if constexpr (!MOM) {
-    if (wtc && rb == 4 && g == 1 && ng == 1) {
-      FPSK_STREAM_LAUNCH(4, 1, 1, true, true);
-      return hipGetLastError();
-    }
+    FPSK_STREAM_WTC_CASE(4, 1, 1)
   }
   FPSK_STREAM_WTC_CASE(4, 2, 1)
   FPSK_STREAM_WTC_CASE(8, 2, 1)
