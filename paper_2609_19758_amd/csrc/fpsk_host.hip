@@ -382,6 +382,27 @@ fpsketch_status dev_alloc_zero(DevBuf& b, size_t bytes) {
   return FPSK_OK;
 }
 
+// Host memory that kernels read and write in place (pinned, coherent); grows, never shrinks.
+struct HostBuf {
+  void* p = nullptr;
+  size_t bytes = 0;
+};
+
+void host_free(HostBuf& b) {
+  if (b.p != nullptr) (void)hipHostFree(b.p);
+  b.p = nullptr;
+  b.bytes = 0;
+}
+
+fpsketch_status host_alloc(HostBuf& b, size_t bytes) {
+  if (b.p != nullptr && b.bytes >= bytes) return FPSK_OK;
+  host_free(b);
+  const size_t n = std::max<size_t>(bytes + bytes / 2, 4096);
+  FPSK_HIP(hipHostMalloc(&b.p, n, hipHostMallocMapped | hipHostMallocCoherent));
+  b.bytes = n;
+  return FPSK_OK;
+}
+
 void dev_free(DevBuf& b) {
   if (b.p != nullptr) (void)hipFree(b.p);
   b.p = nullptr;
@@ -719,10 +740,13 @@ struct fpsketch_ctx {
   // localize / diagnostic workspaces
   DevRound aux_round;
   Workspace aux_ws;
-  DevBuf scan_counts, scan_rows, scan_base, scan_out, samples, patch_rowptr, patch_col,
-      patch_val, rc_coords, rc_gamma, rc_abs, rc_c;
-  // localize rounds on the device: selection state and histogram, peel list, candidates
-  DevBuf sel_state, sel_hist, peel_list, cands, cand_count;
+  DevBuf scan_counts, scan_total, scan_rows, scan_base, scan_out, samples, patch_rowptr,
+      patch_col, patch_val, rc_coords, rc_gamma, rc_abs;
+  // localize rounds on the device: selection state, histograms and kept keys, candidates
+  DevBuf sel_state, sel_hist, sel_cand, cands, cand_count;
+  // host memory the kernels read and write: figures and candidates of a step (HostHead, then up
+  // to kPublish candidates), the peel list, the recheck's coordinates and results
+  HostBuf host_head, host_peel, host_rc;
   // the selected buckets of a round and their moment sketches (R then T)
   DevBuf mo_list, mo_rt;
   // apply step: the record list and the re-probe's statistics and scratch noise sum
@@ -1034,58 +1058,88 @@ fpsketch_status check_matrices(const fpsketch_ctx* c, const void* A, const void*
   return FPSK_OK;
 }
 
-// rms-hat(C): strided samples on the device, statistics on the host (Sec. III-G).
-fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, hipStream_t st, double* out) {
+// At most this many candidates of a round reach the host through host_head.
+constexpr uint32_t kPublish = 1024;
+
+fpsk::HostHead* head(fpsketch_ctx* c) { return static_cast<fpsk::HostHead*>(c->host_head.p); }
+
+fpsk::Cand* published(fpsketch_ctx* c) {
+  return reinterpret_cast<fpsk::Cand*>(static_cast<char*>(c->host_head.p) +
+                                       sizeof(fpsk::HostHead));
+}
+
+fpsketch_status ensure_selection(fpsketch_ctx* c) {
+  FPSK_TRY(dev_alloc_zero(c->sel_state, sizeof(fpsk::SelState)));
+  FPSK_TRY(dev_alloc_zero(c->sel_hist, 2 * 4096 * sizeof(uint32_t)));
+  FPSK_TRY(dev_alloc(c->sel_cand, fpsk::kSelGather * sizeof(uint64_t)));
+  FPSK_TRY(dev_alloc(c->cand_count, sizeof(uint32_t)));
+  return host_alloc(c->host_head, sizeof(fpsk::HostHead) + kPublish * sizeof(fpsk::Cand));
+}
+
+fpsk::SelArgs sel_args(fpsketch_ctx* c) {
+  fpsk::SelArgs a{};
+  a.st = as<fpsk::SelState>(c->sel_state);
+  a.hist = as<uint32_t>(c->sel_hist);
+  a.cand = as<uint64_t>(c->sel_cand);
+  return a;
+}
+
+// Enqueues rms-hat(C) (Sec. III-G: strided samples, clipped at 64 x their median) and publishes
+// it in head(c) with the exact scan's total (`found`, may be null) and two doubles at `sigma`.
+fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, uint32_t* found,
+                               const double* sigma, hipStream_t st) {
   const int64_t total = c->n1 * c->n3;
   const int64_t stride = std::max<int64_t>(1, total / 65536);
   const int64_t count = (total + stride - 1) / stride;
+  FPSK_TRY(ensure_selection(c));
   FPSK_TRY(dev_alloc(c->samples, static_cast<size_t>(count) * sizeof(float)));
-  FPSK_HIP(fpsk::launch_sample(C, stride, count, as<float>(c->samples), st));
-  std::vector<float> h(static_cast<size_t>(count));
-  FPSK_HIP(hipMemcpyAsync(h.data(), c->samples.p, h.size() * sizeof(float),
-                          hipMemcpyDeviceToHost, st));
-  FPSK_HIP(hipStreamSynchronize(st));
-  *out = rms_hat_from_samples(h.data(), count);
+  fpsk::SelArgs a = sel_args(c);
+  a.samp = as<float>(c->samples);
+  a.C = C;
+  a.stride = stride;
+  a.n = count;
+  fpsk::SetupArgs u{};
+  u.found = found;
+  u.sigma = sigma;
+  u.head = head(c);
+  FPSK_HIP(fpsk::launch_rms(a, u, st));
   return FPSK_OK;
 }
 
-// Recheck a list of coordinates: gamma, sum |A||B| and C_ij.
+// Recheck a list of coordinates: gamma, sum |A||B| and C_ij, for coords (n pairs at the start of
+// host_rc, see recheck_coords_at) into the arrays after them.
+struct Recheck {
+  int64_t* coords;
+  double* gamma;
+  double* abssum;
+  float* cval;
+};
+
+fpsketch_status recheck_buffers(fpsketch_ctx* c, size_t n, Recheck& r) {
+  FPSK_TRY(host_alloc(c->host_rc, n * (2 * sizeof(int64_t) + 2 * sizeof(double) + sizeof(float))));
+  r.coords = static_cast<int64_t*>(c->host_rc.p);
+  r.gamma = reinterpret_cast<double*>(r.coords + 2 * n);
+  r.abssum = r.gamma + n;
+  r.cval = reinterpret_cast<float*>(r.abssum + n);
+  return FPSK_OK;
+}
+
 fpsketch_status recheck_coords(fpsketch_ctx* c, const void* A, const void* B, const float* C,
-                               const std::vector<int64_t>& coords, std::vector<double>& gamma,
-                               std::vector<double>& abssum, std::vector<float>& cval,
-                               hipStream_t st) {
-  const int n = static_cast<int>(coords.size() / 2);
-  gamma.assign(n, 0.0);
-  abssum.assign(n, 0.0);
-  cval.assign(n, 0.0f);
+                               const Recheck& r, size_t n, hipStream_t st) {
   if (n == 0) return FPSK_OK;
-  FPSK_TRY(dev_alloc(c->rc_coords, coords.size() * sizeof(int64_t)));
-  FPSK_TRY(dev_alloc(c->rc_gamma, n * sizeof(double)));
-  FPSK_TRY(dev_alloc(c->rc_abs, n * sizeof(double)));
-  FPSK_TRY(dev_alloc(c->rc_c, n * sizeof(float)));
-  FPSK_HIP(hipMemcpyAsync(c->rc_coords.p, coords.data(), coords.size() * sizeof(int64_t),
-                          hipMemcpyHostToDevice, st));
   FPSK_HIP(fpsk::launch_recheck(static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B),
                                 c->transb ? 1 : c->n3, c->transb ? c->n2 : 1,
-                                C, c->n2, c->n3, c->dt == FPSK_BF16 ? 1 : 0,
-                                as<int64_t>(c->rc_coords), n, as<double>(c->rc_gamma),
-                                as<double>(c->rc_abs), as<float>(c->rc_c), st));
-  FPSK_HIP(hipMemcpyAsync(gamma.data(), c->rc_gamma.p, n * sizeof(double), hipMemcpyDeviceToHost,
-                          st));
-  FPSK_HIP(hipMemcpyAsync(abssum.data(), c->rc_abs.p, n * sizeof(double), hipMemcpyDeviceToHost,
-                          st));
-  FPSK_HIP(hipMemcpyAsync(cval.data(), c->rc_c.p, n * sizeof(float), hipMemcpyDeviceToHost, st));
+                                C, c->n2, c->n3, c->dt == FPSK_BF16 ? 1 : 0, r.coords,
+                                static_cast<int>(n), r.gamma, r.abssum, r.cval, st));
   FPSK_HIP(hipStreamSynchronize(st));
   return FPSK_OK;
 }
 
 // Exact scan (Sec. III-I): first K entries in row-major order that are non-finite or above
-// fp32max/16 in magnitude.
+// fp32max/16 in magnitude, from the row counts of launch_scan_count.
 fpsketch_status exact_scan(fpsketch_ctx* c, const float* C, int32_t K, hipStream_t st,
                            std::vector<int64_t>& coords) {
   coords.clear();
-  FPSK_TRY(dev_alloc(c->scan_counts, static_cast<size_t>(c->n1) * sizeof(int32_t)));
-  FPSK_HIP(fpsk::launch_scan_count(C, c->n1, c->n3, as<int32_t>(c->scan_counts), st));
   std::vector<int32_t> counts(static_cast<size_t>(c->n1));
   FPSK_HIP(hipMemcpyAsync(counts.data(), c->scan_counts.p, counts.size() * sizeof(int32_t),
                           hipMemcpyDeviceToHost, st));
@@ -1153,43 +1207,40 @@ fpsketch_status sketch_round(fpsketch_ctx* c, uint64_t seed, int round, int m, b
   return FPSK_OK;
 }
 
-// One sketch pass at m whose S stays in the auxiliary workspace, with the moment factors and
-// C-grid partials when mom (R and T are then formed at selected buckets by launch_moments_at);
-// max|A|, max|B| to host.
+// Enqueues one sketch pass at m whose S stays in the auxiliary workspace, with the moment
+// factors and C-grid partials when mom (R and T are then formed at selected buckets by
+// launch_moments_at).
 fpsketch_status sketch_round_device(fpsketch_ctx* c, uint64_t seed, int round, int m, bool mom,
                                     const void* A, const void* B, const float* C,
                                     const int32_t* prow, const int32_t* pcol, const float* pval,
-                                    hipStream_t st, HostRound& HR, double* maxA, double* maxB) {
+                                    hipStream_t st, HostRound& HR) {
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, mom, c->transb);
   build_round(seed, round, c->n1, c->n3, m, d.cwb, mom, c->transb, HR);
   FPSK_TRY(upload_round(HR, d.cwb, c->aux_round, st));
   FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb));
-  FPSK_TRY(run_pass(c, c->aux_round, c->aux_ws, A, B, C, mom, 0, nullptr, prow, pcol, pval, st,
-                    nullptr, nullptr, nullptr, BSide::kStream, false));
-  std::vector<float> mp(static_cast<size_t>(d.nA + d.nB));
-  FPSK_HIP(hipMemcpyAsync(mp.data(), c->aux_ws.maxpart.p, mp.size() * sizeof(float),
-                          hipMemcpyDeviceToHost, st));
-  FPSK_HIP(hipStreamSynchronize(st));
-  float ma = 0.0f, mb = 0.0f;
-  for (int i = 0; i < d.nA; ++i) ma = std::fmax(ma, mp[i]);
-  for (int i = 0; i < d.nB; ++i) mb = std::fmax(mb, mp[d.nA + i]);
-  *maxA = ma;
-  *maxB = mb;
-  return FPSK_OK;
+  return run_pass(c, c->aux_round, c->aux_ws, A, B, C, mom, 0, nullptr, prow, pcol, pval, st,
+                  nullptr, nullptr, nullptr, BSide::kStream, false);
 }
 
-// sigma_MAD = 1.4826 median(|S - median S|) of the m^2 buckets in the auxiliary workspace,
-// selected exactly on the device (the host rule's values: even counts take the mean of the two
-// middle order statistics).
-fpsketch_status device_mad_sigma(fpsketch_ctx* c, int64_t mm, hipStream_t st, double* sigma) {
-  FPSK_TRY(dev_alloc(c->sel_state, sizeof(fpsk::SelState)));
-  FPSK_TRY(dev_alloc_zero(c->sel_hist, 256 * sizeof(uint32_t)));
-  FPSK_HIP(fpsk::launch_median_mad(as<double>(c->aux_ws.S), mm, as<fpsk::SelState>(c->sel_state),
-                                   as<uint32_t>(c->sel_hist), st));
-  fpsk::SelState h{};
-  FPSK_HIP(hipMemcpyAsync(&h, c->sel_state.p, sizeof(h), hipMemcpyDeviceToHost, st));
-  FPSK_HIP(hipStreamSynchronize(st));
-  *sigma = 1.4826 * h.mad;
+// Enqueues the noise of the buckets in the auxiliary workspace (sigma_MAD = 1.4826 median(|S -
+// median S|), selected exactly on the device; even counts take the mean of the two middle order
+// statistics) and the round's thresholds and cut at search radius r.
+fpsketch_status round_cut_device(fpsketch_ctx* c, int r, hipStream_t st) {
+  FPSK_TRY(ensure_selection(c));
+  const Decomp& d = c->aux_ws.d;
+  fpsk::SelArgs a = sel_args(c);
+  a.S = as<double>(c->aux_ws.S);
+  a.n = static_cast<int64_t>(d.m) * d.m;
+  fpsk::RoundArgs g{};
+  g.maxpart = as<float>(c->aux_ws.maxpart);
+  g.nA = d.nA;
+  g.nB = d.nB;
+  g.c_n2 = c->p.c_valid * static_cast<double>(c->n2) * std::ldexp(1.0, -23);
+  g.mx = static_cast<double>(std::max(c->n1, c->n3));
+  g.radius = std::max(static_cast<double>(r), 0.5);
+  g.count = as<uint32_t>(c->cand_count);
+  g.head = head(c);
+  FPSK_HIP(fpsk::launch_round_cut(a, g, st));
   return FPSK_OK;
 }
 
@@ -1370,10 +1421,12 @@ void fpsketch_destroy(fpsketch_ctx* c) {
   free_round(c->aux_round);
   free_workspace(c->aux_ws);
   for (Workspace& w : c->pipe_ws) free_workspace(w);
-  for (DevBuf* b : {&c->stats, &c->sigma_acc, &c->zero, &c->tiny, &c->scan_counts, &c->scan_rows, &c->scan_base,
+  for (HostBuf* b : {&c->host_head, &c->host_peel, &c->host_rc}) host_free(*b);
+  for (DevBuf* b : {&c->stats, &c->sigma_acc, &c->zero, &c->tiny, &c->scan_counts,
+                    &c->scan_total, &c->scan_rows, &c->scan_base,
                     &c->scan_out, &c->samples, &c->patch_rowptr, &c->patch_col, &c->patch_val,
-                    &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->rc_c, &c->sel_state,
-                    &c->sel_hist, &c->peel_list, &c->cands, &c->cand_count, &c->apply_list,
+                    &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->sel_state,
+                    &c->sel_hist, &c->sel_cand, &c->cands, &c->cand_count, &c->apply_list,
                     &c->mo_list, &c->mo_rt,
                     &c->reprobe_stats, &c->reprobe_acc, &c->qcache, &c->maxb_cache}) {
     dev_free(*b);
@@ -1737,14 +1790,14 @@ fpsketch_status fpsketch_calibrate_noise(fpsketch_ctx* c, const void* C, fpsketc
   FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
-  double acc[2] = {0.0, 0.0};
-  FPSK_HIP(hipMemcpyAsync(acc, c->sigma_acc.p, sizeof(acc), hipMemcpyDeviceToHost, st));
+  FPSK_TRY(rms_hat_device(c, static_cast<const float*>(C), nullptr, as<double>(c->sigma_acc),
+                          st));
   FPSK_HIP(hipStreamSynchronize(st));
+  const double acc[2] = {head(c)->sigma, head(c)->extra};
   const double sigma_bar = acc[1] > 0 ? acc[0] / acc[1] : std::nan("");
   int32_t rebuilt = 0;
   if (acc[1] > 0) {
-    double rms = 0;
-    FPSK_TRY(rms_hat_device(c, static_cast<const float*>(C), st, &rms));
+    const double rms = head(c)->rms;
     int32_t m_new = c->m;
     recalibrate(c->n1, c->n3, c->m, sigma_bar, rms, c->p, &m_new, &rebuilt);
     if (rebuilt && m_new > fpsk::kMaxM) {
@@ -1785,12 +1838,23 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   std::vector<Found> F;
 
   // 1. Exact scan and absolute recompute (Sec. III-I; Algorithm 2).
+  // rms-hat(C) and the last probe's noise are read with the scan's total: one wait.
+  FPSK_TRY(dev_alloc(c->scan_counts, static_cast<size_t>(c->n1) * sizeof(int32_t)));
+  FPSK_TRY(dev_alloc_zero(c->scan_total, sizeof(uint32_t)));
+  FPSK_HIP(fpsk::launch_scan_count(Cf, c->n1, c->n3, as<int32_t>(c->scan_counts),
+                                   as<uint32_t>(c->scan_total), st));
+  FPSK_TRY(rms_hat_device(c, Cf, as<uint32_t>(c->scan_total), as<double>(c->stats), st));
+  FPSK_HIP(hipStreamSynchronize(st));
+  const double rms = head(c)->rms;
+  double sigma = head(c)->sigma;
   std::vector<int64_t> abs_coords;
-  FPSK_TRY(exact_scan(c, Cf, K, st, abs_coords));
-  std::vector<double> g, ab;
-  std::vector<float> cv;
-  FPSK_TRY(recheck_coords(c, A, B, Cf, abs_coords, g, ab, cv, st));
+  if (head(c)->found > 0) FPSK_TRY(exact_scan(c, Cf, K, st, abs_coords));
   const size_t n_abs = abs_coords.size() / 2;
+  Recheck rc{};
+  FPSK_TRY(recheck_buffers(c, n_abs, rc));
+  std::copy(abs_coords.begin(), abs_coords.end(), rc.coords);
+  FPSK_TRY(recheck_coords(c, A, B, Cf, rc, n_abs, st));
+  const std::vector<double> g(rc.gamma, rc.gamma + n_abs);
   for (size_t t = 0; t < n_abs; ++t) {
     F.push_back({abs_coords[2 * t], abs_coords[2 * t + 1], g[t], 1, 0});
   }
@@ -1823,20 +1887,12 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   }
 
   // 2. Plan from the measured noise (Sec. III-G).
-  double rms = 0.0;
-  FPSK_TRY(rms_hat_device(c, Cf, st, &rms));
-  double sigma = std::nan("");
-  if (sigma_from_probe) {
-    double stt[8];
-    FPSK_HIP(hipMemcpyAsync(stt, c->stats.p, sizeof(stt), hipMemcpyDeviceToHost, st));
-    FPSK_HIP(hipStreamSynchronize(st));
-    sigma = stt[0];
-  } else {
+  if (!sigma_from_probe) {
     HostRound HR0;
-    double ma0 = 0.0, mb0 = 0.0;
-    FPSK_TRY(sketch_round_device(c, seed, 0, c->m, false, A, B, Cf, prow, pcol, pval, st, HR0,
-                                 &ma0, &mb0));
-    FPSK_TRY(device_mad_sigma(c, static_cast<int64_t>(c->m) * c->m, st, &sigma));
+    FPSK_TRY(sketch_round_device(c, seed, 0, c->m, false, A, B, Cf, prow, pcol, pval, st, HR0));
+    FPSK_TRY(round_cut_device(c, 0, st));
+    FPSK_HIP(hipStreamSynchronize(st));
+    sigma = head(c)->sigma;
   }
   const PlanOut plan = plan_localize(c->n1, c->n2, c->n3, c->dt, c->m, sigma, rms, c->p);
   if (plan.m_loc > fpsk::kMaxM) return fail(FPSK_ESHAPE, "m_loc beyond 4096");
@@ -1864,53 +1920,62 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   const double L1 = static_cast<double>(c->L1), L3 = static_cast<double>(c->L3);
   for (int t = 1; t <= c->p.rounds; ++t) {
     HostRound HR;
-    double maxA = 0, maxB = 0;
-    FPSK_TRY(sketch_round_device(c, seed, t, m, true, A, B, Cf, prow, pcol, pval, st, HR, &maxA,
-                                 &maxB));
-    tau = c->p.c_valid * static_cast<double>(c->n2) * std::ldexp(1.0, -23) * maxA * maxB;
+    FPSK_TRY(sketch_round_device(c, seed, t, m, true, A, B, Cf, prow, pcol, pval, st, HR));
     const int64_t mm = static_cast<int64_t>(m) * m;
     double* dS = as<double>(c->aux_ws.S);
     // peel every finite fault confirmed so far (Sec. III-H), in order, on the device (S here;
     // R and T at the selected buckets below)
-    std::vector<fpsk::PeelEntry> peel;
+    FPSK_TRY(host_alloc(c->host_peel, F.size() * sizeof(fpsk::PeelEntry)));
+    fpsk::PeelEntry* peel = static_cast<fpsk::PeelEntry*>(c->host_peel.p);
+    int npeel = 0;
     for (const Found& f : F) {
       if (f.absolute) continue;
       const int64_t o = static_cast<int64_t>(HR.h1[f.i]) * m + HR.h2[f.j];
       const double sv = static_cast<double>(HR.v1[f.i]) * HR.v2[f.j] * f.delta;
-      peel.push_back({o, sv, sv * static_cast<double>(f.i + 1) / L1,
-                      sv * static_cast<double>(f.j + 1) / L3});
+      peel[npeel++] = {o, sv, sv * static_cast<double>(f.i + 1) / L1,
+                       sv * static_cast<double>(f.j + 1) / L3};
     }
-    if (!peel.empty()) {
-      FPSK_TRY(dev_alloc(c->peel_list, peel.size() * sizeof(fpsk::PeelEntry)));
-      FPSK_HIP(hipMemcpyAsync(c->peel_list.p, peel.data(), peel.size() * sizeof(fpsk::PeelEntry),
-                              hipMemcpyHostToDevice, st));
-      FPSK_HIP(fpsk::launch_peel(dS, nullptr, nullptr, as<fpsk::PeelEntry>(c->peel_list),
-                                 static_cast<int>(peel.size()), st));
-    }
-    double sig = 0.0;
-    FPSK_TRY(device_mad_sigma(c, mm, st, &sig));
-    const double tau_c = std::min(tau, 2.0 * sig);
-    const double tau_d = static_cast<double>(std::max(c->n1, c->n3)) * sig /
-                         std::max(static_cast<double>(r), 0.5);
-    const double cut = std::max(tau_c, tau_d);
+    FPSK_HIP(fpsk::launch_peel(dS, peel, npeel, st));
+    FPSK_TRY(round_cut_device(c, r, st));
     // buckets with |S| > cut, with their sketches; by |S| descending, then bucket index
     constexpr uint32_t kCandCap = 1u << 20;
     FPSK_TRY(dev_alloc(c->cands, static_cast<size_t>(kCandCap) * sizeof(fpsk::Cand)));
-    FPSK_TRY(dev_alloc(c->cand_count, sizeof(uint32_t)));
-    FPSK_HIP(hipMemsetAsync(c->cand_count.p, 0, sizeof(uint32_t), st));
-    FPSK_HIP(fpsk::launch_above(dS, nullptr, nullptr, mm, cut, as<fpsk::Cand>(c->cands),
+    FPSK_HIP(fpsk::launch_above(dS, mm, as<fpsk::SelState>(c->sel_state), as<fpsk::Cand>(c->cands),
                                 kCandCap, as<uint32_t>(c->cand_count), st));
-    uint32_t ncand = 0;
-    FPSK_HIP(hipMemcpyAsync(&ncand, c->cand_count.p, sizeof(ncand), hipMemcpyDeviceToHost, st));
+    // R and T (Eq. 2) at the candidates, with the peel terms; with no more than publish of them
+    // they come to the host whole, in one wait
+    const uint32_t publish = std::min<uint32_t>(kPublish, static_cast<uint32_t>(K));
+    fpsk::MomentsAtArgs ma{};
+    ma.P = as<float>(c->aux_ws.P);
+    ma.Pw = as<float>(c->aux_ws.Pw);
+    ma.Q = as<float>(c->aux_ws.Q);
+    ma.Qw = as<float>(c->aux_ws.Qw);
+    ma.partR = as<double>(c->aux_ws.partR);
+    ma.partT = as<double>(c->aux_ws.partT);
+    ma.peel = npeel > 0 ? peel : nullptr;
+    ma.npeel = npeel;
+    ma.m = m;
+    ma.ldp = c->aux_ws.d.ldp;
+    ma.kact = c->aux_ws.d.kact;
+    ma.npc = c->aux_ws.d.npc;
+    ma.cands = as<fpsk::Cand>(c->cands);
+    ma.count = as<uint32_t>(c->cand_count);
+    ma.out = published(c);
+    ma.head = head(c);
+    FPSK_HIP(fpsk::launch_moments_at(ma, static_cast<int>(publish), st));
     FPSK_HIP(hipStreamSynchronize(st));
+    tau = head(c)->tau;
+    const double cut = head(c)->cut;
+    const uint32_t ncand = head(c)->found;
     std::vector<fpsk::Cand> above;
-    if (ncand <= kCandCap) {
+    const bool whole = ncand <= publish;
+    if (whole) {
+      above.assign(published(c), published(c) + ncand);
+    } else if (ncand <= kCandCap) {
       above.resize(ncand);
-      if (ncand > 0) {
-        FPSK_HIP(hipMemcpyAsync(above.data(), c->cands.p, ncand * sizeof(fpsk::Cand),
-                                hipMemcpyDeviceToHost, st));
-        FPSK_HIP(hipStreamSynchronize(st));
-      }
+      FPSK_HIP(hipMemcpyAsync(above.data(), c->cands.p, ncand * sizeof(fpsk::Cand),
+                              hipMemcpyDeviceToHost, st));
+      FPSK_HIP(hipStreamSynchronize(st));
     } else {
       // more candidates than the buffer holds: scan the whole grid on the host
       std::vector<double> S(mm);
@@ -1925,8 +1990,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
       return x.o < y.o;
     });
     if (static_cast<int64_t>(above.size()) > K) above.resize(K);
-    // R and T (Eq. 2) at the top-K buckets only, with the peel terms
-    if (!above.empty()) {
+    if (!whole) {
       const size_t na = above.size();
       std::vector<int64_t> ol(na);
       for (size_t q = 0; q < na; ++q) ol[q] = above[q].o;
@@ -1934,23 +1998,11 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
       FPSK_TRY(dev_alloc(c->mo_rt, 2 * na * sizeof(double)));
       FPSK_HIP(hipMemcpyAsync(c->mo_list.p, ol.data(), na * sizeof(int64_t),
                               hipMemcpyHostToDevice, st));
-      fpsk::MomentsAtArgs g{};
-      g.P = as<float>(c->aux_ws.P);
-      g.Pw = as<float>(c->aux_ws.Pw);
-      g.Q = as<float>(c->aux_ws.Q);
-      g.Qw = as<float>(c->aux_ws.Qw);
-      g.partR = as<double>(c->aux_ws.partR);
-      g.partT = as<double>(c->aux_ws.partT);
-      g.o = as<int64_t>(c->mo_list);
-      g.peel = peel.empty() ? nullptr : as<fpsk::PeelEntry>(c->peel_list);
-      g.npeel = static_cast<int>(peel.size());
-      g.r = as<double>(c->mo_rt);
-      g.t = g.r + na;
-      g.m = m;
-      g.ldp = c->aux_ws.d.ldp;
-      g.kact = c->aux_ws.d.kact;
-      g.npc = c->aux_ws.d.npc;
-      FPSK_HIP(fpsk::launch_moments_at(g, static_cast<int>(na), st));
+      ma.cands = nullptr;
+      ma.o = as<int64_t>(c->mo_list);
+      ma.r = as<double>(c->mo_rt);
+      ma.t = ma.r + na;
+      FPSK_HIP(fpsk::launch_moments_at(ma, static_cast<int>(na), st));
       std::vector<double> rt(2 * na);
       FPSK_HIP(hipMemcpyAsync(rt.data(), c->mo_rt.p, 2 * na * sizeof(double),
                               hipMemcpyDeviceToHost, st));
@@ -1991,10 +2043,11 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
         coords.push_back(j);
       }
     }
-    std::vector<double> gg, aa;
-    std::vector<float> cc;
-    FPSK_TRY(recheck_coords(c, A, B, Cf, coords, gg, aa, cc, st));
-    n_rechecked += static_cast<int32_t>(coords.size() / 2);
+    const size_t nc = coords.size() / 2;
+    FPSK_TRY(recheck_buffers(c, nc, rc));
+    std::copy(coords.begin(), coords.end(), rc.coords);
+    FPSK_TRY(recheck_coords(c, A, B, Cf, rc, nc, st));
+    n_rechecked += static_cast<int32_t>(nc);
     std::vector<char> alive(live.size(), 1);
     size_t nlive = live.size();
     for (const auto& od : offs) {
@@ -2006,8 +2059,8 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
         const int64_t kk = key(i, j);
         if (inF.count(kk)) continue;
         const int32_t sl = slot.at(kk);
-        const double diff = gg[sl] - static_cast<double>(cc[sl]);
-        const double bound = c->p.c_valid * std::ldexp(1.0, -23) * aa[sl];
+        const double diff = rc.gamma[sl] - static_cast<double>(rc.cval[sl]);
+        const double bound = c->p.c_valid * std::ldexp(1.0, -23) * rc.abssum[sl];
         if (std::fabs(diff) > bound) {
           F.push_back({i, j, diff, 0, t});
           inF.insert(kk);

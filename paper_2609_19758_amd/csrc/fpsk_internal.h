@@ -145,12 +145,10 @@ hipError_t launch_stream(const StreamArgs& s, int dt, bool moments, int rb, int 
 hipError_t launch_product(const ProductArgs& a, int ts, bool kw, bool moments, hipStream_t st,
                           hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_scan_count(const float* C, int64_t n1, int64_t n3, int32_t* counts,
-                             hipStream_t st);
+                             uint32_t* total, hipStream_t st);
 hipError_t launch_scan_extract(const float* C, int64_t n3, const int32_t* rows,
                                const int32_t* base, int nrows, int32_t cap, int64_t* out,
                                hipStream_t st);
-hipError_t launch_sample(const float* C, int64_t stride, int64_t count, float* out,
-                         hipStream_t st);
 // B[k][j] is read at B + k * bsk + j * bsj (n3, 1 for B as stored; 1, n2 for W = B^T).
 // dst (m x ldp) = transpose of src (n2 x mq), columns past m and rows past n2 left alone.
 hipError_t launch_transpose_q(const float* src, float* dst, int m, int64_t n2, int mq, int ldp,
@@ -159,18 +157,55 @@ hipError_t launch_recheck(const uint16_t* A, const uint16_t* B, int64_t bsk, int
                           const float* C, int64_t n2, int64_t n3, int dt, const int64_t* coords,
                           int n, double* gamma, double* abssum, float* cval, hipStream_t st);
 
-// Order statistics of a bucket grid on the device (the MAD and candidate scan of a localize
-// round).  The selection state lives in device memory.
+// Order statistics on the device (the MAD of a localize round, the median inside rms-hat).  The
+// selection state lives in device memory; histograms are zero between selections.
+constexpr int kSelSmall = 1 << 14;       // keys that one work-group selects from in one launch
+constexpr uint32_t kSelGather = 1 << 16; // keys sharing two digits that are kept
 struct SelState {
-  uint64_t prefix;     // key bits fixed so far
-  uint64_t k;          // rank sought among the keys that match the prefix
-  uint64_t next;       // smallest key above the selected one
-  uint32_t count_eq;   // keys equal to the selected one (after the last digit)
-  int32_t pass;        // digits fixed so far
-  double med;          // median of S
-  double mad;          // median of |S - med|
+  uint64_t pref, k;          // first digit, rank within it
+  uint64_t pref2, k2, cnt2;  // both digits, rank within them, keys that share them
+  uint64_t count;            // keys selected from
+  uint64_t next;             // smallest key above those sharing both digits
+  uint64_t lo, not_hi;       // range of those when they are too many to keep
+  uint32_t ncand;
+  uint32_t pad;
+  double med, mad;
+  double sigma, tau, cut;    // the round's noise, analytic threshold and candidate cut
 };
-struct PeelEntry {     // S[o] -= ds, R[o] -= dr, T[o] -= dt
+struct SelArgs {
+  const double* S;       // the bucket grid (n values) ...
+  float* samp;           // ... or the samples C[i stride], i < n
+  const float* C;
+  int64_t stride, n;
+  SelState* st;
+  uint32_t* hist;        // 2 x 4096
+  uint64_t* cand;        // kSelGather
+  int dev;               // 1: |S - state->med| in place of S
+};
+// Figures of a localize step in host memory (written by a kernel, read after the stream is
+// waited for).
+struct HostHead {
+  double rms;            // rms-hat(C)
+  double sigma, extra;   // the round's sigma_MAD; for the setup the words SetupArgs names
+  double tau, cut;
+  uint32_t found;        // buckets above the cut; for the setup entries of the exact scan
+  uint32_t pad;
+};
+struct RoundArgs {
+  const float* maxpart;
+  int nA, nB;
+  double c_n2;           // c n2 2^-23
+  double mx;             // max(n1, n3)
+  double radius;         // max(r, 0.5)
+  uint32_t* count;       // candidate counter, cleared
+  HostHead* head;        // may be null
+};
+struct SetupArgs {
+  uint32_t* found;       // exact scan's total (may be null), cleared once published
+  const double* sigma;   // two doubles to publish (may be null)
+  HostHead* head;
+};
+struct PeelEntry {     // S[o] -= ds, R[o] -= dr, T[o] -= dt (in host memory the device reads)
   int64_t o;
   double ds, dr, dt;
 };
@@ -183,11 +218,18 @@ struct MomentsAtArgs {
   const float* Qw;
   const double* partR;
   const double* partT;
-  const int64_t* o;
   const PeelEntry* peel;
+  int m, ldp, kact, npc, npeel;
+  // either a list of buckets and outputs r, t ...
+  const int64_t* o;
   double* r;
   double* t;
-  int m, ldp, kact, npc, npeel;
+  // ... or the *count candidates the device found, written whole to out (host memory) with their
+  // number in head->found; nothing is formed when there are more than the launch's n
+  const struct Cand* cands;
+  const uint32_t* count;
+  struct Cand* out;
+  HostHead* head;
 };
 hipError_t launch_moments_at(const MomentsAtArgs& g, int n, hipStream_t st);
 struct ApplyEntry {    // one record of the apply step: C[o] <- d, or C[o] + d
@@ -211,18 +253,16 @@ struct Cand {          // a bucket above the cut with its three sketches
   int64_t o;
   double s, r, t;
 };
-// Applies the peel list in order (one thread), so the result equals sequential subtraction.
-hipError_t launch_peel(double* S, double* R, double* T, const PeelEntry* list, int n,
-                       hipStream_t st);
-// st->med = median of S[0 .. n), then st->mad = median of |S - med| (even counts: the mean of
-// the two middle order statistics; NaN orders above +inf).  hist: 256 words of scratch, zero
-// on entry and on return.
-hipError_t launch_median_mad(const double* S, int64_t n, SelState* st, uint32_t* hist,
-                             hipStream_t st_);
-// Appends (o, S, R, T) of every bucket with |S[o]| > cut to out (at most cap; *count receives
+hipError_t launch_peel(double* S, const PeelEntry* list, int n, hipStream_t st);
+// Median of S[0 .. n), MAD (even counts: the mean of the two middle order statistics; NaN orders
+// above +inf), then the round's cut (RoundArgs) into the state.
+hipError_t launch_round_cut(const SelArgs& a, const RoundArgs& r, hipStream_t st);
+// rms-hat of C from its n samples, and what else the host reads with it.
+hipError_t launch_rms(const SelArgs& a, const SetupArgs& u, hipStream_t st);
+// Appends (o, S) of every bucket with |S[o]| > state->cut to out (at most cap; *count receives
 // the number found, which may exceed cap); the order of the entries is unspecified.
-hipError_t launch_above(const double* S, const double* R, const double* T, int64_t n,
-                        double cut, Cand* out, uint32_t cap, uint32_t* count, hipStream_t st);
+hipError_t launch_above(const double* S, int64_t n, const SelState* state, Cand* out,
+                        uint32_t cap, uint32_t* count, hipStream_t st);
 
 hipError_t launch_read(const void* src, int64_t bytes, uint32_t* out, int grid, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, int grid, hipStream_t st);

@@ -531,19 +531,33 @@ __device__ __forceinline__ bool is_absolute_entry(float x) {
   return !(fabsf(x) <= static_cast<float>(kHugeLimit));
 }
 
+// Entries of the exact scan in each row of C, one work-group per row, added to *total.  Bound by
+// the read of C: 16-byte loads at any alignment, four in flight a thread (4-byte loads read
+// 16384^2 at 3.7 TB/s, 290 us; now 6.9 TB/s, 155 us).
 __global__ __launch_bounds__(kThreads) void scan_count_kernel(const float* C, int64_t n3,
-                                                              int32_t* counts) {
-  __shared__ int red[kThreads];
+                                                              int32_t* counts, uint32_t* total) {
+  __shared__ int red[kThreads / 64];
   const int64_t row = blockIdx.x;
+  const float* c = C + row * n3;
+  const int64_t n4 = n3 / 4;
   int cnt = 0;
-  for (int64_t j = threadIdx.x; j < n3; j += kThreads) cnt += is_absolute_entry(C[row * n3 + j]);
-  red[threadIdx.x] = cnt;
-  __syncthreads();
-  for (int st = kThreads / 2; st > 0; st >>= 1) {
-    if (threadIdx.x < st) red[threadIdx.x] += red[threadIdx.x + st];
-    __syncthreads();
+#pragma unroll 4
+  for (int64_t j = threadIdx.x; j < n4; j += kThreads) {
+    const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_a4*>(c + 4 * j));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) cnt += is_absolute_entry(v[e]);
   }
-  if (threadIdx.x == 0) counts[row] = red[0];
+  const int64_t j = 4 * n4 + threadIdx.x;
+  if (j < n3) cnt += is_absolute_entry(c[j]);
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) cnt += __shfl_xor(cnt, d, 64);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = cnt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const int n = red[0] + red[1] + red[2] + red[3];
+    counts[row] = n;
+    if (n > 0) atomicAdd(total, static_cast<uint32_t>(n));
+  }
 }
 
 __global__ __launch_bounds__(kThreads) void scan_extract_kernel(const float* C, int64_t n3,
@@ -580,10 +594,21 @@ __global__ __launch_bounds__(kThreads) void scan_extract_kernel(const float* C, 
 }
 
 // ----------------------------------------------------------------------------------------
-// Order statistics of the bucket grid (the MAD of Sec. III-E and the candidate scan of
-// Algorithm 1) by radix selection over order-preserving 64-bit keys: eight passes of 8-bit
-// digits, each a histogram of the keys that match the digits fixed so far, then one work-group
-// that fixes the next digit.  Exact: the selected key is the k-th smallest.
+// Order statistics: the median and MAD of a bucket grid (Sec. III-E, Algorithm 1) and the median
+// inside rms-hat(C) (Sec. III-G), by radix selection over order-preserving 64-bit keys in 12-bit
+// digits.  Exact: the selected key is the k-th smallest.  Up to kSelSmall values one work-group
+// does it all in one launch.  Above that the first two digits are histograms over the whole chip,
+// each launch deriving the digit before it from the finished histogram by itself (a scan of 4096
+// bins per work-group, instead of a launch of one work-group between two passes); the third pass
+// gathers the keys that share those 24 bits - a few thousand of 16.7 M for a noise grid - and one
+// work-group finishes among them.  Bound by launches at small grids and by the three reads of the
+// grid at m = 4096.  Eight passes of 8-bit digits with a step launch each took 38 launches per
+// median and MAD: 60 buckets a side 68 us of kernels and 38 launches, 432 a side 113 us, 4096 a
+// side 670 us; now 16 us in one launch, 61 us and 190 us.
+
+constexpr int kSelThreads = 1024;
+constexpr int kSelBits = 12;
+constexpr int kSelBins = 1 << kSelBits;
 
 // Key order equals the order of the doubles (-0 just below +0); NaN sorts above +inf.
 __device__ __forceinline__ uint64_t order_key(double x) {
@@ -597,117 +622,429 @@ __device__ __forceinline__ double key_value(uint64_t k) {
   return __builtin_bit_cast(double, u);
 }
 
-// MODE 0: keys of S; MODE 1: keys of |S - st->med|
-template <int MODE>
-__device__ __forceinline__ uint64_t sel_key(const double* S, int64_t i, double med) {
-  const double x = MODE == 0 ? S[i] : fabs(S[i] - med);
-  return order_key(x);
+constexpr int kSelRank = 256;        // keys ranked against each other (more: another digit)
+
+struct SelLds {
+  uint32_t hist[kSelBins];
+  uint64_t cand[kSelRank];
+  uint64_t wmin[kSelThreads / 64];
+  uint32_t wsum[kSelThreads / 64];
+  uint32_t bin, cnt, ncand, total;
+  uint64_t k, sel, next;
+};
+
+__device__ __forceinline__ uint64_t sel_mask(int fixed) {
+  return fixed == 0 ? 0ull : ~0ull << (64 - fixed);
 }
 
-__global__ __launch_bounds__(kThreads) void sel_init_kernel(SelState* st, uint64_t k) {
-  st->prefix = 0;
-  st->k = k;
-  st->next = ~0ull;
-  st->count_eq = 0;
-  st->pass = 0;
-}
-
-template <int MODE>
-__global__ __launch_bounds__(kThreads) void sel_hist_kernel(const double* S, int64_t n,
-                                                            const SelState* st, uint32_t* hist) {
-  __shared__ uint32_t h[256];
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int shift = 56 - 8 * st->pass;
-  const uint64_t hmask = shift == 56 ? 0ull : (~0ull << (shift + 8));
-  const uint64_t pref = st->prefix;
-  const double med = st->med;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kThreads) {
-    const uint64_t key = sel_key<MODE>(S, i, med);
-    if ((key & hmask) == pref) atomicAdd(&h[(key >> shift) & 255u], 1u);
+// Bin of the histogram that holds rank k (l.bin), the rank within it (l.k) and its count (l.cnt);
+// l.total is the count of all bins.  k >= total selects nothing (the last bin).
+__device__ void sel_scan(SelLds& l, uint64_t k) {
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  uint32_t c[4], sum = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    c[j] = l.hist[4 * t + j];
+    sum += c[j];
   }
+  uint32_t incl = sum;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t o = __shfl_up(incl, d, 64);
+    if (lane >= d) incl += o;
+  }
+  if (lane == 63) l.wsum[w] = incl;
   __syncthreads();
-  if (h[threadIdx.x] != 0) atomicAdd(&hist[threadIdx.x], h[threadIdx.x]);
+  uint32_t before = 0, total = 0;
+  for (int i = 0; i < kSelThreads / 64; ++i) {
+    const uint32_t v = l.wsum[i];
+    if (i < w) before += v;
+    total += v;
+  }
+  uint64_t e = before + incl - sum;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if ((k >= e && k < e + c[j]) || (t == kSelThreads - 1 && j == 3 && k >= total)) {
+      l.bin = 4 * t + j;
+      l.cnt = c[j];
+      l.k = k >= total ? 0 : k - e;
+    }
+    e += c[j];
+  }
+  if (t == 0) l.total = total;
+  __syncthreads();
 }
 
-// One work-group of 256: the digit whose cumulative count passes k (the first bin b with
-// k < count(bins 0..b), or bin 255 when none before it does); clears the histogram.  The
-// cumulative counts come from an inclusive scan across the 256 threads.
-__global__ __launch_bounds__(kThreads) void sel_step_kernel(SelState* st, uint32_t* hist) {
-  static_assert(kThreads == 256, "one thread per digit");
-  __shared__ uint32_t h[256];
+__device__ __forceinline__ void sel_zero(SelLds& l) {
+#pragma unroll
+  for (int j = 0; j < kSelBins / kSelThreads; ++j) l.hist[threadIdx.x + kSelThreads * j] = 0;
+  __syncthreads();
+}
+
+__device__ uint64_t sel_block_min(SelLds& l, uint64_t v) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) {
+    const uint64_t o = __shfl_xor(static_cast<unsigned long long>(v), d, 64);
+    v = o < v ? o : v;
+  }
+  if ((threadIdx.x & 63) == 0) l.wmin[threadIdx.x >> 6] = v;
+  __syncthreads();
+  uint64_t r = l.wmin[0];
+  for (int i = 1; i < kSelThreads / 64; ++i) r = l.wmin[i] < r ? l.wmin[i] : r;
+  __syncthreads();
+  return r;
+}
+
+// One work-group: the k-th smallest (l.sel) of the keys key(0 .. n) that share the top `fixed`
+// bits of pref (cnt of them; k counts among those), and in l.next the key of rank k + 1 (~0 when
+// there is none).
+template <typename Key>
+__device__ void block_select(SelLds& l, Key key, int64_t n, uint64_t pref, int fixed,
+                             uint64_t cnt, uint64_t k) {
   const int t = threadIdx.x;
-  const uint64_t k = st->k;
-  const uint32_t mine = hist[t];
-  h[t] = mine;
-  hist[t] = 0;
-  __syncthreads();
-  for (int d = 1; d < 256; d <<= 1) {
-    const uint32_t add = t >= d ? h[t - d] : 0u;
-    __syncthreads();
-    h[t] += add;
-    __syncthreads();
-  }
-  const uint64_t incl = h[t], excl = incl - mine;
-  const bool hit = t == 255 ? excl <= k : (excl <= k && k < incl);
-  if (hit) {
-    const int shift = 56 - 8 * st->pass;
-    st->prefix |= static_cast<uint64_t>(t) << shift;
-    st->k = k - excl;
-    st->count_eq = mine;
-    st->pass += 1;
-  }
-}
-
-// Smallest key above the selected one (the upper middle element when it differs).
-template <int MODE>
-__global__ __launch_bounds__(kThreads) void sel_next_kernel(const double* S, int64_t n,
-                                                            SelState* st) {
-  __shared__ uint64_t red[kThreads];
-  const uint64_t sel = st->prefix;
-  const double med = st->med;
-  uint64_t best = ~0ull;
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
-       i += static_cast<int64_t>(gridDim.x) * kThreads) {
-    const uint64_t key = sel_key<MODE>(S, i, med);
-    if (key > sel && key < best) best = key;
-  }
-  red[threadIdx.x] = best;
-  __syncthreads();
-  for (int w = kThreads / 2; w > 0; w >>= 1) {
-    if (static_cast<int>(threadIdx.x) < w && red[threadIdx.x + w] < red[threadIdx.x]) {
-      red[threadIdx.x] = red[threadIdx.x + w];
+  while (cnt > kSelRank && fixed < 64) {
+    const int wd = 64 - fixed < kSelBits ? 64 - fixed : kSelBits;
+    const int shift = 64 - fixed - wd;
+    const uint64_t hm = sel_mask(fixed);
+    sel_zero(l);
+#pragma unroll 4
+    for (int64_t i = t; i < n; i += kSelThreads) {
+      const uint64_t x = key(i);
+      if ((x & hm) == pref) atomicAdd(&l.hist[(x >> shift) & ((1u << wd) - 1)], 1u);
     }
     __syncthreads();
+    sel_scan(l, k);
+    pref |= static_cast<uint64_t>(l.bin) << shift;
+    fixed += wd;
+    cnt = l.cnt;
+    k = l.k;
+    __syncthreads();
   }
-  if (threadIdx.x == 0 && red[0] != ~0ull) atomicMin(reinterpret_cast<unsigned long long*>(&st->next), static_cast<unsigned long long>(red[0]));
+  const uint64_t hm = sel_mask(fixed);
+  const uint64_t top = pref | ~hm;
+  const bool few = cnt <= kSelRank;
+  if (t == 0) {
+    l.ncand = 0;
+    l.sel = pref;          // every bit fixed and more equal keys than candidates
+    l.next = ~0ull;
+  }
+  __syncthreads();
+  uint64_t mn = ~0ull;
+#pragma unroll 4
+  for (int64_t i = t; i < n; i += kSelThreads) {
+    const uint64_t x = key(i);
+    if ((x & hm) == pref) {
+      if (few) l.cand[atomicAdd(&l.ncand, 1u)] = x;
+    } else if (x > top && x < mn) {
+      mn = x;
+    }
+  }
+  mn = sel_block_min(l, mn);
+  if (few) {
+    const int nc = static_cast<int>(cnt);
+    if (t < nc) {
+      const uint64_t x = l.cand[t];
+      uint64_t less = 0;
+#pragma unroll 8
+      for (int j = 0; j < nc; ++j) {
+        const uint64_t y = l.cand[j];
+        less += y < x || (y == x && j < t);
+      }
+      if (less == k) l.sel = x;
+      if (less == k + 1) l.next = x;
+    }
+    if (t == 0 && k + 1 >= cnt) l.next = mn;
+  } else if (t == 0) {
+    l.next = k + 1 < cnt ? pref : mn;
+  }
+  __syncthreads();
 }
 
-// The median from the selected order statistic(s): x_(n/2) for odd n, else the mean of
-// x_(n/2 - 1) (selected) and x_(n/2) (the same key while equal keys remain, else the next).
+// What a selection reads.  kSelGrid: S, or |S - median| for the MAD (a.dev, at run time: the MAD's
+// launches then find the median's code in the instruction caches); kSelAbs: the finite |samples|.
+enum SelMode { kSelGrid = 0, kSelAbs = 1 };
+
 template <int MODE>
-__global__ __launch_bounds__(kThreads) void sel_final_kernel(SelState* st, int64_t n) {
-  const double lo = key_value(st->prefix);
-  double v = lo;
-  if (n % 2 == 0) {
-    const double hi = (st->k + 1 < st->count_eq) ? lo : key_value(st->next);
-    v = 0.5 * (lo + hi);
-  }
-  if (MODE == 0) {
-    st->med = v;
+__device__ __forceinline__ uint64_t sel_key(const SelArgs& a, int64_t i, double med) {
+  if constexpr (MODE == kSelAbs) {
+    return order_key(fabs(static_cast<double>(a.samp[i])));
   } else {
-    st->mad = v;
+    const double x = a.S[i];
+    return order_key(a.dev ? fabs(x - med) : x);
   }
 }
 
-__global__ __launch_bounds__(1) void peel_kernel(double* S, double* R, double* T,
-                                                 const PeelEntry* list, int n) {
-  for (int q = 0; q < n; ++q) {
-    const PeelEntry e = list[q];
-    S[e.o] -= e.ds;
-    if (R != nullptr) R[e.o] -= e.dr;
-    if (T != nullptr) T[e.o] -= e.dt;
+// Keys of samples that count (non-finite ones sort above every finite one and are left out).
+template <int MODE>
+__device__ __forceinline__ bool sel_counts(uint64_t key) {
+  return MODE != kSelAbs || key < 0xFFF0000000000000ull;
+}
+
+__device__ __forceinline__ uint64_t lower_rank(uint64_t n) {
+  return n == 0 ? 0 : (n % 2 ? n / 2 : n / 2 - 1);
+}
+
+__device__ __forceinline__ double median_value(uint64_t sel, uint64_t next, uint64_t n) {
+  const double lo = key_value(sel);
+  return n % 2 ? lo : 0.5 * (lo + key_value(next));
+}
+
+__device__ __forceinline__ void sel_flush(const SelLds& l, uint32_t* hist) {
+#pragma unroll
+  for (int j = 0; j < kSelBins / kSelThreads; ++j) {
+    const int b = threadIdx.x + kSelThreads * j;
+    if (l.hist[b] != 0) atomicAdd(&hist[b], l.hist[b]);
+  }
+}
+
+// Pass 1: histogram of the top digit (kSelAbs also takes the samples from C).
+template <int MODE>
+__global__ __launch_bounds__(kSelThreads) void sel_hist1_kernel(SelArgs a) {
+  __shared__ SelLds l;
+  sel_zero(l);
+  const double med = a.st->med;
+#pragma unroll 4
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kSelThreads + threadIdx.x; i < a.n;
+       i += static_cast<int64_t>(gridDim.x) * kSelThreads) {
+    if (MODE == kSelAbs) a.samp[i] = a.C[i * a.stride];
+    const uint64_t key = sel_key<MODE>(a, i, med);
+    if (sel_counts<MODE>(key)) atomicAdd(&l.hist[key >> (64 - kSelBits)], 1u);
+  }
+  __syncthreads();
+  sel_flush(l, a.hist);
+}
+
+__device__ __forceinline__ void sel_load(SelLds& l, const uint32_t* hist) {
+#pragma unroll
+  for (int j = 0; j < kSelBins / kSelThreads; ++j) {
+    const int b = threadIdx.x + kSelThreads * j;
+    l.hist[b] = hist[b];
+  }
+  __syncthreads();
+}
+
+// Pass 2: the first digit from pass 1's histogram, then the second digit's histogram.
+template <int MODE>
+__global__ __launch_bounds__(kSelThreads) void sel_hist2_kernel(SelArgs a) {
+  __shared__ SelLds l;
+  sel_load(l, a.hist);
+  uint64_t n = static_cast<uint64_t>(a.n);
+  if (MODE == kSelAbs) {           // the finite samples: the histogram's total
+    sel_scan(l, 0);
+    n = l.total;
+    __syncthreads();
+  }
+  sel_scan(l, lower_rank(n));
+  const uint64_t pref = static_cast<uint64_t>(l.bin) << (64 - kSelBits);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.st->pref = pref;
+    a.st->k = l.k;
+    a.st->count = n;
+    a.st->ncand = 0;
+    a.st->next = ~0ull;
+    a.st->lo = ~0ull;
+    a.st->not_hi = ~0ull;
+  }
+  __syncthreads();
+  sel_zero(l);
+  const uint64_t hm = sel_mask(kSelBits);
+  const double med = a.st->med;
+#pragma unroll 4
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kSelThreads + threadIdx.x; i < a.n;
+       i += static_cast<int64_t>(gridDim.x) * kSelThreads) {
+    const uint64_t key = sel_key<MODE>(a, i, med);
+    if ((key & hm) == pref && sel_counts<MODE>(key)) {
+      atomicAdd(&l.hist[(key >> (64 - 2 * kSelBits)) & (kSelBins - 1)], 1u);
+    }
+  }
+  __syncthreads();
+  sel_flush(l, a.hist + kSelBins);
+}
+
+// Pass 3: the second digit, then the keys that share both digits (at most kSelGather of them are
+// kept) and the smallest key above them.
+template <int MODE>
+__global__ __launch_bounds__(kSelThreads) void sel_gather_kernel(SelArgs a) {
+  __shared__ SelLds l;
+  sel_load(l, a.hist + kSelBins);
+  sel_scan(l, a.st->k);
+  const uint64_t pref = a.st->pref | static_cast<uint64_t>(l.bin) << (64 - 2 * kSelBits);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    a.st->pref2 = pref;
+    a.st->k2 = l.k;
+    a.st->cnt2 = l.cnt;
+  }
+  const uint64_t hm = sel_mask(2 * kSelBits);
+  const uint64_t top = pref | ~hm;
+  const double med = a.st->med;
+  const bool keep = l.cnt <= kSelGather;
+  uint64_t mn = ~0ull, lo = ~0ull, hi = 0;
+  __syncthreads();
+#pragma unroll 4
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * kSelThreads + threadIdx.x; i < a.n;
+       i += static_cast<int64_t>(gridDim.x) * kSelThreads) {
+    const uint64_t key = sel_key<MODE>(a, i, med);
+    if (!sel_counts<MODE>(key)) continue;
+    if ((key & hm) == pref) {
+      if (keep) a.cand[atomicAdd(&a.st->ncand, 1u)] = key;
+      lo = key < lo ? key : lo;
+      hi = key > hi ? key : hi;
+    } else if (key > top && key < mn) {
+      mn = key;
+    }
+  }
+  auto fold = [](uint64_t* p, uint64_t v) {
+    if (threadIdx.x == 0 && v != ~0ull) {
+      atomicMin(reinterpret_cast<unsigned long long*>(p), static_cast<unsigned long long>(v));
+    }
+  };
+  fold(&a.st->next, sel_block_min(l, mn));
+  if (!keep) {             // ties: their range, with the largest as its complement
+    fold(&a.st->lo, sel_block_min(l, lo));
+    fold(&a.st->not_hi, sel_block_min(l, ~hi));
+  }
+}
+
+// The finish of a selection over the chip, by one work-group: l.sel and l.next; clears the
+// histograms for the next selection.
+template <int MODE>
+__device__ void sel_finish(SelLds& l, const SelArgs& a, double med) {
+  const uint64_t cnt = a.st->cnt2, k = a.st->k2, pref = a.st->pref2, above = a.st->next;
+  if (cnt <= kSelGather) {
+    const uint64_t* cand = a.cand;
+    block_select(l, [cand](int64_t i) { return cand[i]; }, static_cast<int64_t>(cnt), pref,
+                 2 * kSelBits, cnt, k);
+    if (threadIdx.x == 0 && l.next == ~0ull) l.next = above;
+  } else if (a.st->lo == ~a.st->not_hi) {
+    // one value (a grid of zeros, as exact products leave)
+    if (threadIdx.x == 0) {
+      l.sel = a.st->lo;
+      l.next = k + 1 < cnt ? a.st->lo : above;
+    }
+  } else {
+    // a cluster beyond the candidate buffer: over all keys again
+    const SelArgs b = a;
+    block_select(l, [b, med](int64_t i) {
+      const uint64_t key = sel_key<MODE>(b, i, med);
+      return sel_counts<MODE>(key) ? key : ~0ull;
+    }, a.n, pref, 2 * kSelBits, cnt, k);
+  }
+  for (int j = threadIdx.x; j < 2 * kSelBins; j += kSelThreads) a.hist[j] = 0;
+  __syncthreads();
+}
+
+__global__ __launch_bounds__(kSelThreads) void sel_median_kernel(SelArgs a) {
+  __shared__ SelLds l;
+  sel_finish<kSelGrid>(l, a, 0.0);
+  if (threadIdx.x == 0) a.st->med = median_value(l.sel, l.next, static_cast<uint64_t>(a.n));
+}
+
+// The decisions of a localize round that follow its noise (Algorithm 1): sigma_MAD =
+// 1.4826 MAD, the analytic threshold from max|A| and max|B|, the cut max(tau_c, tau_d).
+__device__ void round_cut(const SelArgs& a, const RoundArgs& r, double mad, SelLds& l) {
+  const int t = threadIdx.x;
+  float ma = strided_max(r.maxpart, r.nA, t, kSelThreads, 0.0f);
+  float mb = strided_max(r.maxpart + r.nA, r.nB, t, kSelThreads, 0.0f);
+  // maxima of non-negative floats through their bit patterns, smallest of the complements
+  const uint64_t na = sel_block_min(l, ~static_cast<uint64_t>(__float_as_uint(ma)));
+  const uint64_t nb = sel_block_min(l, ~static_cast<uint64_t>(__float_as_uint(mb)));
+  if (t != 0) return;
+  const double max_a = __uint_as_float(static_cast<uint32_t>(~na));
+  const double max_b = __uint_as_float(static_cast<uint32_t>(~nb));
+  const double sig = 1.4826 * mad;
+  const double tau = r.c_n2 * max_a * max_b;
+  const double two = 2.0 * sig;
+  const double tau_c = two < tau ? two : tau;
+  const double tau_d = r.mx * sig / r.radius;
+  a.st->mad = mad;
+  a.st->sigma = sig;
+  a.st->tau = tau;
+  a.st->cut = tau_c < tau_d ? tau_d : tau_c;
+  *r.count = 0;
+  if (r.head != nullptr) {
+    r.head->sigma = sig;
+    r.head->tau = tau;
+    r.head->cut = a.st->cut;
+  }
+}
+
+__global__ __launch_bounds__(kSelThreads) void sel_mad_kernel(SelArgs a, RoundArgs r) {
+  __shared__ SelLds l;
+  sel_finish<kSelGrid>(l, a, a.st->med);
+  const double mad = median_value(l.sel, l.next, static_cast<uint64_t>(a.n));
+  __syncthreads();
+  round_cut(a, r, mad, l);
+}
+
+// Small grids: median, MAD and the round's cut in one launch of one work-group.
+__global__ __launch_bounds__(kSelThreads) void sel_small_kernel(SelArgs a, RoundArgs r) {
+  __shared__ SelLds l;
+  const uint64_t n = static_cast<uint64_t>(a.n);
+  SelArgs b = a;
+  double med = 0.0, mad = 0.0;
+  for (b.dev = 0; b.dev < 2; ++b.dev) {
+    const SelArgs c = b;
+    block_select(l, [c, med](int64_t i) { return sel_key<kSelGrid>(c, i, med); }, a.n, 0, 0, n,
+                 lower_rank(n));
+    mad = median_value(l.sel, l.next, n);
+    if (b.dev == 0) med = mad;
+    __syncthreads();
+  }
+  round_cut(a, r, mad, l);
+}
+
+// rms-hat(C) from the samples: magnitudes clipped at 64 x their median (finite samples only), and
+// the figures the host needs before a localization, published to host memory.
+__global__ __launch_bounds__(kSelThreads) void rms_kernel(SelArgs a, SetupArgs u) {
+  __shared__ SelLds l;
+  __shared__ double red[lds_reduce_doubles<kSelThreads, 1>()];
+  sel_finish<kSelAbs>(l, a, 0.0);
+  const uint64_t nf = a.st->count;
+  const double clip = 64.0 * median_value(l.sel, l.next, nf);
+  double acc[1] = {0.0};
+#pragma unroll 8
+  for (int64_t i = threadIdx.x; i < a.n; i += kSelThreads) {
+    const double x = fabs(static_cast<double>(a.samp[i]));
+    const double c = x < clip ? x : clip;
+    acc[0] += __builtin_isfinite(x) ? c * c : 0.0;
+  }
+  lds_reduce<kSelThreads, 1>(acc, red, 0u);
+  if (threadIdx.x == 0) {
+    u.head->rms = nf > 0 ? sqrt(acc[0] / static_cast<double>(nf)) : __builtin_nan("");
+    u.head->found = u.found != nullptr ? *u.found : 0u;
+    u.head->sigma = u.sigma != nullptr ? u.sigma[0] : 0.0;
+    u.head->extra = u.sigma != nullptr ? u.sigma[1] : 0.0;
+    if (u.found != nullptr) *u.found = 0;       // zero again for the next scan
+  }
+}
+
+// S[o] -= ds of a list, each bucket's entries in list order (one thread takes a bucket's first
+// entry and walks the rest), so the result equals sequential subtraction.  The list is read from
+// host memory once, into LDS, kPeelChunk entries at a time.
+constexpr int kPeelChunk = 512;
+
+__global__ __launch_bounds__(kPeelChunk) void peel_kernel(double* S, const PeelEntry* list,
+                                                          int n) {
+  __shared__ int64_t o[kPeelChunk];
+  __shared__ double d[kPeelChunk];
+  const int t = threadIdx.x;
+  for (int base = 0; base < n; base += kPeelChunk) {
+    const int c = n - base < kPeelChunk ? n - base : kPeelChunk;
+    if (t < c) {
+      o[t] = list[base + t].o;
+      d[t] = list[base + t].ds;
+    }
+    __syncthreads();
+    bool first = t < c;
+    for (int j = 0; j < t && first; ++j) first = o[j] != o[t];
+    if (first) {
+      double v = S[o[t]];
+      for (int j = t; j < c; ++j) {
+        if (o[j] == o[t]) v -= d[j];
+      }
+      S[o[t]] = v;
+    }
+    __syncthreads();
   }
 }
 
@@ -718,7 +1055,16 @@ __global__ __launch_bounds__(1) void peel_kernel(double* S, double* R, double* T
 __global__ __launch_bounds__(kThreads) void moments_at_kernel(MomentsAtArgs g) {
   __shared__ double red[lds_reduce_doubles<kThreads, 2>()];
   const int q = blockIdx.x;
-  const int64_t o = g.o[q];
+  int64_t o;
+  if (g.cands != nullptr) {
+    // candidates as the device found them: all of them, when they are few enough to publish
+    const uint32_t found = *g.count;
+    if (q == 0 && threadIdx.x == 0) g.head->found = found;
+    if (static_cast<uint32_t>(q) >= found || found > gridDim.x) return;
+    o = g.cands[q].o;
+  } else {
+    o = g.o[q];
+  }
   const int64_t a = o / g.m, b = o - (o / g.m) * g.m;
   const float* pw = g.Pw + a * g.ldp;
   const float* pp = g.P + a * g.ldp;
@@ -749,8 +1095,12 @@ __global__ __launch_bounds__(kThreads) void moments_at_kernel(MomentsAtArgs g) {
       v[1] -= g.peel[p].dt;
     }
   }
-  g.r[q] = v[0];
-  g.t[q] = v[1];
+  if (g.cands != nullptr) {
+    g.out[q] = Cand{o, g.cands[q].s, v[0], v[1]};
+  } else {
+    g.r[q] = v[0];
+    g.t[q] = v[1];
+  }
 }
 
 // Apply step of Algorithm 2: one thread per record (the coordinates are distinct).
@@ -763,24 +1113,19 @@ __global__ __launch_bounds__(kThreads) void apply_kernel(float* C, const ApplyEn
                       : static_cast<float>(static_cast<double>(C[e.o]) + e.d);
 }
 
-__global__ __launch_bounds__(kThreads) void above_kernel(const double* S, const double* R,
-                                                         const double* T, int64_t n, double cut,
-                                                         Cand* out, uint32_t cap,
-                                                         uint32_t* count) {
+__global__ __launch_bounds__(kThreads) void above_kernel(const double* S, int64_t n,
+                                                         const SelState* st, Cand* out,
+                                                         uint32_t cap, uint32_t* count) {
+  const double cut = st->cut;
+#pragma unroll 4
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x; i < n;
        i += static_cast<int64_t>(gridDim.x) * kThreads) {
     const double s = S[i];
     if (fabs(s) > cut) {
       const uint32_t p = atomicAdd(count, 1u);
-      if (p < cap) out[p] = Cand{i, s, R != nullptr ? R[i] : 0.0, T != nullptr ? T[i] : 0.0};
+      if (p < cap) out[p] = Cand{i, s, 0.0, 0.0};
     }
   }
-}
-
-__global__ __launch_bounds__(kThreads) void sample_kernel(const float* C, int64_t stride,
-                                                          int64_t count, float* out) {
-  const int64_t t = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
-  if (t < count) out[t] = C[t * stride];
 }
 
 // One wave per coordinate: gamma = sum_k A_ik B_kj and sum_k |A_ik B_kj|, exact products
@@ -884,9 +1229,9 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
 }
 
 hipError_t launch_scan_count(const float* C, int64_t n1, int64_t n3, int32_t* counts,
-                             hipStream_t st) {
+                             uint32_t* total, hipStream_t st) {
   hipLaunchKernelGGL(scan_count_kernel, dim3(static_cast<unsigned>(n1)), dim3(kThreads), 0, st,
-                     C, n3, counts);
+                     C, n3, counts, total);
   return hipGetLastError();
 }
 
@@ -899,18 +1244,9 @@ hipError_t launch_scan_extract(const float* C, int64_t n3, const int32_t* rows,
   return hipGetLastError();
 }
 
-hipError_t launch_sample(const float* C, int64_t stride, int64_t count, float* out,
-                         hipStream_t st) {
-  if (count <= 0) return hipSuccess;
-  const unsigned grid = static_cast<unsigned>((count + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL(sample_kernel, dim3(grid), dim3(kThreads), 0, st, C, stride, count, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_peel(double* S, double* R, double* T, const PeelEntry* list, int n,
-                       hipStream_t st) {
+hipError_t launch_peel(double* S, const PeelEntry* list, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(peel_kernel, dim3(1), dim3(1), 0, st, S, R, T, list, n);
+  hipLaunchKernelGGL(peel_kernel, dim3(1), dim3(kPeelChunk), 0, st, S, list, n);
   return hipGetLastError();
 }
 
@@ -920,25 +1256,41 @@ unsigned grid_for(int64_t n) {
   return static_cast<unsigned>(g < 1 ? 1 : (g > 1024 ? 1024 : g));
 }
 
+// Work-groups of a pass of the selection: 2 keys a thread (their loads are the pass), at most two
+// work-groups per CU.
+unsigned sel_grid(int64_t n) {
+  const int64_t g = (n + 2 * kSelThreads - 1) / (2 * kSelThreads);
+  return static_cast<unsigned>(g < 1 ? 1 : (g > 512 ? 512 : g));
+}
+
 template <int MODE>
-void select_median(const double* S, int64_t n, SelState* st, uint32_t* hist, hipStream_t s) {
-  const unsigned g = grid_for(n);
-  hipLaunchKernelGGL(sel_init_kernel, dim3(1), dim3(1), 0, s, st,
-                     static_cast<uint64_t>(n % 2 ? n / 2 : n / 2 - 1));
-  for (int p = 0; p < 8; ++p) {
-    hipLaunchKernelGGL(sel_hist_kernel<MODE>, dim3(g), dim3(kThreads), 0, s, S, n, st, hist);
-    hipLaunchKernelGGL(sel_step_kernel, dim3(1), dim3(kThreads), 0, s, st, hist);
-  }
-  if (n % 2 == 0) hipLaunchKernelGGL(sel_next_kernel<MODE>, dim3(g), dim3(kThreads), 0, s, S, n, st);
-  hipLaunchKernelGGL(sel_final_kernel<MODE>, dim3(1), dim3(1), 0, s, st, n);
+void sel_passes(const SelArgs& a, hipStream_t st) {
+  const dim3 g(sel_grid(a.n)), b(kSelThreads);
+  hipLaunchKernelGGL(sel_hist1_kernel<MODE>, g, b, 0, st, a);
+  hipLaunchKernelGGL(sel_hist2_kernel<MODE>, g, b, 0, st, a);
+  hipLaunchKernelGGL(sel_gather_kernel<MODE>, g, b, 0, st, a);
 }
 }  // namespace
 
-hipError_t launch_median_mad(const double* S, int64_t n, SelState* st, uint32_t* hist,
-                             hipStream_t s) {
-  if (n <= 0) return hipErrorInvalidValue;
-  select_median<0>(S, n, st, hist, s);
-  select_median<1>(S, n, st, hist, s);
+hipError_t launch_round_cut(const SelArgs& a0, const RoundArgs& r, hipStream_t st) {
+  SelArgs a = a0;
+  if (a.n <= 0) return hipErrorInvalidValue;
+  if (a.n <= kSelSmall) {
+    hipLaunchKernelGGL(sel_small_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
+    return hipGetLastError();
+  }
+  sel_passes<kSelGrid>(a, st);
+  hipLaunchKernelGGL(sel_median_kernel, dim3(1), dim3(kSelThreads), 0, st, a);
+  a.dev = 1;
+  sel_passes<kSelGrid>(a, st);
+  hipLaunchKernelGGL(sel_mad_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
+  return hipGetLastError();
+}
+
+hipError_t launch_rms(const SelArgs& a, const SetupArgs& u, hipStream_t st) {
+  if (a.n <= 0) return hipErrorInvalidValue;
+  sel_passes<kSelAbs>(a, st);
+  hipLaunchKernelGGL(rms_kernel, dim3(1), dim3(kSelThreads), 0, st, a, u);
   return hipGetLastError();
 }
 
@@ -982,10 +1334,10 @@ hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st)
   return hipGetLastError();
 }
 
-hipError_t launch_above(const double* S, const double* R, const double* T, int64_t n,
-                        double cut, Cand* out, uint32_t cap, uint32_t* count, hipStream_t st) {
-  hipLaunchKernelGGL(above_kernel, dim3(grid_for(n)), dim3(kThreads), 0, st, S, R, T, n, cut,
-                     out, cap, count);
+hipError_t launch_above(const double* S, int64_t n, const SelState* state, Cand* out,
+                        uint32_t cap, uint32_t* count, hipStream_t st) {
+  hipLaunchKernelGGL(above_kernel, dim3(grid_for(n)), dim3(kThreads), 0, st, S, n, state, out,
+                     cap, count);
   return hipGetLastError();
 }
 

@@ -1,0 +1,100 @@
+"""Device order statistics of a localization: the noise of a fresh sketch (1.4826 x MAD, exact
+selection: equal to numpy's on the same S) and rms-hat(C) (against the library's host rule and the
+oracle's), where the selection changes form: one work-group or the chip, ties and clusters beyond
+the kept keys, odd and even counts, samples that are not finite."""
+import math
+
+import numpy as np
+import pytest
+
+from oracle import fpsketch_oracle as o
+from gpu_util import gemm_f32, to_dev_f32, to_dev_half
+from paper_2609_19758_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fk():
+    from paper_2609_19758_amd import fpsketch
+    fpsketch.load()
+    return fpsketch
+
+
+def _mad(S):
+    return 1.4826 * float(np.median(np.abs(S - np.median(S))))
+
+
+def _fresh_sigma(fk, A, B, C, n1, n2, n3, fmt, m):
+    v = fk.Verifier(n1, n2, n3, fmt, m=m)
+    S = v.sketch(A, B, C, seed=21, rnd=0, m=m, moments=False)[0]
+    v.localize(A, B, C, seed=21, sigma_from_probe=False)
+    plan = v.plan()
+    v.close()
+    return plan, S
+
+
+# grids of one and a few values, around one work-group's limit (128^2), above the kept keys' 2^16
+@pytest.mark.parametrize("m", [1, 2, 3, 17, 127, 128, 129, 256, 257, 401])
+def test_fresh_noise_equals_mad_of_sketch(fk, m):
+    n1, n2, n3, fmt = 514, 96, 602, "bf16"
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("normal", 1.0), ("normal", 1.0), 5)
+    A, B = to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt)
+    plan, S = _fresh_sigma(fk, A, B, gemm_f32(A, B), n1, n2, n3, fmt, m)
+    assert plan["sigma_hat"] == _mad(S)
+
+
+@pytest.mark.parametrize("kind", ["zeros", "cluster", "mixed"])
+def test_ties_and_clusters(fk, kind):
+    """S set bucket by bucket through C: all zeros (one value, more than the kept keys), a cluster
+    of values that share the first two digits (ditto), and both with outliers on each side."""
+    n, m, fmt, n2 = 900, 301, "fp16", 8
+    hr = o.make_round(21, 0, n, n, m)
+    rng = np.random.default_rng(3)
+    want = np.zeros((m, m))
+    if kind != "zeros":
+        want = 2.0 ** 21 + rng.integers(0, 256, size=(m, m))
+    if kind == "mixed":
+        want[rng.random((m, m)) < 0.2] = 0.0
+        want[rng.random((m, m)) < 0.01] = -3.0
+    C = np.zeros((n, n), dtype=np.float32)
+    rows = [np.flatnonzero(hr.h1 == a) for a in range(m)]
+    cols = [np.flatnonzero(hr.h2 == b) for b in range(m)]
+    ra = [a for a in range(m) if rows[a].size]
+    cb = [b for b in range(m) if cols[b].size]
+    for a in ra:
+        i = rows[a][0]
+        for b in cb:
+            j = cols[b][0]
+            C[i, j] = -hr.v1[i] * hr.v2[j] * want[a, b]
+    z = np.zeros((n, n2), dtype=np.uint16)
+    A, B = to_dev_half(z, fmt), to_dev_half(np.ascontiguousarray(z.T), fmt)
+    plan, S = _fresh_sigma(fk, A, B, to_dev_f32(C), n, n2, n, fmt, m)
+    assert np.array_equal(S[np.ix_(ra, cb)], want[np.ix_(ra, cb)])
+    assert plan["sigma_hat"] == _mad(S)
+
+
+@pytest.mark.parametrize("n1,n3,bad", [(1, 1, 0), (1, 2, 1), (3, 5, 0), (255, 257, 3), (256, 256, 0),
+                                       (257, 257, 7), (500, 1000, 1000), (40, 40, 1600)])
+def test_rms_hat(fk, n1, n3, bad):
+    rng = np.random.default_rng(n1 + n3)
+    n2, fmt = 4, "bf16"
+    c = (rng.standard_normal((n1, n3)) * 3.0).astype(np.float32)
+    f = c.reshape(-1)
+    f[rng.choice(f.size, size=f.size // 100, replace=False)] *= 1e6       # clipped at 64 x median
+    idx = rng.choice(f.size, size=bad, replace=False)
+    f[idx] = rng.choice(np.array([np.inf, -np.inf, np.nan], dtype=np.float32), size=bad)
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("normal", 1.0), ("normal", 1.0), 1)
+    v = fk.Verifier(n1, n2, n3, fmt, m=4)
+    A, B = to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt)
+    for _ in range(2):                     # the second call finds the state the first one left
+        v.localize(A, B, to_dev_f32(c), seed=2, sigma_from_probe=False)
+        got = v.plan()["rms_hat"]
+        want = o.rms_hat(c)
+        host = fk.rms_hat_samples(f[::max(1, f.size // 65536)])
+        if not np.isfinite(want):
+            assert not np.isfinite(got) and not np.isfinite(host)
+        else:
+            # sums of at most 131072 squares in FP64 in another order
+            assert math.isclose(got, want, rel_tol=1e-11) and math.isclose(got, host, rel_tol=1e-11)
+    v.close()
