@@ -1,6 +1,6 @@
 // Host side of the FP-Sketch verifier library: the C ABI of include/fpsketch.h.
 //
-// Owns the hash rounds and bucket-sorted tables (Sec. III-B), the bucket-count rules and the
+// Owns the hash rounds (their tables are built by fpsk_tables.hip), the bucket-count rules and the
 // localization plan (Eq. 3-5, Sec. III-G), device workspaces, and the localization driver
 // (Algorithm 2 with Algorithm 1 per round).  Every arithmetic step over A, B and C runs in the
 // kernels of fpsk_kernels.hip; the host handles O(m^2) selection on the dirty path only.
@@ -61,14 +61,23 @@ inline uint64_t sm_mix(uint64_t z) {
 
 inline uint64_t sm_output(uint64_t seed, uint64_t idx) { return sm_mix(seed + (idx + 1) * kGamma); }
 
+// Stream of one side of one round.
+uint64_t side_key(uint64_t seed, int round, int side) {
+  return sm_output(seed, 2ull * static_cast<uint64_t>(round) + side);
+}
+
+inline int32_t hash_bucket(uint64_t x, int m) {
+  return static_cast<int32_t>(((x >> 32) * static_cast<uint64_t>(m)) >> 32);
+}
+
 // Hash of one side of one round: key = output (2 round + side) of the stream at `seed`;
 // index idx uses output idx of the stream at key; bucket = (x >> 32) * m >> 32; sign = bit 0.
 void hash_side(uint64_t seed, int round, int side, int64_t n, int m, int32_t* bucket,
                int8_t* sign) {
-  const uint64_t key = sm_output(seed, 2ull * static_cast<uint64_t>(round) + side);
+  const uint64_t key = side_key(seed, round, side);
   for (int64_t idx = 0; idx < n; ++idx) {
     const uint64_t x = sm_output(key, static_cast<uint64_t>(idx));
-    bucket[idx] = static_cast<int32_t>(((x >> 32) * static_cast<uint64_t>(m)) >> 32);
+    bucket[idx] = hash_bucket(x, m);
     sign[idx] = (x & 1ull) ? -1 : 1;
   }
 }
@@ -222,22 +231,27 @@ double rms_hat_from_samples(const float* s, int64_t count) {
 }
 
 // ------------------------------------------------------------------------------------------
-// Tables of one hash round at one m.
+// Tables of one hash round at one m (built on the device, fpsk_tables.hip).
 
-struct HostRound {
-  int m = 0;
-  int cap = 0;
-  bool mom = false;
-  std::vector<int32_t> h1, h2;
-  std::vector<int8_t> v1, v2;
-  std::vector<int32_t> perm, coff, boff;
-  std::vector<uint16_t> ctab, btab;
-  std::vector<uint8_t> bsign;
-  // B passed transposed: the column lists of each bucket (j | (v2 < 0) << 31, ascending,
-  // padded to cap2 with -1), natural bucket order (the C grid's column order)
-  int cap2 = 0;
-  std::vector<int32_t> perm2;
+// Rows of the largest bucket of each side (columns: only where their lists are built), which
+// size the row lists.
+struct RoundCaps {
+  int cap1 = 1, cap2 = 0;
 };
+
+RoundCaps round_caps(uint64_t seed, int round, int64_t n1, int64_t n3, int m, bool transb) {
+  std::vector<int32_t> cnt;
+  auto largest = [&](int side, int64_t n) {
+    cnt.assign(static_cast<size_t>(m), 0);
+    const uint64_t key = side_key(seed, round, side);
+    for (int64_t i = 0; i < n; ++i) cnt[hash_bucket(sm_output(key, static_cast<uint64_t>(i)), m)]++;
+    return std::max(1, *std::max_element(cnt.begin(), cnt.end()));
+  };
+  RoundCaps r;
+  r.cap1 = largest(0, n1);
+  if (transb) r.cap2 = largest(1, n3);
+  return r;
+}
 
 // Bucket segments are padded to a multiple of 8 for m <= 256 (the kernels then fold 8 list
 // entries per step); above that the lists are unpadded, except the probe's B chunks up to
@@ -248,109 +262,6 @@ int btab_pad(int m, bool mom) { return !mom && m <= 512 ? 8 : table_pad(m); }
 int64_t table_stride(int m, int64_t W, int pad) {
   const int64_t s = W + static_cast<int64_t>(pad - 1) * m;
   return (s + 7) / 8 * 8;
-}
-
-// Staged LDS slot of column offset cc in a B chunk of W columns (W: the zero sentinel slot):
-// column-block major, slot (cc mod 8) (W / 8) + cc / 8, so the thread that loads columns
-// 8g .. 8g + 7 stores them at one base address plus constant offsets, and the 64 lanes of a wave
-// store to consecutive slots.
-int64_t b_slot(int64_t cc, int64_t W) { return cc < W ? (cc & 7) * (W / 8) + (cc >> 3) : W; }
-
-// Column tiles of width W sorted by bucket (stable in column order); segment starts per tile,
-// segments padded with the sentinel W.  Entry format: 0 = offset | (v2 < 0) << 15 (C tiles),
-// 1 = offset (B chunks with moments), 2 = staged slot (B chunks of the probe).
-void build_col_tables(const std::vector<int32_t>& h2, const std::vector<int8_t>& v2, int m,
-                      int64_t W, int format, int pad, std::vector<uint16_t>& tab,
-                      std::vector<int32_t>& off) {
-  const int64_t n3 = static_cast<int64_t>(h2.size());
-  const int64_t T = (n3 + W - 1) / W;
-  const int64_t stride = table_stride(m, W, pad);
-  tab.assign(static_cast<size_t>(T * stride), static_cast<uint16_t>(W));
-  off.assign(static_cast<size_t>(T * (m + 1)), 0);
-  std::vector<int32_t> cnt(static_cast<size_t>(m) + 1), pos(static_cast<size_t>(m));
-  for (int64_t t = 0; t < T; ++t) {
-    const int64_t j0 = t * W, j1 = std::min(n3, j0 + W);
-    std::fill(cnt.begin(), cnt.end(), 0);
-    for (int64_t j = j0; j < j1; ++j) cnt[static_cast<size_t>(h2[j]) + 1]++;
-    int32_t* o = off.data() + t * (m + 1);
-    o[0] = 0;
-    for (int b = 0; b < m; ++b) {
-      const int32_t padded = (cnt[b + 1] + pad - 1) / pad * pad;
-      o[b + 1] = o[b] + padded;
-      pos[b] = o[b];
-    }
-    for (int64_t j = j0; j < j1; ++j) {
-      const int32_t p = pos[h2[j]]++;
-      const int64_t cc = j - j0;
-      uint16_t e;
-      if (format == 0) {
-        e = static_cast<uint16_t>(cc | (v2[j] < 0 ? 0x8000 : 0));
-      } else if (format == 1) {
-        e = static_cast<uint16_t>(cc);
-      } else {
-        e = static_cast<uint16_t>(b_slot(cc, W));
-      }
-      tab[static_cast<size_t>(t * stride + p)] = e;
-    }
-  }
-}
-
-// size_order: the row lists are stored largest bucket first (list slot a holds the a-th largest
-// bucket), so that the row-bucket work-groups, dispatched in list order, start with the longest.
-// The sketch rows then come out in that order; only the probe, whose statistics do not depend
-// on the numbering of the buckets, uses it.
-void build_round(uint64_t seed, int round, int64_t n1, int64_t n3, int m, int64_t cwb, bool mom,
-                 bool transb, HostRound& R, bool size_order = false) {
-  R.m = m;
-  R.mom = mom;
-  R.h1.resize(n1);
-  R.v1.resize(n1);
-  R.h2.resize(n3);
-  R.v2.resize(n3);
-  hash_side(seed, round, 0, n1, m, R.h1.data(), R.v1.data());
-  hash_side(seed, round, 1, n3, m, R.h2.data(), R.v2.data());
-  // rows of each bucket, ascending, padded to the largest bucket with -1
-  std::vector<int32_t> cnt(static_cast<size_t>(m), 0);
-  for (int64_t i = 0; i < n1; ++i) cnt[R.h1[i]]++;
-  R.cap = std::max(1, *std::max_element(cnt.begin(), cnt.end()));
-  std::vector<int32_t> slot(static_cast<size_t>(m));
-  for (int b = 0; b < m; ++b) slot[b] = b;
-  if (size_order) {
-    std::vector<int32_t> byz(static_cast<size_t>(m));
-    for (int b = 0; b < m; ++b) byz[b] = b;
-    std::stable_sort(byz.begin(), byz.end(), [&](int32_t x, int32_t y) { return cnt[x] > cnt[y]; });
-    for (int a = 0; a < m; ++a) slot[byz[a]] = a;
-  }
-  R.perm.assign(static_cast<size_t>(m) * R.cap, -1);
-  std::fill(cnt.begin(), cnt.end(), 0);
-  for (int64_t i = 0; i < n1; ++i) {
-    const int b = R.h1[i];
-    R.perm[static_cast<size_t>(slot[b]) * R.cap + cnt[b]++] =
-        static_cast<int32_t>(static_cast<uint32_t>(i) | (R.v1[i] < 0 ? 0x80000000u : 0u));
-  }
-  build_col_tables(R.h2, R.v2, m, kColTile, 0, table_pad(m), R.ctab, R.coff);
-  build_col_tables(R.h2, R.v2, m, cwb, mom ? 1 : 2, btab_pad(m, mom), R.btab, R.boff);
-  if (transb) {
-    std::vector<int32_t> c2(static_cast<size_t>(m), 0);
-    for (int64_t j = 0; j < n3; ++j) c2[R.h2[j]]++;
-    R.cap2 = std::max(1, *std::max_element(c2.begin(), c2.end()));
-    R.perm2.assign(static_cast<size_t>(m) * R.cap2, -1);
-    std::fill(c2.begin(), c2.end(), 0);
-    for (int64_t j = 0; j < n3; ++j) {
-      const int b = R.h2[j];
-      R.perm2[static_cast<size_t>(b) * R.cap2 + c2[b]++] =
-          static_cast<int32_t>(static_cast<uint32_t>(j) | (R.v2[j] < 0 ? 0x80000000u : 0u));
-    }
-  } else {
-    R.cap2 = 0;
-    R.perm2.clear();
-  }
-  // column signs as bits, padded to whole B chunks
-  const int64_t TB = (n3 + cwb - 1) / cwb;
-  R.bsign.assign(static_cast<size_t>(TB * cwb / 8), 0);
-  for (int64_t j = 0; j < n3; ++j) {
-    if (R.v2[j] < 0) R.bsign[static_cast<size_t>(j / 8)] |= static_cast<uint8_t>(1u << (j % 8));
-  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -596,33 +507,77 @@ struct DevRound {
   bool mom = false;
   int64_t cwb = 0;
   int cap2 = 0;
-  DevBuf perm, ctab, coff, btab, boff, bsign, perm2;
+  DevBuf hb1, hb2, slot, perm, ctab, coff, btab, boff, bsign, perm2;
 };
 
-fpsketch_status upload_round(const HostRound& R, int64_t cwb, DevRound& D, hipStream_t st) {
-  D.m = R.m;
-  D.cap = R.cap;
-  D.mom = R.mom;
-  D.cwb = cwb;
-  auto up = [st](DevBuf& b, const void* src, size_t bytes) -> fpsketch_status {
-    FPSK_TRY(dev_alloc(b, bytes));
-    if (bytes) FPSK_HIP(hipMemcpyAsync(b.p, src, bytes, hipMemcpyHostToDevice, st));
+// Enqueues the tables of hash round `round` of `seed` for the pass `d`.  size_order: the row
+// lists are stored largest bucket first (list slot a holds the a-th largest bucket), so that the
+// row-bucket work-groups, dispatched in list order, start with the longest.  The sketch rows then
+// come out in that order; only the probe, whose statistics do not depend on the numbering of the
+// buckets, uses it.
+fpsketch_status build_round(uint64_t seed, int round, const RoundCaps& caps, int64_t n1,
+                            int64_t n3, const Decomp& d, bool mom, bool transb, bool size_order,
+                            DevRound& D, hipStream_t st) {
+  const int m = d.m;
+  fpsk::TableArgs a{};
+  a.key1 = side_key(seed, round, 0);
+  a.key2 = side_key(seed, round, 1);
+  a.n1 = n1;
+  a.n3 = n3;
+  a.m = m;
+  a.nsign = transb ? 0 : static_cast<int64_t>(d.TB) * d.cwb;
+  a.pad1 = (n1 + 7) / 8 * 8;
+  a.pad3 = std::max((n3 + 7) / 8 * 8, a.nsign);
+  const size_t mz = static_cast<size_t>(m);
+  // list buffers with room to spare, so that another round's slightly larger bucket fits
+  auto lists = [mz](int cap) { return mz * static_cast<size_t>(cap + cap / 8 + 16) * 4; };
+  FPSK_TRY(dev_alloc(D.hb1, static_cast<size_t>(a.pad1) * 2));
+  FPSK_TRY(dev_alloc(D.hb2, static_cast<size_t>(a.pad3) * 2));
+  if (D.perm.bytes < mz * caps.cap1 * 4) FPSK_TRY(dev_alloc(D.perm, lists(caps.cap1)));
+  a.hb1 = as<uint16_t>(D.hb1);
+  a.hb2 = as<uint16_t>(D.hb2);
+  a.perm = as<int32_t>(D.perm);
+  a.cap = caps.cap1;
+  if (size_order) {
+    FPSK_TRY(dev_alloc(D.slot, mz * 4));
+    a.slot = as<int32_t>(D.slot);
+  }
+  auto table = [&](DevBuf& tab, DevBuf& off, int tiles, int64_t W, int stride, int pad,
+                   int format, fpsk::ColTable& t) -> fpsketch_status {
+    FPSK_TRY(dev_alloc(tab, static_cast<size_t>(tiles) * stride * 2));
+    FPSK_TRY(dev_alloc(off, static_cast<size_t>(tiles) * (mz + 1) * 4));
+    t.tab = as<uint16_t>(tab);
+    t.off = as<int32_t>(off);
+    t.tiles = tiles;
+    t.W = static_cast<int>(W);
+    t.stride = stride;
+    t.pad = pad;
+    t.format = format;
     return FPSK_OK;
   };
-  FPSK_TRY(up(D.perm, R.perm.data(), R.perm.size() * 4));
-  FPSK_TRY(up(D.bsign, R.bsign.data(), R.bsign.size()));
-  FPSK_TRY(up(D.ctab, R.ctab.data(), R.ctab.size() * 2));
-  FPSK_TRY(up(D.coff, R.coff.data(), R.coff.size() * 4));
-  FPSK_TRY(up(D.btab, R.btab.data(), R.btab.size() * 2));
-  FPSK_TRY(up(D.boff, R.boff.data(), R.boff.size() * 4));
-  D.cap2 = R.cap2;
-  if (!R.perm2.empty()) FPSK_TRY(up(D.perm2, R.perm2.data(), R.perm2.size() * 4));
-  // host vectors must outlive the asynchronous copies
-  FPSK_HIP(hipStreamSynchronize(st));
+  FPSK_TRY(table(D.ctab, D.coff, d.TC, kColTile, d.ctab_stride, table_pad(m), 0, a.c));
+  if (transb) {
+    if (D.perm2.bytes < mz * caps.cap2 * 4) FPSK_TRY(dev_alloc(D.perm2, lists(caps.cap2)));
+    a.perm2 = as<int32_t>(D.perm2);
+    a.cap2 = caps.cap2;
+  } else {
+    FPSK_TRY(dev_alloc(D.bsign, static_cast<size_t>(a.nsign / 8)));
+    a.bsign = as<uint8_t>(D.bsign);
+    FPSK_TRY(table(D.btab, D.boff, d.TB, d.cwb, d.btab_stride, btab_pad(m, mom), mom ? 1 : 2, a.b));
+  }
+  D.m = m;
+  D.cap = caps.cap1;
+  D.cap2 = caps.cap2;
+  D.mom = mom;
+  D.cwb = d.cwb;
+  FPSK_HIP(fpsk::launch_tables(a, st));
   return FPSK_OK;
 }
 
 void free_round(DevRound& D) {
+  dev_free(D.hb1);
+  dev_free(D.hb2);
+  dev_free(D.slot);
   dev_free(D.perm);
   dev_free(D.bsign);
   dev_free(D.ctab);
@@ -741,16 +696,17 @@ struct fpsketch_ctx {
   DevRound aux_round;
   Workspace aux_ws;
   DevBuf scan_counts, scan_total, scan_rows, scan_base, scan_out, samples, patch_rowptr,
-      patch_col, patch_val, rc_coords, rc_gamma, rc_abs;
+      patch_col, patch_val, rc_coords, rc_gamma, rc_abs, rc_part;
   // localize rounds on the device: selection state, histograms and kept keys, candidates
   DevBuf sel_state, sel_hist, sel_cand, cands, cand_count;
   // host memory the kernels read and write: figures and candidates of a step (HostHead, then up
   // to kPublish candidates), the peel list, the recheck's coordinates and results
   HostBuf host_head, host_peel, host_rc;
+  HostBuf host_stats, host_apply;   // probe statistics; the apply step's records
   // the selected buckets of a round and their moment sketches (R then T)
   DevBuf mo_list, mo_rt;
-  // apply step: the record list and the re-probe's statistics and scratch noise sum
-  DevBuf apply_list, reprobe_stats, reprobe_acc;
+  // apply step: the re-probe's scratch noise sum
+  DevBuf reprobe_acc;
   // the B-side cache of the probe: Q = (B H2^T)^T for the probe's round at m = qcache_m
   // (0: nothing cached) and the per-work-group max |B|
   DevBuf qcache, maxb_cache;
@@ -1038,10 +994,12 @@ fpsketch_status pipe_flush(fpsketch_ctx* c, hipStream_t next_st) {
 }
 
 fpsketch_status build_probe(fpsketch_ctx* c, int m, hipStream_t st) {
-  HostRound R;
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, false, c->transb);
-  build_round(c->p.seed, 0, c->n1, c->n3, m, d.cwb, false, c->transb, R, true);
-  FPSK_TRY(upload_round(R, d.cwb, c->probe_round, st));
+  const RoundCaps caps = round_caps(c->p.seed, 0, c->n1, c->n3, m, c->transb);
+  FPSK_TRY(build_round(c->p.seed, 0, caps, c->n1, c->n3, d, false, c->transb, true,
+                       c->probe_round, st));
+  // the probes that read the tables may run on other streams
+  FPSK_HIP(hipStreamSynchronize(st));
   FPSK_TRY(ensure_workspace(c->probe_ws, c->n1, c->n2, c->n3, m, false, c->transb));
   c->m = m;
   c->qcache_m = 0;      // a cached B side belongs to the previous round
@@ -1176,11 +1134,11 @@ fpsketch_status exact_scan(fpsketch_ctx* c, const float* C, int32_t K, hipStream
 fpsketch_status sketch_round(fpsketch_ctx* c, uint64_t seed, int round, int m, bool mom,
                              const void* A, const void* B, const float* C, const int32_t* prow,
                              const int32_t* pcol, const float* pval, hipStream_t st,
-                             HostRound& HR, std::vector<double>& S, std::vector<double>& Rm,
+                             std::vector<double>& S, std::vector<double>& Rm,
                              std::vector<double>& T, double* maxA, double* maxB) {
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, mom, c->transb);
-  build_round(seed, round, c->n1, c->n3, m, d.cwb, mom, c->transb, HR);
-  FPSK_TRY(upload_round(HR, d.cwb, c->aux_round, st));
+  FPSK_TRY(build_round(seed, round, round_caps(seed, round, c->n1, c->n3, m, c->transb), c->n1,
+                       c->n3, d, mom, c->transb, false, c->aux_round, st));
   FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb));
   FPSK_TRY(run_pass(c, c->aux_round, c->aux_ws, A, B, C, mom, 0, nullptr, prow, pcol, pval, st));
   const size_t mm = static_cast<size_t>(m) * static_cast<size_t>(m);
@@ -1213,10 +1171,10 @@ fpsketch_status sketch_round(fpsketch_ctx* c, uint64_t seed, int round, int m, b
 fpsketch_status sketch_round_device(fpsketch_ctx* c, uint64_t seed, int round, int m, bool mom,
                                     const void* A, const void* B, const float* C,
                                     const int32_t* prow, const int32_t* pcol, const float* pval,
-                                    hipStream_t st, HostRound& HR) {
+                                    hipStream_t st, const RoundCaps& caps) {
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, mom, c->transb);
-  build_round(seed, round, c->n1, c->n3, m, d.cwb, mom, c->transb, HR);
-  FPSK_TRY(upload_round(HR, d.cwb, c->aux_round, st));
+  FPSK_TRY(build_round(seed, round, caps, c->n1, c->n3, d, mom, c->transb, false, c->aux_round,
+                       st));
   FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb));
   return run_pass(c, c->aux_round, c->aux_ws, A, B, C, mom, 0, nullptr, prow, pcol, pval, st,
                   nullptr, nullptr, nullptr, BSide::kStream, false);
@@ -1250,6 +1208,87 @@ struct Found {
   int absolute;
   int round;
 };
+
+// Recheck of whole search windows of radius r (at most kMaxWinR).
+struct WindowCheck {
+  fpsketch_ctx* c;
+  const void* A;
+  const void* B;
+  const float* C;
+  int64_t r;
+  int64_t wd() const { return 2 * r + 1; }
+  int64_t size() const { return wd() * wd(); }
+};
+
+// The windows around `centers` (pairs i, j; each window meets C): gamma, sum |A||B| and C_ij in
+// [center][di][dj] order in host memory, those outside C undefined.  Waits for the stream.
+fpsketch_status recheck_windows(const WindowCheck& wc, const std::vector<int64_t>& centers,
+                                Recheck& rc, hipStream_t st) {
+  fpsketch_ctx* c = wc.c;
+  const size_t n = centers.size() / 2, out = n * static_cast<size_t>(wc.size());
+  if (n == 0) return FPSK_OK;
+  FPSK_TRY(host_alloc(c->host_rc, 2 * n * sizeof(int64_t) + out * (2 * sizeof(double) + sizeof(float))));
+  rc.coords = static_cast<int64_t*>(c->host_rc.p);
+  rc.gamma = reinterpret_cast<double*>(rc.coords + 2 * n);
+  rc.abssum = rc.gamma + out;
+  rc.cval = reinterpret_cast<float*>(rc.abssum + out);
+  std::copy(centers.begin(), centers.end(), rc.coords);
+  fpsk::WindowArgs g{};
+  g.A = static_cast<const uint16_t*>(wc.A);
+  g.B = static_cast<const uint16_t*>(wc.B);
+  g.bsk = c->transb ? 1 : c->n3;
+  g.bsj = c->transb ? c->n2 : 1;
+  g.C = wc.C;
+  g.n1 = c->n1;
+  g.n2 = c->n2;
+  g.n3 = c->n3;
+  g.centers = rc.coords;
+  g.n = static_cast<int>(n);
+  g.r = static_cast<int>(wc.r);
+  const size_t slices = static_cast<size_t>(fpsk::window_slices(c->n2, g.n));
+  FPSK_TRY(dev_alloc(c->rc_part, slices * out * 2 * sizeof(double)));
+  g.part = as<double>(c->rc_part);
+  g.gamma = rc.gamma;
+  g.abssum = rc.abssum;
+  g.cval = rc.cval;
+  FPSK_HIP(fpsk::launch_windows(g, c->dt == FPSK_BF16 ? 1 : 0, st));
+  FPSK_HIP(hipStreamSynchronize(st));
+  return FPSK_OK;
+}
+
+// Distinct coordinates of C in the windows that are not in F.
+int64_t window_coords(const WindowCheck& wc, const std::vector<int64_t>& centers,
+                      const std::vector<Found>& F) {
+  const int64_t n1 = wc.c->n1, n3 = wc.c->n3, r = wc.r;
+  const size_t n = centers.size() / 2;
+  auto lo = [r](int64_t x) { return std::max<int64_t>(0, x - r); };
+  auto hi = [r](int64_t x, int64_t lim) { return std::min(lim - 1, x + r); };
+  bool apart = n <= 1024;
+  for (size_t u = 0; u < n && apart; ++u)
+    for (size_t v = 0; v < u && apart; ++v)
+      apart = std::llabs(centers[2 * u] - centers[2 * v]) > 2 * r ||
+              std::llabs(centers[2 * u + 1] - centers[2 * v + 1]) > 2 * r;
+  if (apart) {
+    int64_t total = 0;
+    for (size_t u = 0; u < n; ++u) {
+      const int64_t ci = centers[2 * u], cj = centers[2 * u + 1];
+      total += (hi(ci, n1) - lo(ci) + 1) * (hi(cj, n3) - lo(cj) + 1);
+      for (const Found& f : F) total -= std::llabs(f.i - ci) <= r && std::llabs(f.j - cj) <= r;
+    }
+    return total;
+  }
+  std::vector<int64_t> keys, found;
+  for (size_t u = 0; u < n; ++u) {
+    const int64_t ci = centers[2 * u], cj = centers[2 * u + 1];
+    for (int64_t i = lo(ci); i <= hi(ci, n1); ++i)
+      for (int64_t j = lo(cj); j <= hi(cj, n3); ++j) keys.push_back(i * n3 + j);
+  }
+  std::sort(keys.begin(), keys.end());
+  keys.erase(std::unique(keys.begin(), keys.end()), keys.end());
+  int64_t total = static_cast<int64_t>(keys.size());
+  for (const Found& f : F) total -= std::binary_search(keys.begin(), keys.end(), f.i * n3 + f.j);
+  return total;
+}
 
 }  // namespace
 
@@ -1421,14 +1460,14 @@ void fpsketch_destroy(fpsketch_ctx* c) {
   free_round(c->aux_round);
   free_workspace(c->aux_ws);
   for (Workspace& w : c->pipe_ws) free_workspace(w);
-  for (HostBuf* b : {&c->host_head, &c->host_peel, &c->host_rc}) host_free(*b);
+  for (HostBuf* b : {&c->host_head, &c->host_peel, &c->host_rc, &c->host_stats, &c->host_apply}) host_free(*b);
   for (DevBuf* b : {&c->stats, &c->sigma_acc, &c->zero, &c->tiny, &c->scan_counts,
                     &c->scan_total, &c->scan_rows, &c->scan_base,
                     &c->scan_out, &c->samples, &c->patch_rowptr, &c->patch_col, &c->patch_val,
-                    &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->sel_state,
-                    &c->sel_hist, &c->sel_cand, &c->cands, &c->cand_count, &c->apply_list,
+                    &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->rc_part, &c->sel_state,
+                    &c->sel_hist, &c->sel_cand, &c->cands, &c->cand_count, 
                     &c->mo_list, &c->mo_rt,
-                    &c->reprobe_stats, &c->reprobe_acc, &c->qcache, &c->maxb_cache}) {
+                    &c->reprobe_acc, &c->qcache, &c->maxb_cache}) {
     dev_free(*b);
   }
   delete c;
@@ -1657,8 +1696,11 @@ fpsketch_status fpsketch_probe_stats(fpsketch_ctx* c, double* out, void* stream)
   FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
-  FPSK_HIP(hipMemcpyAsync(out, c->stats.p, 8 * sizeof(double), hipMemcpyDeviceToHost, st));
+  FPSK_TRY(host_alloc(c->host_stats, 8 * sizeof(double)));
+  double* h = static_cast<double*>(c->host_stats.p);
+  FPSK_HIP(fpsk::launch_publish_stats(as<double>(c->stats), h, st));
   FPSK_HIP(hipStreamSynchronize(st));
+  std::copy(h, h + 8, out);
   return FPSK_OK;
 }
 
@@ -1680,11 +1722,10 @@ fpsketch_status fpsketch_sketch(fpsketch_ctx* c, const void* A, const void* B, c
   FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
-  HostRound HR;
   std::vector<double> hS, hR, hT;
   double ma = 0, mb = 0;
   FPSK_TRY(sketch_round(c, seed, round, m, moments != 0, A, B, static_cast<const float*>(C),
-                        nullptr, nullptr, nullptr, st, HR, hS, hR, hT, &ma, &mb));
+                        nullptr, nullptr, nullptr, st, hS, hR, hT, &ma, &mb));
   std::memcpy(S, hS.data(), hS.size() * sizeof(double));
   if (moments) {
     std::memcpy(R, hR.data(), hR.size() * sizeof(double));
@@ -1741,7 +1782,10 @@ fpsketch_status fpsketch_apply(fpsketch_ctx* c, const void* A, const void* B, vo
   if (still_dirty == nullptr || n < 0 || (n > 0 && recs == nullptr)) {
     return fail(FPSK_EINVAL, "null argument or negative record count");
   }
-  std::vector<fpsk::ApplyEntry> list(static_cast<size_t>(n));
+  // (the context's device is current before its host memory grows)
+  FPSK_TRY(set_device(c));
+  FPSK_TRY(host_alloc(c->host_apply, static_cast<size_t>(n) * sizeof(fpsk::ApplyEntry)));
+  fpsk::ApplyEntry* list = static_cast<fpsk::ApplyEntry*>(c->host_apply.p);
   std::unordered_set<int64_t> seen;
   for (int32_t t = 0; t < n; ++t) {
     const fpsketch_fault& f = recs[t];
@@ -1752,30 +1796,21 @@ fpsketch_status fpsketch_apply(fpsketch_ctx* c, const void* A, const void* B, vo
     if (!seen.insert(o).second) return fail(FPSK_EINVAL, "record coordinate listed twice");
     list[t] = {o, f.delta, f.absolute ? 1 : 0, 0};
   }
-  FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
   float* Cm = static_cast<float*>(C);
-  if (n > 0) {
-    FPSK_TRY(dev_alloc(c->apply_list, list.size() * sizeof(fpsk::ApplyEntry)));
-    FPSK_HIP(hipMemcpyAsync(c->apply_list.p, list.data(), list.size() * sizeof(fpsk::ApplyEntry),
-                            hipMemcpyHostToDevice, st));
-    FPSK_HIP(fpsk::launch_apply(Cm, as<fpsk::ApplyEntry>(c->apply_list), n, st));
-  }
-  // re-probe with a fresh round at the probe's m; its statistics go to buffers of their own
+  // re-probe with a fresh round at the probe's m; its statistics go to host memory
   const int m = c->m;
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, false, c->transb);
-  HostRound HR;
-  build_round(seed, 0, c->n1, c->n3, m, d.cwb, false, c->transb, HR, true);
-  FPSK_TRY(upload_round(HR, d.cwb, c->aux_round, st));
+  FPSK_TRY(build_round(seed, 0, round_caps(seed, 0, c->n1, c->n3, m, c->transb), c->n1, c->n3, d,
+                       false, c->transb, true, c->aux_round, st));
   FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, false, c->transb));
-  FPSK_TRY(dev_alloc(c->reprobe_stats, 8 * sizeof(double)));
+  FPSK_TRY(host_alloc(c->host_stats, 8 * sizeof(double)));
+  double* stt = static_cast<double*>(c->host_stats.p);
   FPSK_TRY(dev_alloc(c->reprobe_acc, 2 * sizeof(double)));
+  if (n > 0) FPSK_HIP(fpsk::launch_apply(Cm, list, n, st));
   FPSK_TRY(run_pass(c, c->aux_round, c->aux_ws, A, B, Cm, false, 1, nullptr, nullptr, nullptr,
-                    nullptr, st, nullptr, as<double>(c->reprobe_stats),
-                    as<double>(c->reprobe_acc)));
-  double stt[8];
-  FPSK_HIP(hipMemcpyAsync(stt, c->reprobe_stats.p, sizeof(stt), hipMemcpyDeviceToHost, st));
+                    nullptr, st, nullptr, stt, as<double>(c->reprobe_acc)));
   FPSK_HIP(hipStreamSynchronize(st));
   *still_dirty = stt[5] != 0.0 ? 1 : 0;
   return FPSK_OK;
@@ -1888,8 +1923,8 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
 
   // 2. Plan from the measured noise (Sec. III-G).
   if (!sigma_from_probe) {
-    HostRound HR0;
-    FPSK_TRY(sketch_round_device(c, seed, 0, c->m, false, A, B, Cf, prow, pcol, pval, st, HR0));
+    const RoundCaps caps = round_caps(seed, 0, c->n1, c->n3, c->m, c->transb);
+    FPSK_TRY(sketch_round_device(c, seed, 0, c->m, false, A, B, Cf, prow, pcol, pval, st, caps));
     FPSK_TRY(round_cut_device(c, 0, st));
     FPSK_HIP(hipStreamSynchronize(st));
     sigma = head(c)->sigma;
@@ -1918,9 +1953,10 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   int32_t n_rechecked = 0;
   const int m = plan.m_loc;
   const double L1 = static_cast<double>(c->L1), L3 = static_cast<double>(c->L3);
+  RoundCaps caps = round_caps(seed, 1, c->n1, c->n3, m, c->transb);
   for (int t = 1; t <= c->p.rounds; ++t) {
-    HostRound HR;
-    FPSK_TRY(sketch_round_device(c, seed, t, m, true, A, B, Cf, prow, pcol, pval, st, HR));
+    FPSK_TRY(sketch_round_device(c, seed, t, m, true, A, B, Cf, prow, pcol, pval, st, caps));
+    const uint64_t key1 = side_key(seed, t, 0), key2 = side_key(seed, t, 1);
     const int64_t mm = static_cast<int64_t>(m) * m;
     double* dS = as<double>(c->aux_ws.S);
     // peel every finite fault confirmed so far (Sec. III-H), in order, on the device (S here;
@@ -1930,8 +1966,10 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     int npeel = 0;
     for (const Found& f : F) {
       if (f.absolute) continue;
-      const int64_t o = static_cast<int64_t>(HR.h1[f.i]) * m + HR.h2[f.j];
-      const double sv = static_cast<double>(HR.v1[f.i]) * HR.v2[f.j] * f.delta;
+      const uint64_t x1 = sm_output(key1, static_cast<uint64_t>(f.i));
+      const uint64_t x2 = sm_output(key2, static_cast<uint64_t>(f.j));
+      const int64_t o = static_cast<int64_t>(hash_bucket(x1, m)) * m + hash_bucket(x2, m);
+      const double sv = ((x1 ^ x2) & 1ull) ? -f.delta : f.delta;
       peel[npeel++] = {o, sv, sv * static_cast<double>(f.i + 1) / L1,
                        sv * static_cast<double>(f.j + 1) / L3};
     }
@@ -1963,6 +2001,8 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     ma.out = published(c);
     ma.head = head(c);
     FPSK_HIP(fpsk::launch_moments_at(ma, static_cast<int>(publish), st));
+    // the next round's list sizes, while this round runs
+    if (t < c->p.rounds) caps = round_caps(seed, t + 1, c->n1, c->n3, m, c->transb);
     FPSK_HIP(hipStreamSynchronize(st));
     tau = head(c)->tau;
     const double cut = head(c)->cut;
@@ -2030,24 +2070,41 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     if (live.empty()) continue;
     // Acceptance of every window coordinate is a pure function of (i, j): recheck them all,
     // then replay Algorithm 1's offset-major loop sequentially.
-    std::vector<int64_t> coords;
+    const WindowCheck wc{c, A, B, Cf, r};
+    Recheck rc{};
+    std::vector<int64_t> slot0;           // first result of each live center's window
     std::unordered_map<int64_t, int32_t> slot;
-    for (const Center& cd : live) {
-      for (const auto& od : offs) {
-        const int64_t i = cd.ci + od.first, j = cd.cj + od.second;
-        if (i < 0 || i >= c->n1 || j < 0 || j >= c->n3) continue;
-        const int64_t kk = key(i, j);
-        if (inF.count(kk) || slot.count(kk)) continue;
-        slot.emplace(kk, static_cast<int32_t>(coords.size() / 2));
-        coords.push_back(i);
-        coords.push_back(j);
+    if (r <= fpsk::kMaxWinR) {
+      std::vector<int64_t> centers;
+      for (const Center& cd : live) {
+        const bool in = cd.ci + r >= 0 && cd.ci - r < c->n1 && cd.cj + r >= 0 && cd.cj - r < c->n3;
+        slot0.push_back(in ? static_cast<int64_t>(centers.size() / 2) * wc.size() : 0);
+        if (in) {
+          centers.push_back(cd.ci);
+          centers.push_back(cd.cj);
+        }
       }
+      FPSK_TRY(recheck_windows(wc, centers, rc, st));
+      n_rechecked += static_cast<int32_t>(window_coords(wc, centers, F));
+    } else {
+      std::vector<int64_t> coords;
+      for (const Center& cd : live) {
+        for (const auto& od : offs) {
+          const int64_t i = cd.ci + od.first, j = cd.cj + od.second;
+          if (i < 0 || i >= c->n1 || j < 0 || j >= c->n3) continue;
+          const int64_t kk = key(i, j);
+          if (inF.count(kk) || slot.count(kk)) continue;
+          slot.emplace(kk, static_cast<int32_t>(coords.size() / 2));
+          coords.push_back(i);
+          coords.push_back(j);
+        }
+      }
+      const size_t nc = coords.size() / 2;
+      FPSK_TRY(recheck_buffers(c, nc, rc));
+      std::copy(coords.begin(), coords.end(), rc.coords);
+      FPSK_TRY(recheck_coords(c, A, B, Cf, rc, nc, st));
+      n_rechecked += static_cast<int32_t>(nc);
     }
-    const size_t nc = coords.size() / 2;
-    FPSK_TRY(recheck_buffers(c, nc, rc));
-    std::copy(coords.begin(), coords.end(), rc.coords);
-    FPSK_TRY(recheck_coords(c, A, B, Cf, rc, nc, st));
-    n_rechecked += static_cast<int32_t>(nc);
     std::vector<char> alive(live.size(), 1);
     size_t nlive = live.size();
     for (const auto& od : offs) {
@@ -2058,7 +2115,8 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
         if (i < 0 || i >= c->n1 || j < 0 || j >= c->n3) continue;
         const int64_t kk = key(i, j);
         if (inF.count(kk)) continue;
-        const int32_t sl = slot.at(kk);
+        const int64_t sl = slot0.empty() ? slot.at(kk)
+                                         : slot0[u] + (od.first + r) * wc.wd() + od.second + r;
         const double diff = rc.gamma[sl] - static_cast<double>(rc.cval[sl]);
         const double bound = c->p.c_valid * std::ldexp(1.0, -23) * rc.abssum[sl];
         if (std::fabs(diff) > bound) {

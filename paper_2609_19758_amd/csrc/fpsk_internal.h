@@ -129,6 +129,32 @@ struct ProductArgs {
   double* xpart;
 };
 
+// Tables of one hash round, built on the device.
+struct ColTable {       // column tiles of W columns, their lists sorted by bucket
+  uint16_t* tab;        // tiles x stride
+  int32_t* off;         // tiles x (m + 1) segment starts
+  int tiles, W, stride;
+  int pad;              // segments padded to this multiple with the sentinel W
+  int format;           // entries: 0 offset | negative sign << 15, 1 offset, 2 staged LDS slot
+};
+struct TableArgs {
+  uint64_t key1, key2;  // streams of the rows' and the columns' hashes
+  int64_t n1, n3;
+  int64_t pad1, pad3;   // padded to multiples of 8 (pad3 also to whole sign bytes of the chunks)
+  int m;
+  uint16_t* hb1;        // pad1, pad3 words: bucket | negative sign << 15, 0x7fff past the end
+  uint16_t* hb2;
+  int32_t* slot;        // null: lists in bucket order; else scratch for the order by size
+  int32_t* perm;        // m x cap
+  int cap;
+  int32_t* perm2;       // m x cap2 (null: none)
+  int cap2;
+  uint8_t* bsign;       // column signs as bits
+  int64_t nsign;        // columns they cover, a multiple of 8 (0: none)
+  ColTable c, b;
+};
+hipError_t launch_tables(const TableArgs& a, hipStream_t st);
+
 // e0 / e1 (may be null): events that the first / last dispatch of the call records its
 // start / end time in.
 // Pipelined probe launch (m <= 64, block path): the decision of `dec` (if has_dec), the nprod
@@ -232,7 +258,7 @@ struct MomentsAtArgs {
   HostHead* head;
 };
 hipError_t launch_moments_at(const MomentsAtArgs& g, int n, hipStream_t st);
-struct ApplyEntry {    // one record of the apply step: C[o] <- d, or C[o] + d
+struct ApplyEntry {    // one record of the apply step: C[o] <- d, or C[o] + d (in host memory)
   int64_t o;
   double d;
   int32_t absolute;
@@ -246,6 +272,7 @@ struct PadTinyArgs {
   uint16_t* dst;
 };
 hipError_t launch_pad_tiny(const PadTinyArgs& a, hipStream_t st);
+hipError_t launch_publish_stats(const double* stats, double* out, hipStream_t st);
 hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st);
 // Zeroes columns [c0, c1) of rows x ld FP32 rows (c1 <= ld).
 hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipStream_t st);
@@ -264,6 +291,27 @@ hipError_t launch_rms(const SelArgs& a, const SetupArgs& u, hipStream_t st);
 hipError_t launch_above(const double* S, int64_t n, const SelState* state, Cand* out,
                         uint32_t cap, uint32_t* count, hipStream_t st);
 
+// The recheck of n search windows of radius r <= kMaxWinR around centers (i, j): outputs
+// [center][di][dj], those outside C left alone.  part: window_slices(n2, n) n (2r + 1)^2 pairs.
+constexpr int kWinRows = 3;
+constexpr int kMaxWinR = 31;
+struct WindowArgs {
+  const uint16_t* A;
+  const uint16_t* B;
+  int64_t bsk, bsj;       // B[k][j] at B + k bsk + j bsj
+  const float* C;
+  int64_t n1, n2, n3;
+  const int64_t* centers; // n pairs; these and the outputs may be host memory
+  int n, r;
+  double* part;
+  double* gamma;
+  double* abssum;
+  float* cval;
+  int jl;                 // lanes per row of B and k per slice (set by the launcher)
+  int64_t ks;
+};
+int window_slices(int64_t n2, int n);
+hipError_t launch_windows(const WindowArgs& g, int dt, hipStream_t st);
 hipError_t launch_read(const void* src, int64_t bytes, uint32_t* out, int grid, hipStream_t st);
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, int grid, hipStream_t st);
 

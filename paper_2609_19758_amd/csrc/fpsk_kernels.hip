@@ -1161,6 +1161,112 @@ __global__ __launch_bounds__(kThreads) void recheck_kernel(const uint16_t* A, co
   }
 }
 
+// The recheck of whole search windows: for each center the (2r + 1)^2 coordinates around it.  A
+// work-group takes kWinRows rows of one window over one slice of k; lanes hold the window's
+// columns (jl >= 2r + 1 lanes) by 8 consecutive k each, so that a row of B is read as one short
+// run for all its columns and a row of A 16 bytes at a time, once for the window instead of once
+// per coordinate.  Exact products accumulated in FP64; lanes, waves and slices are combined in
+// fixed order (window_sum_kernel adds the slices).  Bound by the latency of the scattered rows of
+// B: one coordinate a wave, 64 rows of B a load, took 219 us for 16 windows of 81 at 16384^3 and
+// 40 us for 8 at 4096^3; now 73 us and 26 us.
+template <int DT>
+__global__ __launch_bounds__(kThreads) void window_kernel(WindowArgs g) {
+  constexpr int R = kWinRows;
+  __shared__ double red[kThreads / 64][2 * R][64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int wd = 2 * g.r + 1;
+  const int ctr = blockIdx.x, di0 = blockIdx.y * R, slice = blockIdx.z;
+  const int jj = lane & (g.jl - 1), kg = lane / g.jl, nkg = 64 / g.jl;
+  const int64_t ci = g.centers[2 * ctr], cj = g.centers[2 * ctr + 1];
+  const int64_t j = cj - g.r + jj;
+  const bool jok = jj < wd && j >= 0 && j < g.n3;
+  const uint16_t* bcol = g.B + (jok ? j : 0) * g.bsj;
+  const uint16_t* arow[R];
+  bool iok[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    const int64_t i = ci - g.r + di0 + q;
+    iok[q] = di0 + q < wd && i >= 0 && i < g.n1;
+    arow[q] = g.A + (iok[q] ? i : 0) * g.n2;
+  }
+  double acc[R], aab[R];
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    acc[q] = 0.0;
+    aab[q] = 0.0;
+  }
+  const int64_t k1 = (slice + 1) * g.ks < g.n2 ? (slice + 1) * g.ks : g.n2;
+  for (int64_t k = slice * g.ks + 8 * (w * nkg + kg); k < k1; k += 8 * nkg * (kThreads / 64)) {
+    uint32_t b[8];
+    u32x4 a[R];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) b[e] = jok && k + e < k1 ? bcol[(k + e) * g.bsk] : 0u;
+    if (k + 8 <= k1) {
+#pragma unroll
+      for (int q = 0; q < R; ++q) a[q] = *reinterpret_cast<const u32x4_a2*>(arow[q] + k);
+    } else {
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        a[q] = u32x4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int e = 0; e < 7; ++e) {
+          if (k + e < k1) a[q][e >> 1] |= static_cast<uint32_t>(arow[q][k + e]) << (16 * (e & 1));
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const double y = static_cast<double>(half_bits_to_float<DT>(b[e]));
+#pragma unroll
+      for (int q = 0; q < R; ++q) {
+        const uint32_t wq = a[q][e >> 1];
+        const double x = static_cast<double>((e & 1) ? hi_half<DT>(wq) : lo_half<DT>(wq));
+        const double p = x * y;
+        acc[q] += p;
+        aab[q] += fabs(p);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < R; ++q) {
+    red[w][q][lane] = acc[q];
+    red[w][R + q][lane] = aab[q];
+  }
+  __syncthreads();
+  // output (row q, column c): the k groups of the four waves in order
+  for (int o = threadIdx.x; o < 2 * R * wd; o += kThreads) {
+    const int v = o / wd, c = o - v * wd;
+    double s = 0.0;
+    for (int ww = 0; ww < kThreads / 64; ++ww) {
+      for (int kk = 0; kk < nkg; ++kk) s += red[ww][v][kk * g.jl + c];
+    }
+    const int q = v < R ? v : v - R;
+    if (di0 + q < wd) {
+      const int64_t at = (static_cast<int64_t>(slice) * g.n + ctr) * wd * wd + (di0 + q) * wd + c;
+      g.part[2 * at + (v < R ? 0 : 1)] = s;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void window_sum_kernel(WindowArgs g, int slices) {
+  const int wd = 2 * g.r + 1;
+  const int64_t total = static_cast<int64_t>(g.n) * wd * wd;
+  const int64_t o = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  if (o >= total) return;
+  const int ctr = static_cast<int>(o / (wd * wd)), q = static_cast<int>(o - static_cast<int64_t>(ctr) * wd * wd);
+  const int64_t i = g.centers[2 * ctr] - g.r + q / wd, j = g.centers[2 * ctr + 1] - g.r + q % wd;
+  if (i < 0 || i >= g.n1 || j < 0 || j >= g.n3) return;
+  double s = 0.0, a = 0.0;
+#pragma unroll 8
+  for (int sl = 0; sl < slices; ++sl) {
+    s += g.part[2 * (sl * total + o)];
+    a += g.part[2 * (sl * total + o) + 1];
+  }
+  g.gamma[o] = s;
+  g.abssum[o] = a;
+  g.cval[o] = g.C[i * g.n3 + j];
+}
+
 // ----------------------------------------------------------------------------------------
 // Reference streams of known size: a plain read (XOR-folded so no load is dropped) and a
 // plain copy, 16 bytes per lane, grid-stride.
@@ -1315,6 +1421,17 @@ hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipSt
   return hipGetLastError();
 }
 
+// The 8 probe statistics to host memory: a launch and the caller's wait, without the staging of
+// a copy to pageable memory.
+__global__ __launch_bounds__(64) void publish_stats_kernel(const double* stats, double* out) {
+  if (threadIdx.x < 8) out[threadIdx.x] = stats[threadIdx.x];
+}
+
+hipError_t launch_publish_stats(const double* stats, double* out, hipStream_t st) {
+  hipLaunchKernelGGL(publish_stats_kernel, dim3(1), dim3(64), 0, st, stats, out);
+  return hipGetLastError();
+}
+
 // Copies of matrices of fewer than 8 elements into 32-byte slots (zero past them): thread t of
 // block b copies halfword t of matrix b.
 __global__ __launch_bounds__(64) void pad_tiny_kernel(PadTinyArgs a) {
@@ -1367,6 +1484,34 @@ hipError_t launch_recheck(const uint16_t* A, const uint16_t* B, int64_t bsk, int
     hipLaunchKernelGGL(recheck_kernel<0>, dim3(grid), dim3(kThreads), 0, st, A, B, bsk, bsj, C,
                        n2, n3, coords, n, gamma, abssum, cval);
   }
+  return hipGetLastError();
+}
+
+int window_slices(int64_t n2, int n) {
+  // about 1024 work-groups, slices of at least 512 k
+  const int64_t s = std::min<int64_t>((n2 + 511) / 512, (1024 + n - 1) / n);
+  return static_cast<int>(std::max<int64_t>(1, s));
+}
+
+hipError_t launch_windows(const WindowArgs& g0, int dt, hipStream_t st) {
+  WindowArgs g = g0;
+  if (g.n <= 0) return hipSuccess;
+  const int wd = 2 * g.r + 1;
+  g.jl = 1;
+  while (g.jl < wd) g.jl *= 2;
+  if (g.jl > 64) return hipErrorInvalidValue;
+  int slices = window_slices(g.n2, g.n);
+  g.ks = ((g.n2 + slices - 1) / slices + 7) / 8 * 8;
+  slices = static_cast<int>((g.n2 + g.ks - 1) / g.ks);
+  const dim3 grid(g.n, (wd + kWinRows - 1) / kWinRows, slices);
+  if (dt == 1) {
+    hipLaunchKernelGGL(window_kernel<1>, grid, dim3(kThreads), 0, st, g);
+  } else {
+    hipLaunchKernelGGL(window_kernel<0>, grid, dim3(kThreads), 0, st, g);
+  }
+  const int64_t total = static_cast<int64_t>(g.n) * wd * wd;
+  hipLaunchKernelGGL(window_sum_kernel, dim3(static_cast<unsigned>((total + kThreads - 1) / kThreads)),
+                     dim3(kThreads), 0, st, g, slices);
   return hipGetLastError();
 }
 
