@@ -334,6 +334,7 @@ struct Decomp {
   int ctab_stride = 0, btab_stride = 0, tab_off = 0;
   int ts = 32, nt = 1, NS = 1, ksl = 0;
   bool kw = false;             // product tiles whose k-range the 4 waves split
+  bool i8 = false;             // product on 8-bit digits
   size_t lds_stream = 0;
   int kact = 0;                // k-range of the factors: n2 rounded up to a multiple of 4
   int ldp = 0;                 // row stride of the factors (kact padded; see decompose)
@@ -440,6 +441,20 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
   ns = std::max(1, std::min<int>({ns, 32, static_cast<int>((n2 + kstep - 1) / kstep)}));
   int64_t ksl = (n2 + ns - 1) / ns;
   ksl = (ksl + kstep - 1) / kstep * kstep;
+  // S alone on the quadrant tiles: the digit product, in 128 x 64 tiles, from m^2 n2 = 2^28 on.
+  // Its three extra launches cost about 16 us: at m = 260, n2 = 1030 (0.07 x 10^9) it takes 36 us
+  // against 15 us on the FP64 cores, at m = 279, n2 = 4096 (0.32 x 10^9) 42 against 53 with their
+  // reductions, at m = 698, n2 = 16384 163 against 275.  Slices for about 512 work-groups, of at
+  // least 512 k (a slice's epilogue and its share of the reduction cost as much as about 500 k) and
+  // at most what 32-bit sums hold.
+  d.i8 = !mom && !d.kw && n2 >= fpsk::kDigitMinK &&
+         static_cast<double>(m) * m * static_cast<double>(n2) >= 0x1p28;
+  if (d.i8) {
+    const int64_t wg = static_cast<int64_t>((m + 127) / 128) * ((m + 63) / 64);
+    int64_t want = std::max<int64_t>(1, std::min<int64_t>({512 / wg, 32, n2 / fpsk::kDigitMinK}));
+    want = std::max<int64_t>(want, (n2 + fpsk::kDigitMaxK - 1) / fpsk::kDigitMaxK);
+    ksl = ((n2 + want - 1) / want + 31) / 32 * 32;
+  }
   d.ksl = static_cast<int>(ksl);
   d.NS = static_cast<int>((n2 + ksl - 1) / ksl);
   // dynamic LDS of the stream kernel: a data area (A/C combine and column sums, or the staged
@@ -596,6 +611,7 @@ struct Workspace {
   DevBuf P, Pw, Q, Qw, partS, partR, partT, scratch, S, R, T, maxpart, tilestat;
   DevBuf xpart;                // probe block-product partials
   DevBuf Qk, Qwk;              // k-major B-side rows (qk passes), transposed into Q, Qw
+  DevBuf rexp, digP, digQ;     // digit product: row scales and digit fragments
 };
 
 fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n3, int m,
@@ -628,6 +644,12 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
   FPSK_TRY(dev_alloc(W.maxpart, static_cast<size_t>(d.nA + d.nB) * sizeof(float)));
   FPSK_TRY(dev_alloc(W.tilestat, static_cast<size_t>(tiles) * 4 * sizeof(double)));
   if (d.nX > 0) FPSK_TRY(dev_alloc(W.xpart, static_cast<size_t>(d.xns) * mm));
+  if (W.ds.i8) {
+    const size_t row = static_cast<size_t>((n2 + 31) / 32) * 128;    // 4 digits of each k
+    FPSK_TRY(dev_alloc(W.rexp, static_cast<size_t>(m) * 2 * sizeof(int32_t)));
+    FPSK_TRY(dev_alloc(W.digP, static_cast<size_t>((m + 127) / 128) * 128 * row));
+    FPSK_TRY(dev_alloc(W.digQ, static_cast<size_t>((m + 63) / 64) * 64 * row));
+  }
   if (d.qk) {
     const size_t qk = static_cast<size_t>(n2) * static_cast<size_t>(m) * sizeof(float);
     FPSK_TRY(dev_alloc(W.Qk, qk));
@@ -638,7 +660,8 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
 
 void free_workspace(Workspace& W) {
   for (DevBuf* b : {&W.P, &W.Pw, &W.Q, &W.Qw, &W.partS, &W.partR, &W.partT, &W.scratch, &W.S,
-                    &W.R, &W.T, &W.maxpart, &W.tilestat, &W.xpart, &W.Qk, &W.Qwk}) {
+                    &W.R, &W.T, &W.maxpart, &W.tilestat, &W.xpart, &W.Qk, &W.Qwk, &W.rexp, &W.digP,
+                    &W.digQ}) {
     dev_free(*b);
   }
 }
@@ -869,6 +892,11 @@ fpsketch_status pass_args(fpsketch_ctx* c, const DevRound& R, Workspace& W, cons
   a.clip_tiles = (mode == 1 && !mom && d.nX == 0 && d.m >= 192) ? 1 : 0;
   a.NS = d.NS;
   a.ksl = d.ksl;
+  a.i8 = d.i8 ? 1 : 0;
+  a.zero = c->zero.p;
+  a.rexp = as<int32_t>(W.rexp);
+  a.digP = as<uint32_t>(W.digP);
+  a.digQ = as<uint32_t>(W.digQ);
   a.npc = d.npc;
   a.mode = mode;
   a.maxpart = s.maxpart;
@@ -965,6 +993,7 @@ fpsketch_status run_pass(fpsketch_ctx* c, const DevRound& R, Workspace& W, const
     a.ts = ds.ts;
     a.NS = ds.NS;
     a.ksl = ds.ksl;
+    a.i8 = ds.i8 ? 1 : 0;
     FPSK_HIP(fpsk::launch_product(a, ds.ts, ds.kw, false, st, ev ? ev[2] : nullptr,
                                   ev ? ev[3] : nullptr));
     return FPSK_OK;

@@ -14,6 +14,9 @@ constexpr int kBChunkHalfs = 16384;    // halfs of B staged in LDS per chunk (32
 constexpr int kMaxM = 4096;            // largest bucket count the kernels accept
 constexpr double kHugeLimit = 3.4028234663852886e38 / 16.0;   // fp32max / 16
 // block product of the probe (m <= 64)
+constexpr int kDigitMinK = 512;          // smallest n2, and k per slice, of the digit product
+constexpr int kDigitMaxK = 16384;        // k per slice at most: 32-bit sums of 4 products, 4 2^14 k < 2^31
+constexpr int32_t kNoDigits = 0x7fffffff;
 constexpr int kXSlice = 4096;            // k per block-product work-group
 constexpr int kMaxXSlices = 4;           // n2 <= kMaxXSlices * kXSlice
 
@@ -123,6 +126,14 @@ struct ProductArgs {
   // probe with m <= 64 (nX > 0): nX = xnb^2 xns block-product work-groups of xb x xb outputs
   // over k-slices of kXSlice, their partials in xpart (xns x m x m, slice 0 minus the C grid)
   int nX, xb, xnb, xns;
+  // S alone on 64 x 64 tiles (i8): the factors as 8-bit digits on the integer matrix cores, tiles
+  // with a row that does not fit them on the FP64 ones (fpsk_digits.hip)
+  int i8;
+  int32_t* rexp;          // 2 m: scale exponent of every row of P, then of Q; kNoDigits where not
+  uint32_t* digP;         // digit fragments of P (rows padded to 128) and Q (to 64)
+  uint32_t* digQ;
+  const void* zero;       // >= 64 bytes of zeros
+  int to_scratch;         // tile partials go to the scratch for reduce_kernel
   // launch index i -> slot (i mod 8) nX / 8 + i / 8; xslots slots per slice, in supertiles of
   // xsr x xsc blocks, xnstc supertiles per row of blocks (slots past the grid are idle)
   int xsr, xsc, xnstc, xslots;
@@ -161,6 +172,8 @@ hipError_t launch_tables(const TableArgs& a, hipStream_t st);
 // block products of `prod` and the stream pass of `s` (which may be empty: nA = nB = nC = 0).
 // lds_bytes covers the stream pass and probe_pipe_lds(xb).
 size_t probe_pipe_lds(int xb);
+// The digit product's launches: row scales, digit fragments, the product of every tile they fit.
+hipError_t launch_digit_product(const ProductArgs& a, hipStream_t st, hipEvent_t e0);
 hipError_t launch_probe_pipe(const StreamArgs& s, const ProductArgs& prod, const ProductArgs& dec,
                              int nprod, int has_dec, int dt, int xb, size_t lds_bytes,
                              hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);

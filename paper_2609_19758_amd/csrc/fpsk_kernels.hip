@@ -125,6 +125,20 @@ __global__ __launch_bounds__(kThreads) void mfma_product_kernel(ProductArgs pa) 
   const int slice = slot / ntiles, tile = slot - slice * ntiles;
   const int ta = tile / pa.nt, tb = tile - ta * pa.nt;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  if constexpr (!KW && !MOM) {
+    // beside the digit product: only tiles with a row that has no digits
+    if (pa.i8) {
+      __shared__ int none[2];
+      if (w < 2) {
+        const int row = (w == 0 ? ta : tb) * TS + lane;
+        const bool bad = row < m && pa.rexp[w * m + row] == kNoDigits;
+        const bool any = __ballot(bad) != 0;
+        if (lane == 0) none[w] = any;
+      }
+      __syncthreads();
+      if (!none[0] && !none[1]) return;
+    }
+  }
   const int ro = KW ? 0 : (w >> 1) * WT, co = KW ? 0 : (w & 1) * WT;   // wave origin in the tile
   // k per step: 32 for S alone on the quadrant tiles (large m), so that the 4 lanes of a factor
   // row read one whole 128-byte line (two 16-byte pieces each) per step (m = 698: 339 -> 332 us
@@ -275,7 +289,7 @@ __global__ __launch_bounds__(kThreads) void mfma_product_kernel(ProductArgs pa) 
           const int row = ta * TS + rt, col = tb * TS + ct;
           const bool valid = owner && row < m && col < m;
           const double v = acc[x][i][j][r];
-          if (pa.NS > 1) {
+          if (pa.to_scratch) {
             if (owner) {
               pa.scratch[((static_cast<int64_t>(slice) * ntiles + tile) * NX + x) * TS * TS +
                          rt * TS + ct] = v;
@@ -292,7 +306,7 @@ __global__ __launch_bounds__(kThreads) void mfma_product_kernel(ProductArgs pa) 
             }
           }
         }
-  if (pa.NS > 1 || pa.mode != 1) return;
+  if (pa.to_scratch || pa.mode != 1) return;
   double r3[3] = {lsum, lmax, lbad};
   lds_reduce<kThreads, 3>(r3, red, 0x2u);
   if (threadIdx.x == 0) {
@@ -1311,7 +1325,14 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
   }
   const dim3 grid((a.nt * a.nt * a.NS + 7) / 8 * 8);     // whole rounds of the 8 XCDs
   const dim3 rgrid(a.nt * a.nt);
-  const bool red = a.NS > 1, dec = a.mode == 1;
+  const bool dec = a.mode == 1;
+  a.to_scratch = a.NS > 1 || (a.i8 && dec);
+  const bool red = a.to_scratch != 0;
+  if (a.i8) {
+    const hipError_t e = launch_digit_product(a, st, e0);
+    if (e != hipSuccess) return e;
+    e0 = nullptr;
+  }
 #define FPSK_PRODUCT_CASE(TS_, WB_, KW_, MOM_)                                              \
   if (ts == TS_ && kw == KW_ && moments == MOM_) {                                          \
     launch_k(mfma_product_kernel<WB_, KW_, MOM_>, grid, dim3(kThreads), 0, st, e0,          \
