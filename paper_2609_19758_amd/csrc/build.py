@@ -15,7 +15,7 @@ OUT = os.path.join(PKG, "libfpsketch.so")
 # Diagnostic build: the same kernels with the stream pass's per-work-group timeline recorded
 # (bench.py --wg-timeline reads it).  The binding never loads it for the probe path.
 OUT_TIMELINE = os.path.join(PKG, "libfpsketch_timeline.so")
-SOURCES = ["fpsk_stream.hip", "fpsk_kernels.hip", "fpsk_tables.hip", "fpsk_digits.hip",
+SOURCES = ["fpsk_stream.hip", "fpsk_wide.hip", "fpsk_kernels.hip", "fpsk_tables.hip", "fpsk_digits.hip",
            "fpsk_host.hip"]
 
 # gfx950 only; packed FP32 instructions disabled (hipcc forms them from plain float code).

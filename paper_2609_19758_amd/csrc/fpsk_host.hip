@@ -341,8 +341,8 @@ struct Decomp {
   // probe block product (nX > 0): work-groups of xb x xb outputs over xns k-slices
   int xb = 0, xnb = 0, xns = 0, nX = 0;
   int xsr = 1, xsc = 1, xnstc = 1, xslots = 0;   // supertiles of blocks (XCD-local sets)
-  // B work-groups of 1 or 2 rows write Q k-major (n2 x m), then a transpose forms Q
-  bool qk = false;
+  bool wide = false;                  // m > 1024: C and B sides in launches of their own
+  int ctw = kColTile;                 // columns per C tile
   bool wt_c = false;                  // C work-groups of one tile per wave
   bool wt_a = false, wt_w = false;   // row-bucket work-groups of four tiles (small buckets)
 };
@@ -379,18 +379,17 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
     d.rb = 8, d.g = 2;
   } else if (m <= 1024) {
     d.rb = 4, d.g = 4;
-  } else if (m <= 2048) {
-    d.rb = 2, d.g = 8;
   } else {
-    d.rb = 1, d.g = 16;
+    d.wide = true;
+    d.rb = 4;
+    d.ctw = fpsk::kWideCols;
   }
-  d.cwb = fpsk::kBChunkHalfs / d.rb;
+  d.cwb = d.wide ? fpsk::kWideCols : fpsk::kBChunkHalfs / d.rb;
   d.TB = static_cast<int>((n3 + d.cwb - 1) / d.cwb);
   d.nB = static_cast<int>((n2 + d.rb - 1) / d.rb);
   // B passed transposed: row-bucket work-groups over the rows of W = B^T, as many as A's
   if (transb) d.nB = m * (d.wt_w ? tq : d.TA);
-  d.qk = !transb && d.rb < 4;
-  d.TC = static_cast<int>((n3 + kColTile - 1) / kColTile);
+  d.TC = static_cast<int>((n3 + d.ctw - 1) / d.ctw);
   int npc = static_cast<int>((1024 + m - 1) / m);
   npc = std::max(1, std::min(npc, d.TC));
   d.tg = (d.TC + npc - 1) / npc;
@@ -459,7 +458,7 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
   d.NS = static_cast<int>((n2 + ksl - 1) / ksl);
   // dynamic LDS of the stream kernel: a data area (A/C combine and column sums, or the staged
   // B chunk plus its zero column), then the staged sorted column list
-  d.ctab_stride = static_cast<int>(table_stride(m, kColTile, table_pad(m)));
+  d.ctab_stride = static_cast<int>(table_stride(m, d.ctw, table_pad(m)));
   d.btab_stride = static_cast<int>(table_stride(m, d.cwb, btab_pad(m, mom)));
   const size_t comb = (mom ? 4096 : 2048) * sizeof(double);
   const size_t cs = (mom ? 1040 : 520) * sizeof(double);
@@ -470,7 +469,7 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
       d.wt_c ? (mom ? 8 : 4) * 520 * sizeof(double) +
                    (m <= 256 ? 4 * static_cast<size_t>(d.ctab_stride) * sizeof(uint16_t) : 0)
              : 0;
-  const size_t data = (std::max({comb + cs, bdata, wtc}) + 15) / 16 * 16;
+  const size_t data = (std::max({comb + cs, d.wide ? 0 : bdata, wtc}) + 15) / 16 * 16;
   d.tab_off = static_cast<int>(data);
   // (the probe's B group fold, 8-row work-groups up to m = 256, stages the m + 1 segment
   // starts after the column list; at larger m they would take up to 16 KiB per work-group)
@@ -484,6 +483,7 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
     d.lds_stream = data + std::max<size_t>(static_cast<size_t>(d.ctab_stride) * sizeof(uint16_t),
                                            (static_cast<size_t>(m) + 1) * sizeof(int32_t));
   }
+  if (d.wide) d.lds_stream = data;      // row-bucket work-groups only
   if (d.wt_c) {
     // the four staged 512-entry tile lists of the one-tile-per-wave C work-groups
     d.lds_stream = std::max(d.lds_stream, data + 4 * 512 * sizeof(uint16_t));
@@ -570,7 +570,7 @@ fpsketch_status build_round(uint64_t seed, int round, const RoundCaps& caps, int
     t.format = format;
     return FPSK_OK;
   };
-  FPSK_TRY(table(D.ctab, D.coff, d.TC, kColTile, d.ctab_stride, table_pad(m), 0, a.c));
+  FPSK_TRY(table(D.ctab, D.coff, d.TC, d.ctw, d.ctab_stride, table_pad(m), 0, a.c));
   if (transb) {
     if (D.perm2.bytes < mz * caps.cap2 * 4) FPSK_TRY(dev_alloc(D.perm2, lists(caps.cap2)));
     a.perm2 = as<int32_t>(D.perm2);
@@ -610,7 +610,6 @@ struct Workspace {
   bool mom = false;
   DevBuf P, Pw, Q, Qw, partS, partR, partT, scratch, S, R, T, maxpart, tilestat;
   DevBuf xpart;                // probe block-product partials
-  DevBuf Qk, Qwk;              // k-major B-side rows (qk passes), transposed into Q, Qw
   DevBuf rexp, digP, digQ;     // digit product: row scales and digit fragments
 };
 
@@ -650,17 +649,12 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
     FPSK_TRY(dev_alloc(W.digP, static_cast<size_t>((m + 127) / 128) * 128 * row));
     FPSK_TRY(dev_alloc(W.digQ, static_cast<size_t>((m + 63) / 64) * 64 * row));
   }
-  if (d.qk) {
-    const size_t qk = static_cast<size_t>(n2) * static_cast<size_t>(m) * sizeof(float);
-    FPSK_TRY(dev_alloc(W.Qk, qk));
-    if (mom) FPSK_TRY(dev_alloc(W.Qwk, qk));
-  }
   return FPSK_OK;
 }
 
 void free_workspace(Workspace& W) {
   for (DevBuf* b : {&W.P, &W.Pw, &W.Q, &W.Qw, &W.partS, &W.partR, &W.partT, &W.scratch, &W.S,
-                    &W.R, &W.T, &W.maxpart, &W.tilestat, &W.xpart, &W.Qk, &W.Qwk, &W.rexp, &W.digP,
+                    &W.R, &W.T, &W.maxpart, &W.tilestat, &W.xpart, &W.rexp, &W.digP,
                     &W.digQ}) {
     dev_free(*b);
   }
@@ -855,11 +849,6 @@ fpsketch_status pass_args(fpsketch_ctx* c, const DevRound& R, Workspace& W, cons
     return fail(FPSK_EINVAL, "internal: tables do not match the pass");
   }
   s.ldp = d.ldp;
-  if (d.qk) {
-    s.Qk = as<float>(W.Qk);
-    s.Qwk = mom ? as<float>(W.Qwk) : nullptr;
-    s.mq = d.m;
-  }
   if (bside == BSide::kFillCache) {
     // B work-groups only, into the cache (Q and the per-work-group max |B|)
     s.nA = 0;
@@ -971,19 +960,12 @@ fpsketch_status run_pass(fpsketch_ctx* c, const DevRound& R, Workspace& W, const
   if (bside == BSide::kFillCache) {
     FPSK_HIP(fpsk::launch_stream(s, c->dt == FPSK_BF16 ? 1 : 0, false, d.rb, d.g, d.ng,
                                  d.lds_stream, st));
-    if (d.qk) {
-      FPSK_HIP(fpsk::launch_transpose_q(s.Qk, s.Q, d.m, c->n2, s.mq, d.ldp, st));
-    }
     return FPSK_OK;
   }
   // with ev: the dispatches themselves time-stamp ev[0..1] (stream kernel) and ev[2..3]
   // (first product dispatch start to last dispatch end)
   FPSK_HIP(fpsk::launch_stream(s, c->dt == FPSK_BF16 ? 1 : 0, mom, d.rb, d.g, d.ng,
                                d.lds_stream, st, ev ? ev[0] : nullptr, ev ? ev[1] : nullptr));
-  if (d.qk && s.nB > 0) {
-    FPSK_HIP(fpsk::launch_transpose_q(s.Qk, s.Q, d.m, c->n2, s.mq, d.ldp, st));
-    if (mom) FPSK_HIP(fpsk::launch_transpose_q(s.Qwk, s.Qw, d.m, c->n2, s.mq, d.ldp, st));
-  }
   if (mom && !prod_mom) {
     // the moment factors stay for launch_moments_at; the product forms S alone
     const Decomp& ds = W.ds;

@@ -10,6 +10,7 @@ namespace fpsk {
 
 constexpr int kThreads = 256;          // work-group size of every kernel (4 wave64)
 constexpr int kColTile = 512;          // columns per A or C tile: 64 lanes x 8 elements
+constexpr int kWideCols = 8192;        // columns per step of the C and B sides at m > 1024
 constexpr int kBChunkHalfs = 16384;    // halfs of B staged in LDS per chunk (32 KiB)
 constexpr int kMaxM = 4096;            // largest bucket count the kernels accept
 constexpr double kHugeLimit = 3.4028234663852886e38 / 16.0;   // fp32max / 16
@@ -37,7 +38,7 @@ struct StreamArgs {
   int transb;
   const int32_t* perm2;
   int cap2;
-  // C column tiles of kColTile: per tile (ctab_stride entries), columns sorted by bucket as
+  // C column tiles of kColTile (kWideCols at m > 1024): per tile (ctab_stride entries), columns sorted by bucket as
   // (offset in tile) | (v2 < 0) << 15, with coff[t * (m + 1) + b] segment starts; for m <= 256
   // each segment is padded to a multiple of 8 with the sentinel offset kColTile (a zero column)
   const uint16_t* ctab;
@@ -58,12 +59,6 @@ struct StreamArgs {
   float* Q;        // m x ldp      (B H2^T)^T: row b holds column b of B H2^T
   float* Qw;       // m x ldp      (B W2 H2^T)^T      (moments only)
   int ldp;
-  // B work-groups of 1 or 2 rows (m > 1024) write Q (Qw) k-major instead, n2 x mq, for a
-  // transpose into Q: a bucket-major row per work-group would be an 8-byte or smaller piece per
-  // bucket; null otherwise
-  float* Qk;
-  float* Qwk;
-  int mq;
   double* partS;   // npc x m x m  partial H1 C H2^T over column-tile groups
   double* partR;   // npc x m x m  partial H1 W1 C H2^T
   double* partT;   // npc x m x m  partial H1 C W2 H2^T
@@ -177,6 +172,11 @@ hipError_t launch_digit_product(const ProductArgs& a, hipStream_t st, hipEvent_t
 hipError_t launch_probe_pipe(const StreamArgs& s, const ProductArgs& prod, const ProductArgs& dec,
                              int nprod, int has_dec, int dt, int xb, size_t lds_bytes,
                              hipStream_t st, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
+// The C and B sides for m > 1024 (fpsk_wide.hip).
+hipError_t launch_wide_c(const StreamArgs& s, bool mom, hipStream_t st, hipEvent_t e0,
+                         hipEvent_t e1);
+hipError_t launch_wide_b(const StreamArgs& s, int dt, bool mom, hipStream_t st, hipEvent_t e0,
+                         hipEvent_t e1);
 hipError_t launch_stream(const StreamArgs& s, int dt, bool moments, int rb, int g, int ng,
                          size_t lds_bytes, hipStream_t st, hipEvent_t e0 = nullptr,
                          hipEvent_t e1 = nullptr);
@@ -189,9 +189,6 @@ hipError_t launch_scan_extract(const float* C, int64_t n3, const int32_t* rows,
                                const int32_t* base, int nrows, int32_t cap, int64_t* out,
                                hipStream_t st);
 // B[k][j] is read at B + k * bsk + j * bsj (n3, 1 for B as stored; 1, n2 for W = B^T).
-// dst (m x ldp) = transpose of src (n2 x mq), columns past m and rows past n2 left alone.
-hipError_t launch_transpose_q(const float* src, float* dst, int m, int64_t n2, int mq, int ldp,
-                              hipStream_t st);
 hipError_t launch_recheck(const uint16_t* A, const uint16_t* B, int64_t bsk, int64_t bsj,
                           const float* C, int64_t n2, int64_t n3, int dt, const int64_t* coords,
                           int n, double* gamma, double* abssum, float* cval, hipStream_t st);

@@ -304,11 +304,7 @@ __device__ __forceinline__ void store_cols(uint16_t* dst, const u32x4* v) {
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     uint16_t* d = dst + e * (kBChunkHalfs / 8);
-    if constexpr (RB == 1) {
-      d[0] = static_cast<uint16_t>(v[0][e >> 1] >> (16 * (e & 1)));
-    } else if constexpr (RB == 2) {
-      *reinterpret_cast<uint32_t*>(d) = pick_half<RB>(v[0][e >> 1], v[1][e >> 1], e & 1);
-    } else if constexpr (RB == 4) {
+    if constexpr (RB == 4) {
       u32x2 o;
       o[0] = pick_half<RB>(v[0][e >> 1], v[1][e >> 1], e & 1);
       o[1] = pick_half<RB>(v[2][e >> 1], v[3][e >> 1], e & 1);
@@ -331,9 +327,7 @@ __device__ __forceinline__ int col_slot(int cc) {
 // RBG consecutive halfs of one staged column.
 template <int DT, int RBG>
 __device__ __forceinline__ void load_col(const uint16_t* src, float* x) {
-  if constexpr (RBG == 1) {
-    x[0] = half_bits_to_float<DT>(*src);
-  } else if constexpr (RBG == 2) {
+  if constexpr (RBG == 2) {
     const uint32_t w = *reinterpret_cast<const uint32_t*>(src);
     x[0] = lo_half<DT>(w);
     x[1] = hi_half<DT>(w);
@@ -701,7 +695,7 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
   for (int g = 0; g < (GF ? 0 : G); ++g) {
     const int b = bslot + SLOTS * g;
     const int64_t kg = k0 + rg * RBG;        // this thread's first row
-    if (RBG == 4 && s.Qk == nullptr && b < m && kg + 4 <= s.n2) {
+    if (RBG == 4 && b < m && kg + 4 <= s.n2) {
       // one 16-byte piece per Q row (kg is a multiple of 4; rows start on 256-byte boundaries)
       const int64_t o = static_cast<int64_t>(b) * s.ldp + kg;
       *reinterpret_cast<f32x4*>(s.Q + o) =
@@ -717,14 +711,8 @@ __device__ void b_unit(const StreamArgs& s, int u, uint16_t* L, uint16_t* tabL, 
       for (int r = 0; r < RBG; ++r) {
         const int64_t k = k0 + rg * RBG + r;
         if (k < s.n2) {
-          if (s.Qk != nullptr) {
-            // k-major rows (consecutive buckets of a wave write consecutive floats)
-            s.Qk[k * s.mq + b] = static_cast<float>(acc[g][r]);
-            if (MOM) s.Qwk[k * s.mq + b] = static_cast<float>(accw[g][r]);
-          } else {
-            s.Q[static_cast<int64_t>(b) * s.ldp + k] = static_cast<float>(acc[g][r]);
-            if (MOM) s.Qw[static_cast<int64_t>(b) * s.ldp + k] = static_cast<float>(accw[g][r]);
-          }
+          s.Q[static_cast<int64_t>(b) * s.ldp + k] = static_cast<float>(acc[g][r]);
+          if (MOM) s.Qw[static_cast<int64_t>(b) * s.ldp + k] = static_cast<float>(accw[g][r]);
         }
       }
     }
@@ -920,9 +908,7 @@ __device__ __forceinline__ void rag_rows_c(const StreamArgs& s, const int64_t (&
 
 template <bool MOM, int G, bool VEC>
 __device__ void c_unit(const StreamArgs& s, int u, double* lds, uint16_t* tabL) {
-  // rows in flight per wave: 4 at m > 2048 (a few rows per bucket, and the fold's 16 buckets
-  // per thread need the registers)
-  constexpr int U = G >= 16 ? 4 : 8;
+  constexpr int U = 8;                       // rows in flight per wave
   constexpr int PADG = G == 1 ? 8 : 1;       // bucket segments padded to this multiple
   const int m = s.m;
   const int a = u / s.npc, gi = u - a * s.npc;
@@ -1271,12 +1257,12 @@ __device__ void c_unit_wt(const StreamArgs& s, int u, double* lds, uint16_t* tab
 
 // LDS layout of the stream kernel (dynamic): the A/C combine area or the staged B chunk first,
 // then the sorted column list of the current B chunk or C tile.  The longer lists of B chunks
-// with fewer rows hold the probe to 3 (2 or 4 rows) or 2 (1 row) work-groups per CU, so those
+// with 4 rows hold the probe to 3 work-groups per CU, so those
 // instances may use the registers of that occupancy instead of spilling at 4's 128.
 // WTC: C work-groups of one tile per wave (c_unit_wt) in place of the one-tile form, as its own
 // instance so that the others keep their code and registers.
 template <int DT, bool MOM, int RB, int G, int NG, bool VEC, bool WTC>
-__global__ __launch_bounds__(kThreads, MOM ? 2 : ((RB == 8 || (RB == 4 && G == 1)) ? 4 : (RB >= 2 ? 3 : 2))) void stream_kernel(
+__global__ __launch_bounds__(kThreads, MOM ? 2 : ((RB == 8 || (RB == 4 && G == 1)) ? 4 : 3)) void stream_kernel(
     StreamArgs s) {
   extern __shared__ double lds_dyn[];
   __shared__ uint32_t ldsu[kThreads / 64];
@@ -1458,16 +1444,34 @@ static hipError_t stream_dispatch(const StreamArgs& s, int rb, int g, int ng, si
   FPSK_STREAM_CASE(4, 1, 1)
   FPSK_STREAM_CASE(4, 2, 1)
   FPSK_STREAM_CASE(4, 4, 1)
-  FPSK_STREAM_CASE(2, 8, 1)
-  FPSK_STREAM_CASE(1, 16, 1)
 #undef FPSK_STREAM_CASE
 #undef FPSK_STREAM_WTC_CASE
 #undef FPSK_STREAM_LAUNCH
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_stream(const StreamArgs& s, int dt, bool moments, int rb, int g, int ng,
+hipError_t launch_stream(const StreamArgs& s0, int dt, bool moments, int rb, int g, int ng,
                          size_t lds_bytes, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
+  StreamArgs s = s0;
+  if (s.m > 1024) {
+    // the C and B sides as launches of their own, then the row-bucket work-groups of A (and W)
+    const bool b = s.nB > 0 && !s.transb;
+    const bool rows = s.nA > 0 || (s.nB > 0 && s.transb);
+    if (s.nC > 0) {
+      const hipError_t e = launch_wide_c(s, moments, st, e0, b || rows ? nullptr : e1);
+      if (e != hipSuccess) return e;
+      e0 = nullptr;
+    }
+    if (b) {
+      const hipError_t e = launch_wide_b(s, dt, moments, st, e0, rows ? nullptr : e1);
+      if (e != hipSuccess) return e;
+      e0 = nullptr;
+      s.nB = 0;
+    }
+    s.nC = 0;
+    if (!rows) return hipSuccess;
+    rb = 8, g = 1, ng = 4;
+  }
   if (dt == 1) {
     return moments ? stream_dispatch<1, true>(s, rb, g, ng, lds_bytes, st, e0, e1)
                    : stream_dispatch<1, false>(s, rb, g, ng, lds_bytes, st, e0, e1);
