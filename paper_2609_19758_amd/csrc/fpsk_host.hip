@@ -712,14 +712,14 @@ struct fpsketch_ctx {
   // localize / diagnostic workspaces
   DevRound aux_round;
   Workspace aux_ws;
-  DevBuf scan_counts, scan_total, scan_rows, scan_base, scan_out, samples, patch_rowptr,
+  DevBuf scan_counts, scan_total, scan_rows, scan_out, samples, patch_rowptr,
       patch_col, patch_val, rc_coords, rc_gamma, rc_abs, rc_part;
   // localize rounds on the device: selection state, histograms and kept keys, candidates
   DevBuf sel_state, sel_hist, sel_cand, cands, cand_count;
   // host memory the kernels read and write: figures and candidates of a step (HostHead, then up
   // to kPublish candidates), the peel list, the recheck's coordinates and results
   HostBuf host_head, host_peel, host_rc;
-  HostBuf host_stats, host_apply;   // probe statistics; the apply step's records
+  HostBuf host_abs, host_stats, host_apply;   // probe statistics; the apply step's records
   // the selected buckets of a round and their moment sketches (R then T)
   DevBuf mo_list, mo_rt;
   // apply step: the re-probe's scratch noise sum
@@ -1055,7 +1055,7 @@ fpsk::SelArgs sel_args(fpsketch_ctx* c) {
 
 // Enqueues rms-hat(C) (Sec. III-G: strided samples, clipped at 64 x their median) and publishes
 // it in head(c) with the exact scan's total (`found`, may be null) and two doubles at `sigma`.
-fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, uint32_t* found,
+fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, unsigned long long* found,
                                const double* sigma, hipStream_t st) {
   const int64_t total = c->n1 * c->n3;
   const int64_t stride = std::max<int64_t>(1, total / 65536);
@@ -1104,40 +1104,38 @@ fpsketch_status recheck_coords(fpsketch_ctx* c, const void* A, const void* B, co
   return FPSK_OK;
 }
 
-// Exact scan (Sec. III-I): first K entries in row-major order that are non-finite or above
-// fp32max/16 in magnitude, from the row counts of launch_scan_count.
-fpsketch_status exact_scan(fpsketch_ctx* c, const float* C, int32_t K, hipStream_t st,
-                           std::vector<int64_t>& coords) {
-  coords.clear();
-  std::vector<int32_t> counts(static_cast<size_t>(c->n1));
-  FPSK_HIP(hipMemcpyAsync(counts.data(), c->scan_counts.p, counts.size() * sizeof(int32_t),
-                          hipMemcpyDeviceToHost, st));
-  FPSK_HIP(hipStreamSynchronize(st));
-  std::vector<int32_t> rows, base;
-  int64_t total = 0;
-  for (int64_t i = 0; i < c->n1 && total < K; ++i) {
-    if (counts[i] > 0) {
-      rows.push_back(static_cast<int32_t>(i));
-      base.push_back(static_cast<int32_t>(total));
-      total += counts[i];
-    }
-  }
-  if (rows.empty()) return FPSK_OK;
-  const int32_t keep = static_cast<int32_t>(std::min<int64_t>(total, K));
-  FPSK_TRY(dev_alloc(c->scan_rows, rows.size() * sizeof(int32_t)));
-  FPSK_TRY(dev_alloc(c->scan_base, base.size() * sizeof(int32_t)));
-  FPSK_TRY(dev_alloc(c->scan_out, static_cast<size_t>(keep) * 2 * sizeof(int64_t)));
-  FPSK_HIP(hipMemcpyAsync(c->scan_rows.p, rows.data(), rows.size() * sizeof(int32_t),
-                          hipMemcpyHostToDevice, st));
-  FPSK_HIP(hipMemcpyAsync(c->scan_base.p, base.data(), base.size() * sizeof(int32_t),
-                          hipMemcpyHostToDevice, st));
-  FPSK_HIP(fpsk::launch_scan_extract(C, c->n3, as<int32_t>(c->scan_rows),
-                                     as<int32_t>(c->scan_base), static_cast<int>(rows.size()),
-                                     keep, as<int64_t>(c->scan_out), st));
-  coords.resize(static_cast<size_t>(keep) * 2);
-  FPSK_HIP(hipMemcpyAsync(coords.data(), c->scan_out.p, coords.size() * sizeof(int64_t),
-                          hipMemcpyDeviceToHost, st));
-  FPSK_HIP(hipStreamSynchronize(st));
+// Enqueues the exact scan's entries (Sec. III-I: the first `keep` in row-major order, counted by
+// launch_scan_count), their recomputation and the patch list for the sketches; coordinates and
+// recomputed values reach host_abs (keep pairs, then keep doubles) with the next wait.
+fpsketch_status abs_list(fpsketch_ctx* c, const void* A, const void* B, const float* C, int32_t keep,
+                         hipStream_t st) {
+  const size_t n = static_cast<size_t>(keep);
+  FPSK_TRY(dev_alloc(c->scan_rows, (2 * n + 1) * sizeof(int32_t)));
+  FPSK_TRY(dev_alloc(c->scan_out, n * 2 * sizeof(int64_t)));
+  FPSK_TRY(dev_alloc(c->rc_gamma, n * sizeof(double)));
+  FPSK_TRY(dev_alloc(c->rc_abs, n * sizeof(double)));
+  FPSK_TRY(dev_alloc(c->patch_rowptr, (static_cast<size_t>(c->n1) + 1) * sizeof(int32_t)));
+  FPSK_TRY(dev_alloc(c->patch_col, n * sizeof(int32_t)));
+  FPSK_TRY(dev_alloc(c->patch_val, n * sizeof(float)));
+  FPSK_TRY(host_alloc(c->host_abs, n * (2 * sizeof(int64_t) + sizeof(double))));
+  fpsk::AbsArgs g{};
+  g.n1 = c->n1;
+  g.keep = keep;
+  g.counts = as<int32_t>(c->scan_counts);
+  g.rowptr = as<int32_t>(c->patch_rowptr);
+  g.rows = as<int32_t>(c->scan_rows);
+  g.base = g.rows + n;
+  g.nrows = g.base + n;
+  g.coords = as<int64_t>(c->scan_out);
+  g.gamma = as<double>(c->rc_gamma);
+  g.abssum = as<double>(c->rc_abs);
+  g.col = as<int32_t>(c->patch_col);
+  g.val = as<float>(c->patch_val);
+  g.host_coords = static_cast<int64_t*>(c->host_abs.p);
+  g.host_gamma = reinterpret_cast<double*>(g.host_coords + 2 * n);
+  FPSK_HIP(fpsk::launch_abs_list(g, static_cast<const uint16_t*>(A), static_cast<const uint16_t*>(B),
+                                 c->transb ? 1 : c->n3, c->transb ? c->n2 : 1, C, c->n2, c->n3,
+                                 c->dt == FPSK_BF16 ? 1 : 0, st));
   return FPSK_OK;
 }
 
@@ -1471,9 +1469,9 @@ void fpsketch_destroy(fpsketch_ctx* c) {
   free_round(c->aux_round);
   free_workspace(c->aux_ws);
   for (Workspace& w : c->pipe_ws) free_workspace(w);
-  for (HostBuf* b : {&c->host_head, &c->host_peel, &c->host_rc, &c->host_stats, &c->host_apply}) host_free(*b);
+  for (HostBuf* b : {&c->host_head, &c->host_peel, &c->host_rc, &c->host_abs, &c->host_stats, &c->host_apply}) host_free(*b);
   for (DevBuf* b : {&c->stats, &c->sigma_acc, &c->zero, &c->tiny, &c->scan_counts,
-                    &c->scan_total, &c->scan_rows, &c->scan_base,
+                    &c->scan_total, &c->scan_rows,
                     &c->scan_out, &c->samples, &c->patch_rowptr, &c->patch_col, &c->patch_val,
                     &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->rc_part, &c->sel_state,
                     &c->sel_hist, &c->sel_cand, &c->cands, &c->cand_count, 
@@ -1886,51 +1884,38 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   // 1. Exact scan and absolute recompute (Sec. III-I; Algorithm 2).
   // rms-hat(C) and the last probe's noise are read with the scan's total: one wait.
   FPSK_TRY(dev_alloc(c->scan_counts, static_cast<size_t>(c->n1) * sizeof(int32_t)));
-  FPSK_TRY(dev_alloc_zero(c->scan_total, sizeof(uint32_t)));
+  FPSK_TRY(dev_alloc_zero(c->scan_total, sizeof(unsigned long long)));
   FPSK_HIP(fpsk::launch_scan_count(Cf, c->n1, c->n3, as<int32_t>(c->scan_counts),
-                                   as<uint32_t>(c->scan_total), st));
-  FPSK_TRY(rms_hat_device(c, Cf, as<uint32_t>(c->scan_total), as<double>(c->stats), st));
+                                   as<unsigned long long>(c->scan_total), st));
+  FPSK_TRY(rms_hat_device(c, Cf, as<unsigned long long>(c->scan_total), as<double>(c->stats), st));
   FPSK_HIP(hipStreamSynchronize(st));
   const double rms = head(c)->rms;
   double sigma = head(c)->sigma;
-  std::vector<int64_t> abs_coords;
-  if (head(c)->found > 0) FPSK_TRY(exact_scan(c, Cf, K, st, abs_coords));
-  const size_t n_abs = abs_coords.size() / 2;
-  Recheck rc{};
-  FPSK_TRY(recheck_buffers(c, n_abs, rc));
-  std::copy(abs_coords.begin(), abs_coords.end(), rc.coords);
-  FPSK_TRY(recheck_coords(c, A, B, Cf, rc, n_abs, st));
-  const std::vector<double> g(rc.gamma, rc.gamma + n_abs);
-  for (size_t t = 0; t < n_abs; ++t) {
-    F.push_back({abs_coords[2 * t], abs_coords[2 * t + 1], g[t], 1, 0});
-  }
-  // Patch list (row-major order already): C holds fl32(gamma) at these entries while sketching.
+  // C holds fl32(gamma) at the scan's entries while sketching; the host takes their records with
+  // the first wait after they are enqueued (they are not peeled, and come first in F).
+  const int32_t n_abs = static_cast<int32_t>(std::min<uint32_t>(head(c)->found, static_cast<uint32_t>(K)));
   const int32_t* prow = nullptr;
   const int32_t* pcol = nullptr;
   const float* pval = nullptr;
   if (n_abs > 0) {
-    std::vector<int32_t> rowptr(static_cast<size_t>(c->n1) + 1, 0), col(n_abs);
-    std::vector<float> val(n_abs);
-    for (size_t t = 0; t < n_abs; ++t) {
-      rowptr[static_cast<size_t>(abs_coords[2 * t]) + 1]++;
-      col[t] = static_cast<int32_t>(abs_coords[2 * t + 1]);
-      val[t] = static_cast<float>(g[t]);
-    }
-    for (int64_t i = 0; i < c->n1; ++i) rowptr[i + 1] += rowptr[i];
-    FPSK_TRY(dev_alloc(c->patch_rowptr, rowptr.size() * sizeof(int32_t)));
-    FPSK_TRY(dev_alloc(c->patch_col, col.size() * sizeof(int32_t)));
-    FPSK_TRY(dev_alloc(c->patch_val, val.size() * sizeof(float)));
-    FPSK_HIP(hipMemcpyAsync(c->patch_rowptr.p, rowptr.data(), rowptr.size() * sizeof(int32_t),
-                            hipMemcpyHostToDevice, st));
-    FPSK_HIP(hipMemcpyAsync(c->patch_col.p, col.data(), col.size() * sizeof(int32_t),
-                            hipMemcpyHostToDevice, st));
-    FPSK_HIP(hipMemcpyAsync(c->patch_val.p, val.data(), val.size() * sizeof(float),
-                            hipMemcpyHostToDevice, st));
-    FPSK_HIP(hipStreamSynchronize(st));
+    FPSK_TRY(abs_list(c, A, B, Cf, n_abs, st));
     prow = as<int32_t>(c->patch_rowptr);
     pcol = as<int32_t>(c->patch_col);
     pval = as<float>(c->patch_val);
   }
+  std::unordered_set<int64_t> inF;
+  auto key = [c](int64_t i, int64_t j) { return i * c->n3 + j; };
+  bool abs_taken = n_abs == 0;
+  auto take_abs = [&]() {
+    if (abs_taken) return;
+    abs_taken = true;
+    const int64_t* co = static_cast<const int64_t*>(c->host_abs.p);
+    const double* ga = reinterpret_cast<const double*>(co + 2 * static_cast<size_t>(n_abs));
+    for (int32_t t = 0; t < n_abs; ++t) {
+      F.push_back({co[2 * t], co[2 * t + 1], ga[t], 1, 0});
+      inF.insert(key(co[2 * t], co[2 * t + 1]));
+    }
+  };
 
   // 2. Plan from the measured noise (Sec. III-G).
   if (!sigma_from_probe) {
@@ -1938,15 +1923,13 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     FPSK_TRY(sketch_round_device(c, seed, 0, c->m, false, A, B, Cf, prow, pcol, pval, st, caps));
     FPSK_TRY(round_cut_device(c, 0, st));
     FPSK_HIP(hipStreamSynchronize(st));
+    take_abs();
     sigma = head(c)->sigma;
   }
   const PlanOut plan = plan_localize(c->n1, c->n2, c->n3, c->dt, c->m, sigma, rms, c->p);
   if (plan.m_loc > fpsk::kMaxM) return fail(FPSK_ESHAPE, "m_loc beyond 4096");
 
   // 3. Rounds t = 1..k (Algorithm 1).
-  std::unordered_set<int64_t> inF;
-  auto key = [c](int64_t i, int64_t j) { return i * c->n3 + j; };
-  for (const Found& f : F) inF.insert(key(f.i, f.j));
   const int r = plan.r;
   std::vector<std::pair<int, int>> offs;
   for (int di = -r; di <= r; ++di)
@@ -2015,6 +1998,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     // the next round's list sizes, while this round runs
     if (t < c->p.rounds) caps = round_caps(seed, t + 1, c->n1, c->n3, m, c->transb);
     FPSK_HIP(hipStreamSynchronize(st));
+    take_abs();
     tau = head(c)->tau;
     const double cut = head(c)->cut;
     const uint32_t ncand = head(c)->found;

@@ -184,10 +184,27 @@ hipError_t launch_stream(const StreamArgs& s, int dt, bool moments, int rb, int 
 hipError_t launch_product(const ProductArgs& a, int ts, bool kw, bool moments, hipStream_t st,
                           hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
 hipError_t launch_scan_count(const float* C, int64_t n1, int64_t n3, int32_t* counts,
-                             uint32_t* total, hipStream_t st);
-hipError_t launch_scan_extract(const float* C, int64_t n3, const int32_t* rows,
-                               const int32_t* base, int nrows, int32_t cap, int64_t* out,
-                               hipStream_t st);
+                             unsigned long long* total, hipStream_t st);
+// Entries of the exact scan as a patch list (at most keep of them), device memory except host_*.
+struct AbsArgs {
+  int64_t n1;
+  int32_t keep;
+  const int32_t* counts;   // n1
+  int32_t* rowptr;         // n1 + 1
+  int32_t* rows;           // keep rows that hold entries, and each one's first entry
+  int32_t* base;
+  int32_t* nrows;
+  int64_t* coords;         // keep pairs
+  double* gamma;           // keep
+  double* abssum;
+  int32_t* col;
+  float* val;
+  int64_t* host_coords;
+  double* host_gamma;
+};
+hipError_t launch_abs_list(const AbsArgs& g, const uint16_t* A, const uint16_t* B, int64_t bsk,
+                           int64_t bsj, const float* C, int64_t n2, int64_t n3, int dt,
+                           hipStream_t st);
 // B[k][j] is read at B + k * bsk + j * bsj (n3, 1 for B as stored; 1, n2 for W = B^T).
 hipError_t launch_recheck(const uint16_t* A, const uint16_t* B, int64_t bsk, int64_t bsj,
                           const float* C, int64_t n2, int64_t n3, int dt, const int64_t* coords,
@@ -237,7 +254,7 @@ struct RoundArgs {
   HostHead* head;        // may be null
 };
 struct SetupArgs {
-  uint32_t* found;       // exact scan's total (may be null), cleared once published
+  unsigned long long* found;   // exact scan's total (may be null), cleared once published
   const double* sigma;   // two doubles to publish (may be null)
   HostHead* head;
 };

@@ -521,7 +521,8 @@ __device__ __forceinline__ bool is_absolute_entry(float x) {
 // the read of C: 16-byte loads at any alignment, four in flight a thread (4-byte loads read
 // 16384^2 at 3.7 TB/s, 290 us; now 6.9 TB/s, 155 us).
 __global__ __launch_bounds__(kThreads) void scan_count_kernel(const float* C, int64_t n3,
-                                                              int32_t* counts, uint32_t* total) {
+                                                              int32_t* counts,
+                                                              unsigned long long* total) {
   __shared__ int red[kThreads / 64];
   const int64_t row = blockIdx.x;
   const float* c = C + row * n3;
@@ -542,15 +543,75 @@ __global__ __launch_bounds__(kThreads) void scan_count_kernel(const float* C, in
   if (threadIdx.x == 0) {
     const int n = red[0] + red[1] + red[2] + red[3];
     counts[row] = n;
-    if (n > 0) atomicAdd(total, static_cast<uint32_t>(n));
+    if (n > 0) atomicAdd(total, static_cast<unsigned long long>(n));
   }
+}
+
+// The patch list of the scan's entries (at most g.keep, in row-major order), built without a host
+// step in between: one work-group turns the row counts into the CSR row pointers (capped at keep)
+// and the list of rows that hold entries; scan_extract_kernel takes a row per work-group; the
+// recheck recomputes the entries; patch_kernel writes columns and fl32(gamma) for the sketches and
+// publishes coordinates and gamma to the host, which reads them with its next wait.  (Two copies
+// down, five up and three waits took about 150 us of a localization with such entries.)
+__global__ __launch_bounds__(1024) void scan_rows_kernel(AbsArgs g) {
+  __shared__ int64_t wsum[16];
+  __shared__ int64_t carry;
+  __shared__ int nrows;
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  if (t == 0) {
+    carry = 0;
+    nrows = 0;
+  }
+  __syncthreads();
+  for (int64_t i0 = 0; i0 < g.n1; i0 += 1024) {
+    const int64_t i = i0 + t;
+    const int64_t c = i < g.n1 ? g.counts[i] : 0;
+    int64_t incl = c;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int64_t o = __shfl_up(static_cast<long long>(incl), d, 64);
+      if (lane >= d) incl += o;
+    }
+    if (lane == 63) wsum[w] = incl;
+    __syncthreads();
+    int64_t before = carry;
+    for (int v = 0; v < w; ++v) before += wsum[v];
+    const int64_t excl = before + incl - c;
+    if (i < g.n1) {
+      g.rowptr[i] = static_cast<int32_t>(excl < g.keep ? excl : g.keep);
+      if (c > 0 && excl < g.keep) {
+        const int p = atomicAdd(&nrows, 1);           // at most keep rows
+        g.rows[p] = static_cast<int32_t>(i);
+        g.base[p] = static_cast<int32_t>(excl);
+      }
+    }
+    __syncthreads();
+    if (t == 1023) carry = excl + c;
+    __syncthreads();
+  }
+  if (t == 0) {
+    g.rowptr[g.n1] = static_cast<int32_t>(carry < g.keep ? carry : g.keep);
+    *g.nrows = nrows;
+  }
+}
+
+__global__ __launch_bounds__(kThreads) void patch_kernel(AbsArgs g) {
+  const int t = static_cast<int>(blockIdx.x) * kThreads + static_cast<int>(threadIdx.x);
+  if (t >= g.keep) return;
+  g.col[t] = static_cast<int32_t>(g.coords[2 * t + 1]);
+  g.val[t] = static_cast<float>(g.gamma[t]);
+  g.host_coords[2 * t] = g.coords[2 * t];
+  g.host_coords[2 * t + 1] = g.coords[2 * t + 1];
+  g.host_gamma[t] = g.gamma[t];
 }
 
 __global__ __launch_bounds__(kThreads) void scan_extract_kernel(const float* C, int64_t n3,
                                                                 const int32_t* rows,
-                                                                const int32_t* base, int32_t cap,
+                                                                const int32_t* base,
+                                                                const int32_t* nrows, int32_t cap,
                                                                 int64_t* out) {
   __shared__ int wtot[kThreads / 64];
+  if (static_cast<int>(blockIdx.x) >= *nrows) return;
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int64_t row = rows[blockIdx.x];
   int pos = base[blockIdx.x];
@@ -865,6 +926,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_gather_kernel(SelArgs a) {
   const double med = a.st->med;
   const bool keep = l.cnt <= kSelGather;
   uint64_t mn = ~0ull, lo = ~0ull, hi = 0;
+  if (threadIdx.x == 0) l.ncand = 0;
   __syncthreads();
 #pragma unroll 4
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kSelThreads + threadIdx.x; i < a.n;
@@ -872,13 +934,23 @@ __global__ __launch_bounds__(kSelThreads) void sel_gather_kernel(SelArgs a) {
     const uint64_t key = sel_key<MODE>(a, i, med);
     if (!sel_counts<MODE>(key)) continue;
     if ((key & hm) == pref) {
-      if (keep) a.cand[atomicAdd(&a.st->ncand, 1u)] = key;
+      if (keep) {
+        // kept in LDS first: one device-wide atomic per work-group (ties make thousands of keys)
+        const uint32_t p = atomicAdd(&l.ncand, 1u);
+        if (p < kSelRank) l.cand[p] = key;
+        else a.cand[atomicAdd(&a.st->ncand, 1u)] = key;
+      }
       lo = key < lo ? key : lo;
       hi = key > hi ? key : hi;
     } else if (key > top && key < mn) {
       mn = key;
     }
   }
+  __syncthreads();
+  const uint32_t held = l.ncand < kSelRank ? l.ncand : kSelRank;
+  if (threadIdx.x == 0 && held > 0) l.total = atomicAdd(&a.st->ncand, held);
+  __syncthreads();
+  if (threadIdx.x < held) a.cand[l.total + threadIdx.x] = l.cand[threadIdx.x];
   auto fold = [](uint64_t* p, uint64_t v) {
     if (threadIdx.x == 0 && v != ~0ull) {
       atomicMin(reinterpret_cast<unsigned long long*>(p), static_cast<unsigned long long>(v));
@@ -898,7 +970,23 @@ __device__ void sel_finish(SelLds& l, const SelArgs& a, double med) {
   const uint64_t cnt = a.st->cnt2, k = a.st->k2, pref = a.st->pref2, above = a.st->next;
   if (cnt <= kSelGather) {
     const uint64_t* cand = a.cand;
-    block_select(l, [cand](int64_t i) { return cand[i]; }, static_cast<int64_t>(cnt), pref,
+    uint64_t lo = ~0ull, not_hi = ~0ull;
+    if (cnt > kSelRank) {              // ties (zeros of a near-exact product)?
+      for (uint64_t i = threadIdx.x; i < cnt; i += kSelThreads) {
+        const uint64_t x = cand[i];
+        lo = x < lo ? x : lo;
+        not_hi = ~x < not_hi ? ~x : not_hi;
+      }
+      lo = sel_block_min(l, lo);
+      not_hi = sel_block_min(l, not_hi);
+    }
+    if (cnt > kSelRank && lo == ~not_hi) {
+      if (threadIdx.x == 0) {
+        l.sel = lo;
+        l.next = k + 1 < cnt ? lo : above;
+      }
+      __syncthreads();
+    } else block_select(l, [cand](int64_t i) { return cand[i]; }, static_cast<int64_t>(cnt), pref,
                  2 * kSelBits, cnt, k);
     if (threadIdx.x == 0 && l.next == ~0ull) l.next = above;
   } else if (a.st->lo == ~a.st->not_hi) {
@@ -997,7 +1085,8 @@ __global__ __launch_bounds__(kSelThreads) void rms_kernel(SelArgs a, SetupArgs u
   lds_reduce<kSelThreads, 1>(acc, red, 0u);
   if (threadIdx.x == 0) {
     u.head->rms = nf > 0 ? sqrt(acc[0] / static_cast<double>(nf)) : __builtin_nan("");
-    u.head->found = u.found != nullptr ? *u.found : 0u;
+    const unsigned long long f = u.found != nullptr ? *u.found : 0ull;
+    u.head->found = f < 0xffffffffull ? static_cast<uint32_t>(f) : 0xffffffffu;
     u.head->sigma = u.sigma != nullptr ? u.sigma[0] : 0.0;
     u.head->extra = u.sigma != nullptr ? u.sigma[1] : 0.0;
     if (u.found != nullptr) *u.found = 0;       // zero again for the next scan
@@ -1328,18 +1417,22 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
 }
 
 hipError_t launch_scan_count(const float* C, int64_t n1, int64_t n3, int32_t* counts,
-                             uint32_t* total, hipStream_t st) {
+                             unsigned long long* total, hipStream_t st) {
   hipLaunchKernelGGL(scan_count_kernel, dim3(static_cast<unsigned>(n1)), dim3(kThreads), 0, st,
                      C, n3, counts, total);
   return hipGetLastError();
 }
 
-hipError_t launch_scan_extract(const float* C, int64_t n3, const int32_t* rows,
-                               const int32_t* base, int nrows, int32_t cap, int64_t* out,
-                               hipStream_t st) {
-  if (nrows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(scan_extract_kernel, dim3(nrows), dim3(kThreads), 0, st, C, n3, rows, base,
-                     cap, out);
+hipError_t launch_abs_list(const AbsArgs& g, const uint16_t* A, const uint16_t* B, int64_t bsk,
+                           int64_t bsj, const float* C, int64_t n2, int64_t n3, int dt,
+                           hipStream_t st) {
+  hipLaunchKernelGGL(scan_rows_kernel, dim3(1), dim3(1024), 0, st, g);
+  hipLaunchKernelGGL(scan_extract_kernel, dim3(g.keep), dim3(kThreads), 0, st, C, n3, g.rows, g.base,
+                     g.nrows, g.keep, g.coords);
+  const hipError_t e = launch_recheck(A, B, bsk, bsj, nullptr, n2, n3, dt, g.coords, g.keep, g.gamma,
+                                      g.abssum, nullptr, st);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(patch_kernel, dim3((g.keep + kThreads - 1) / kThreads), dim3(kThreads), 0, st, g);
   return hipGetLastError();
 }
 

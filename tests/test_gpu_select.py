@@ -98,3 +98,31 @@ def test_rms_hat(fk, n1, n3, bad):
             # sums of at most 131072 squares in FP64 in another order
             assert math.isclose(got, want, rel_tol=1e-11) and math.isclose(got, host, rel_tol=1e-11)
     v.close()
+
+
+@pytest.mark.parametrize("n1,n3,count,k_cap", [(1, 7, 3, 0), (2500, 300, 40, 0), (2500, 300, 40, 17),
+                                               (1024, 64, 1, 1), (1025, 64, 5000, 64),
+                                               (40, 3000, 2999, 500)])
+def test_scan_entries_in_row_major_order(fk, n1, n3, count, k_cap):
+    """The exact scan's records: the first K out-of-range or non-finite entries in row-major order
+    with their recomputed values, over several groups of 1024 rows, many in one row, more than K."""
+    n2, fmt = 24, "bf16"
+    rng = np.random.default_rng(n1 + count)
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("int", -4, 4), ("int", -4, 4), 6)
+    a64, b64 = o.decode(a_bits, fmt), o.decode(b_bits, fmt)
+    c = (a64 @ b64).astype(np.float32)
+    f = c.reshape(-1)
+    idx = np.sort(rng.choice(f.size, size=count, replace=False))
+    f[idx] = rng.choice(np.array([np.inf, -np.inf, np.nan, 3e38, -2.2e37], dtype=np.float32), size=count)
+    v = fk.Verifier(n1, n2, n3, fmt, m=8, k_cap=k_cap)
+    K = k_cap if k_cap else 128
+    want = idx[:K]
+    for fresh in (True, False):
+        recs, n, _ = v.localize(to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt), to_dev_f32(c),
+                                seed=2, sigma_from_probe=not fresh, cap=8192)
+        absolute = [r for r in recs if r[3]]
+        assert recs[:len(absolute)] == absolute
+        assert [r[0] * n3 + r[1] for r in absolute] == want.tolist()
+        assert all(r[4] == 0 and r[2] == a64[r[0]] @ b64[:, r[1]] for r in absolute)
+        assert v.plan()["n_abs"] == len(want)
+    v.close()
