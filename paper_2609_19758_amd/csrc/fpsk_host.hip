@@ -1189,11 +1189,16 @@ fpsketch_status sketch_round_device(fpsketch_ctx* c, uint64_t seed, int round, i
                   nullptr, nullptr, nullptr, BSide::kStream, false);
 }
 
-// Enqueues the noise of the buckets in the auxiliary workspace (sigma_MAD = 1.4826 median(|S -
-// median S|), selected exactly on the device; even counts take the mean of the two middle order
-// statistics) and the round's thresholds and cut at search radius r.
-fpsketch_status round_cut_device(fpsketch_ctx* c, int r, hipStream_t st) {
+// Candidates of a round kept on the device (more: the host scans the grid).
+constexpr uint32_t kCandCap = 1u << 20;
+
+// Enqueues a round's decisions on the buckets in the auxiliary workspace: the peel, the noise
+// (sigma_MAD = 1.4826 median(|S - median S|), selected exactly; even counts take the mean of the two
+// middle order statistics), the thresholds and cut at search radius r, the buckets above it.
+fpsketch_status round_cut_device(fpsketch_ctx* c, int r, const fpsk::PeelEntry* peel, int npeel,
+                                 hipStream_t st) {
   FPSK_TRY(ensure_selection(c));
+  FPSK_TRY(dev_alloc(c->cands, static_cast<size_t>(kCandCap) * sizeof(fpsk::Cand)));
   const Decomp& d = c->aux_ws.d;
   fpsk::SelArgs a = sel_args(c);
   a.S = as<double>(c->aux_ws.S);
@@ -1205,6 +1210,10 @@ fpsketch_status round_cut_device(fpsketch_ctx* c, int r, hipStream_t st) {
   g.c_n2 = c->p.c_valid * static_cast<double>(c->n2) * std::ldexp(1.0, -23);
   g.mx = static_cast<double>(std::max(c->n1, c->n3));
   g.radius = std::max(static_cast<double>(r), 0.5);
+  g.peel = peel;
+  g.npeel = npeel;
+  g.cands = as<fpsk::Cand>(c->cands);
+  g.cap = kCandCap;
   g.count = as<uint32_t>(c->cand_count);
   g.head = head(c);
   FPSK_HIP(fpsk::launch_round_cut(a, g, st));
@@ -1921,7 +1930,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   if (!sigma_from_probe) {
     const RoundCaps caps = round_caps(seed, 0, c->n1, c->n3, c->m, c->transb);
     FPSK_TRY(sketch_round_device(c, seed, 0, c->m, false, A, B, Cf, prow, pcol, pval, st, caps));
-    FPSK_TRY(round_cut_device(c, 0, st));
+    FPSK_TRY(round_cut_device(c, 0, nullptr, 0, st));
     FPSK_HIP(hipStreamSynchronize(st));
     take_abs();
     sigma = head(c)->sigma;
@@ -1967,13 +1976,8 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
       peel[npeel++] = {o, sv, sv * static_cast<double>(f.i + 1) / L1,
                        sv * static_cast<double>(f.j + 1) / L3};
     }
-    FPSK_HIP(fpsk::launch_peel(dS, peel, npeel, st));
-    FPSK_TRY(round_cut_device(c, r, st));
-    // buckets with |S| > cut, with their sketches; by |S| descending, then bucket index
-    constexpr uint32_t kCandCap = 1u << 20;
-    FPSK_TRY(dev_alloc(c->cands, static_cast<size_t>(kCandCap) * sizeof(fpsk::Cand)));
-    FPSK_HIP(fpsk::launch_above(dS, mm, as<fpsk::SelState>(c->sel_state), as<fpsk::Cand>(c->cands),
-                                kCandCap, as<uint32_t>(c->cand_count), st));
+    // the round's noise, thresholds and buckets with |S| > cut
+    FPSK_TRY(round_cut_device(c, r, peel, npeel, st));
     // R and T (Eq. 2) at the candidates, with the peel terms; with no more than publish of them
     // they come to the host whole, in one wait
     const uint32_t publish = std::min<uint32_t>(kPublish, static_cast<uint32_t>(K));

@@ -244,23 +244,31 @@ struct HostHead {
   uint32_t found;        // buckets above the cut; for the setup entries of the exact scan
   uint32_t pad;
 };
+struct PeelEntry {     // S[o] -= ds, R[o] -= dr, T[o] -= dt (in host memory the device reads)
+  int64_t o;
+  double ds, dr, dt;
+};
+struct Cand {          // a bucket above the cut with its three sketches
+  int64_t o;
+  double s, r, t;
+};
 struct RoundArgs {
   const float* maxpart;
   int nA, nB;
   double c_n2;           // c n2 2^-23
   double mx;             // max(n1, n3)
   double radius;         // max(r, 0.5)
-  uint32_t* count;       // candidate counter, cleared
+  const PeelEntry* peel; // subtracted first (may be null)
+  int npeel;
+  Cand* cands;           // buckets above the cut in any order, at most cap of them (at least
+  uint32_t cap;          // kSelSmall fit)
+  uint32_t* count;       // their number, which may exceed cap
   HostHead* head;        // may be null
 };
 struct SetupArgs {
   unsigned long long* found;   // exact scan's total (may be null), cleared once published
   const double* sigma;   // two doubles to publish (may be null)
   HostHead* head;
-};
-struct PeelEntry {     // S[o] -= ds, R[o] -= dr, T[o] -= dt (in host memory the device reads)
-  int64_t o;
-  double ds, dr, dt;
 };
 // Moment sketches R, T at a list of n buckets o (launch_moments_at): the factors (rows ldp
 // apart, zero from n2 to kact), the npc C-grid partials of R and T, the peel list.
@@ -279,9 +287,9 @@ struct MomentsAtArgs {
   double* t;
   // ... or the *count candidates the device found, written whole to out (host memory) with their
   // number in head->found; nothing is formed when there are more than the launch's n
-  const struct Cand* cands;
+  const Cand* cands;
   const uint32_t* count;
-  struct Cand* out;
+  Cand* out;
   HostHead* head;
 };
 hipError_t launch_moments_at(const MomentsAtArgs& g, int n, hipStream_t st);
@@ -303,21 +311,11 @@ hipError_t launch_publish_stats(const double* stats, double* out, hipStream_t st
 hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st);
 // Zeroes columns [c0, c1) of rows x ld FP32 rows (c1 <= ld).
 hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipStream_t st);
-struct Cand {          // a bucket above the cut with its three sketches
-  int64_t o;
-  double s, r, t;
-};
-hipError_t launch_peel(double* S, const PeelEntry* list, int n, hipStream_t st);
-// Median of S[0 .. n), MAD (even counts: the mean of the two middle order statistics; NaN orders
-// above +inf), then the round's cut (RoundArgs) into the state.
+// A round's decisions on its grid S[0 .. n): the peel, the median and MAD (even counts: the mean
+// of the two middle order statistics; NaN orders above +inf), the cut, and the buckets above it.
 hipError_t launch_round_cut(const SelArgs& a, const RoundArgs& r, hipStream_t st);
 // rms-hat of C from its n samples, and what else the host reads with it.
 hipError_t launch_rms(const SelArgs& a, const SetupArgs& u, hipStream_t st);
-// Appends (o, S) of every bucket with |S[o]| > state->cut to out (at most cap; *count receives
-// the number found, which may exceed cap); the order of the entries is unspecified.
-hipError_t launch_above(const double* S, int64_t n, const SelState* state, Cand* out,
-                        uint32_t cap, uint32_t* count, hipStream_t st);
-
 // The recheck of n search windows of radius r <= kMaxWinR around centers (i, j): outputs
 // [center][di][dj], those outside C left alone.  part: window_slices(n2, n) n (2r + 1)^2 pairs.
 constexpr int kWinRows = 3;

@@ -1050,9 +1050,45 @@ __global__ __launch_bounds__(kSelThreads) void sel_mad_kernel(SelArgs a, RoundAr
   round_cut(a, r, mad, l);
 }
 
-// Small grids: median, MAD and the round's cut in one launch of one work-group.
+// S[o] -= ds of a list, each bucket's entries in list order (one thread takes a bucket's first
+// entry and walks the rest), so the result equals sequential subtraction.  The list is read from
+// host memory once, into LDS, kPeelChunk entries at a time.
+constexpr int kPeelChunk = 512;
+
+struct PeelLds {
+  int64_t o[kPeelChunk];
+  double d[kPeelChunk];
+};
+
+__device__ void peel_list(PeelLds& l, double* S, const PeelEntry* list, int n) {
+  const int t = threadIdx.x;
+  for (int base = 0; base < n; base += kPeelChunk) {
+    const int c = n - base < kPeelChunk ? n - base : kPeelChunk;
+    if (t < c) {
+      l.o[t] = list[base + t].o;
+      l.d[t] = list[base + t].ds;
+    }
+    __syncthreads();
+    bool first = t < c;
+    for (int j = 0; j < t && first; ++j) first = l.o[j] != l.o[t];
+    if (first) {
+      double v = S[l.o[t]];
+      for (int j = t; j < c; ++j) {
+        if (l.o[j] == l.o[t]) v -= l.d[j];
+      }
+      S[l.o[t]] = v;
+    }
+    __syncthreads();
+  }
+}
+
+// Small grids: the peel, median, MAD, the round's cut and its candidates in one launch of one
+// work-group (a launch each cost a 60-bucket round 20 us of its 110).
 __global__ __launch_bounds__(kSelThreads) void sel_small_kernel(SelArgs a, RoundArgs r) {
   __shared__ SelLds l;
+  __shared__ PeelLds pl;
+  __shared__ double cut;
+  if (r.npeel > 0) peel_list(pl, const_cast<double*>(a.S), r.peel, r.npeel);
   const uint64_t n = static_cast<uint64_t>(a.n);
   SelArgs b = a;
   double med = 0.0, mad = 0.0;
@@ -1065,6 +1101,19 @@ __global__ __launch_bounds__(kSelThreads) void sel_small_kernel(SelArgs a, Round
     __syncthreads();
   }
   round_cut(a, r, mad, l);
+  if (threadIdx.x == 0) {
+    cut = a.st->cut;
+    l.ncand = 0;
+  }
+  __syncthreads();
+  const double bar = cut;
+#pragma unroll 4
+  for (int64_t i = threadIdx.x; i < a.n; i += kSelThreads) {
+    const double s = a.S[i];
+    if (fabs(s) > bar) r.cands[atomicAdd(&l.ncand, 1u)] = Cand{i, s, 0.0, 0.0};
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) *r.count = l.ncand;
 }
 
 // rms-hat(C) from the samples: magnitudes clipped at 64 x their median (finite samples only), and
@@ -1093,34 +1142,10 @@ __global__ __launch_bounds__(kSelThreads) void rms_kernel(SelArgs a, SetupArgs u
   }
 }
 
-// S[o] -= ds of a list, each bucket's entries in list order (one thread takes a bucket's first
-// entry and walks the rest), so the result equals sequential subtraction.  The list is read from
-// host memory once, into LDS, kPeelChunk entries at a time.
-constexpr int kPeelChunk = 512;
-
 __global__ __launch_bounds__(kPeelChunk) void peel_kernel(double* S, const PeelEntry* list,
                                                           int n) {
-  __shared__ int64_t o[kPeelChunk];
-  __shared__ double d[kPeelChunk];
-  const int t = threadIdx.x;
-  for (int base = 0; base < n; base += kPeelChunk) {
-    const int c = n - base < kPeelChunk ? n - base : kPeelChunk;
-    if (t < c) {
-      o[t] = list[base + t].o;
-      d[t] = list[base + t].ds;
-    }
-    __syncthreads();
-    bool first = t < c;
-    for (int j = 0; j < t && first; ++j) first = o[j] != o[t];
-    if (first) {
-      double v = S[o[t]];
-      for (int j = t; j < c; ++j) {
-        if (o[j] == o[t]) v -= d[j];
-      }
-      S[o[t]] = v;
-    }
-    __syncthreads();
-  }
+  __shared__ PeelLds l;
+  peel_list(l, S, list, n);
 }
 
 // The moment sketches of Eq. 2 at the selected buckets only: for bucket o = a m + b,
@@ -1436,12 +1461,6 @@ hipError_t launch_abs_list(const AbsArgs& g, const uint16_t* A, const uint16_t* 
   return hipGetLastError();
 }
 
-hipError_t launch_peel(double* S, const PeelEntry* list, int n, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(peel_kernel, dim3(1), dim3(kPeelChunk), 0, st, S, list, n);
-  return hipGetLastError();
-}
-
 namespace {
 unsigned grid_for(int64_t n) {
   const int64_t g = (n + 8 * kThreads - 1) / (8 * kThreads);
@@ -1471,11 +1490,17 @@ hipError_t launch_round_cut(const SelArgs& a0, const RoundArgs& r, hipStream_t s
     hipLaunchKernelGGL(sel_small_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
     return hipGetLastError();
   }
+  if (r.npeel > 0) {
+    hipLaunchKernelGGL(peel_kernel, dim3(1), dim3(kPeelChunk), 0, st, const_cast<double*>(a.S), r.peel,
+                       r.npeel);
+  }
   sel_passes<kSelGrid>(a, st);
   hipLaunchKernelGGL(sel_median_kernel, dim3(1), dim3(kSelThreads), 0, st, a);
   a.dev = 1;
   sel_passes<kSelGrid>(a, st);
   hipLaunchKernelGGL(sel_mad_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
+  hipLaunchKernelGGL(above_kernel, dim3(grid_for(a.n)), dim3(kThreads), 0, st, a.S, a.n, a.st,
+                     r.cands, r.cap, r.count);
   return hipGetLastError();
 }
 
@@ -1534,13 +1559,6 @@ hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st)
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(apply_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, st, C,
                      list, n);
-  return hipGetLastError();
-}
-
-hipError_t launch_above(const double* S, int64_t n, const SelState* state, Cand* out,
-                        uint32_t cap, uint32_t* count, hipStream_t st) {
-  hipLaunchKernelGGL(above_kernel, dim3(grid_for(n)), dim3(kThreads), 0, st, S, n, state, out,
-                     cap, count);
   return hipGetLastError();
 }
 
