@@ -2,8 +2,8 @@
 //
 // Owns the hash rounds (their tables are built by fpsk_tables.hip), the bucket-count rules and the
 // localization plan (Eq. 3-5, Sec. III-G), device workspaces, and the localization driver
-// (Algorithm 2 with Algorithm 1 per round).  Every arithmetic step over A, B and C runs in the
-// kernels of fpsk_kernels.hip; the host handles O(m^2) selection on the dirty path only.
+// (Algorithm 2 with Algorithm 1 per round).  Every step over A, B, C or a bucket grid runs in
+// kernels; the host turns the candidate buckets of a round into records.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

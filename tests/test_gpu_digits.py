@@ -107,3 +107,45 @@ def test_float_operands(fk, n1, n2, n3, m, fmt):
     D = o.abs_contributions(a64, b64, C.cpu().numpy(), hr)[0]
     assert (np.abs(S - ref) <= 2.0 ** -20 * D + 1e-300).all()
     assert np.std(S - ref) <= 0.05 * np.std(ref)
+
+
+@pytest.mark.parametrize("n1,n2,n3,m", [(600, 4100, 500, 300), (900, 1100, 700, 1100),
+                                        (500, 300, 400, 1500)])
+def test_capture(fk, n1, n2, n3, m):
+    """Probes on the digit product and on the work-groups for more than 1024 buckets, captured in a
+    graph and replayed between eager calls, give the eager statistics."""
+    import torch
+    fmt = "bf16"
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("normal", 1.0), ("normal", 0.02), 8)
+    A, B = to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt)
+    C = gemm_f32(A, B)
+    D = C.clone()
+    D[n1 // 2, n3 // 3] += 50.0
+    v = fk.Verifier(n1, n2, n3, fmt, m=m)
+    v.probe(A, B, C)
+    clean = v.probe_stats()
+    v.probe(A, B, D)
+    dirty = v.probe_stats()
+    # With m > n1 most buckets are empty (73% and 93% here), the mean-based noise estimate is low and
+    # the clean product exceeds its threshold (2.4 and 29 times, 0.5 times at m = 300): the oracle's
+    # decision is the one to meet.
+    ref = o.probe(wl.half_bits_to_f32(a_bits, fmt).astype(np.float64),
+                  wl.half_bits_to_f32(b_bits, fmt).astype(np.float64), C.cpu().numpy(),
+                  o.make_round(v.params.seed, 0, n1, n3, m), o.Params())
+    assert bool(clean["dirty"]) == ref.dirty == (m > n1) and dirty["dirty"]
+    assert dirty["max_abs"] > 2 * clean["max_abs"]
+    flag = torch.zeros(1, dtype=torch.int32, device="cuda")
+    g, cap = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    cap.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(cap):
+        with torch.cuda.graph(g, stream=cap):
+            v.probe(A, B, D, d_dirty=flag)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        flag.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert int(flag.item()) == 1 and v.probe_stats() == dirty
+        v.probe(A, B, C)
+        assert v.probe_stats() == clean
+    v.close()
