@@ -77,8 +77,8 @@ struct StreamArgs {
   // small buckets: row-bucket work-groups of four tiles, one per wave (A side; W side with
   // transb), m x ceil(TA / 4) of them
   int wt_a, wt_w;
-  // C work-groups with one column tile per wave, four tiles at a time (256 < m <= 1024,
-  // buckets of at most 32 rows, at least 4 tiles per work-group)
+  // C work-groups with one column tile per wave, four tiles at a time (256 < m <= 1024, or probes
+  // with B as stored at 48 < m <= 192; buckets of at most 32 rows, at least 4 tiles)
   int wt_c;
   // the 4-row probe B work-groups of the one-tile-per-wave instances start at chunk
   // (row block mod TB) and wrap (n3 a whole number of chunks, TB > 1)
