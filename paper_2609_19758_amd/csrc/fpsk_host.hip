@@ -285,11 +285,25 @@ fpsketch_status dev_alloc(DevBuf& b, size_t bytes) {
   return FPSK_OK;
 }
 
-// As dev_alloc, and a new allocation is zero-filled.
+void dev_free(DevBuf& b) {
+  if (b.p != nullptr) (void)hipFree(b.p);
+  b.p = nullptr;
+  b.bytes = 0;
+}
+
+// As dev_alloc, and a new allocation is zero-filled.  The fill runs on the null stream, which the
+// caller's (possibly non-blocking) stream does not wait for, so it is waited for here; a buffer
+// that could not be filled is given back rather than kept with other contents.
 fpsketch_status dev_alloc_zero(DevBuf& b, size_t bytes) {
   if (b.p != nullptr && b.bytes >= bytes) return FPSK_OK;
   FPSK_TRY(dev_alloc(b, bytes));
-  if (bytes != 0) FPSK_HIP(hipMemset(b.p, 0, bytes));
+  if (bytes == 0) return FPSK_OK;
+  hipError_t e = hipMemset(b.p, 0, bytes);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  if (e != hipSuccess) {
+    dev_free(b);
+    return fail(FPSK_EHIP, std::string("zero fill failed: ") + hipGetErrorString(e));
+  }
   return FPSK_OK;
 }
 
@@ -312,12 +326,6 @@ fpsketch_status host_alloc(HostBuf& b, size_t bytes) {
   FPSK_HIP(hipHostMalloc(&b.p, n, hipHostMallocMapped | hipHostMallocCoherent));
   b.bytes = n;
   return FPSK_OK;
-}
-
-void dev_free(DevBuf& b) {
-  if (b.p != nullptr) (void)hipFree(b.p);
-  b.p = nullptr;
-  b.bytes = 0;
 }
 
 template <typename T>

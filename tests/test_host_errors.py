@@ -1,0 +1,118 @@
+"""The library's host code on the CPU: the order of its work on streams, what it leaves behind when
+an allocation or a launch fails, launches within the runtime's limits.
+
+The built library runs against a stand-in for the HIP runtime (host_runtime.cpp: nothing is
+executed, allocations and launches can be made to fail) in a process of its own, where the stand-in
+is loaded before the library and so takes its calls.
+"""
+import ctypes
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+from paper_2609_19758_amd import fpsketch as fk  # noqa: E402
+
+STREAM = 0x1000          # a stream that is not the default one: the stand-in only compares it
+
+
+@pytest.fixture(scope="session")
+def runtime(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("rt") / "libhostrt.so")
+    inc = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__",
+                    f"-I{inc}", f"-I{os.path.join(ROOT, 'paper_2609_19758_amd', 'csrc')}",
+                    f"-I{os.path.join(ROOT, 'include')}", "-o", out,
+                    os.path.join(ROOT, "tests", "host_runtime.cpp")], check=True)
+    return out
+
+
+def _run(runtime, scenario, *args):
+    env = dict(os.environ, PYTHONPATH=ROOT)
+    res = subprocess.run([sys.executable, os.path.abspath(__file__), runtime, scenario,
+                          *map(str, args)], capture_output=True, text=True, timeout=100, env=env)
+    assert res.returncode == 0, res.stdout + res.stderr
+
+
+# ---- in the process of its own -------------------------------------------------------------
+
+
+class Host:
+    """The library on the stand-in, one context, matrices that are never read."""
+
+    def __init__(self, runtime, n1=700, n2=96, n3=600, **params):
+        self.rt = ctypes.CDLL(runtime, mode=ctypes.RTLD_GLOBAL)
+        self.rt.rt_log.restype = self.rt.rt_faults.restype = ctypes.c_char_p
+        self.rt.rt_unordered.restype = ctypes.c_char_p
+        self.rt.rt_blocks.restype = ctypes.c_int64
+        self.rt.rt_noise.argtypes = [ctypes.c_double, ctypes.c_double]
+        self.lib = ctypes.CDLL(fk.LIB_PATH)
+        for name, (res, argtypes) in fk._SIGS.items():
+            fn = getattr(self.lib, name)
+            fn.restype, fn.argtypes = res, argtypes
+        self.n1, self.n2, self.n3 = n1, n2, n3
+        self.p = fk.Params()
+        self.lib.fpsketch_default_params(ctypes.byref(self.p))
+        for k, v in params.items():
+            setattr(self.p, k, v)
+        self.c = None
+
+    def create(self):
+        c = ctypes.c_void_p()
+        s = self.lib.fpsketch_create(self.n1, self.n2, self.n3, fk.BF16, ctypes.byref(self.p),
+                                     ctypes.byref(c))
+        self.c = c if s == fk.OK else None
+        return s
+
+    def localize(self, from_probe=1, cap=64):
+        out, n = (fk.Fault * max(1, cap))(), ctypes.c_int32()
+        buf = ctypes.addressof(out)
+        return self.lib.fpsketch_localize(self.c, buf, buf, buf, fk.F32, 5, from_probe, out, cap,
+                                          ctypes.byref(n), STREAM)
+
+    def log(self):
+        return self.rt.rt_log().decode()
+
+    def grid(self, kernel):
+        """Grid of the last logged launch of a kernel."""
+        return [int(x) for x in re.findall(rf"{kernel}\w* (\d+) \d+ \d+\n", self.log())][-1]
+
+    def check(self):
+        assert self.rt.rt_faults() == b"", self.rt.rt_faults().decode()
+
+
+def fills(h):
+    """Kernels on a stream of the caller's run after the zero fills of the buffers they use."""
+    h.rt.rt_scan_total(3)
+    assert h.create() == fk.OK
+    buf = ctypes.addressof(h.p)
+    for _ in range(2):
+        assert h.lib.fpsketch_probe(h.c, buf, buf, buf, fk.F32, None, STREAM) == fk.OK
+        assert h.lib.fpsketch_probe_deferred(h.c, buf, buf, buf, fk.F32, None, STREAM) == fk.OK
+        assert h.lib.fpsketch_cache_b(h.c, buf, STREAM) == fk.OK
+        assert h.localize(0) == fk.OK and h.localize(1) == fk.OK
+    assert h.rt.rt_unordered() == b"", h.rt.rt_unordered().decode()
+    h.lib.fpsketch_destroy(h.c)
+
+
+SCENARIOS = {"fills": (fills, {})}
+
+
+# ---- the tests -------------------------------------------------------------------------------
+
+
+@pytest.mark.parametrize("name", sorted(SCENARIOS))
+def test_host(runtime, name):
+    _run(runtime, name)
+
+
+if __name__ == "__main__":
+    fn, kw = SCENARIOS[sys.argv[2]]
+    fn(Host(sys.argv[1], **kw))
+    print("ok")
