@@ -1061,10 +1061,10 @@ fpsk::SelArgs sel_args(fpsketch_ctx* c) {
   return a;
 }
 
-// Enqueues rms-hat(C) (Sec. III-G: strided samples, clipped at 64 x their median) and publishes
-// it in head(c) with the exact scan's total (`found`, may be null) and two doubles at `sigma`.
-fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, unsigned long long* found,
-                               const double* sigma, hipStream_t st) {
+// Enqueues rms-hat(C) (Sec. III-G: strided samples, clipped at 64 x their median) and, with scan,
+// the exact scan's counts; publishes rms-hat, the scan's total and two doubles at `sigma` in head(c).
+fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, bool scan, const double* sigma,
+                               hipStream_t st) {
   const int64_t total = c->n1 * c->n3;
   const int64_t stride = std::max<int64_t>(1, total / 65536);
   const int64_t count = (total + stride - 1) / stride;
@@ -1076,7 +1076,15 @@ fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, unsigned long lo
   a.stride = stride;
   a.n = count;
   fpsk::SetupArgs u{};
-  u.found = found;
+  if (scan) {
+    FPSK_TRY(dev_alloc(c->scan_counts, static_cast<size_t>(c->n1) * sizeof(int32_t)));
+    FPSK_TRY(dev_alloc(c->scan_total, sizeof(unsigned long long)));
+    u.C = C;
+    u.n1 = c->n1;
+    u.n3 = c->n3;
+    u.counts = as<int32_t>(c->scan_counts);
+    u.found = as<unsigned long long>(c->scan_total);
+  }
   u.sigma = sigma;
   u.head = head(c);
   FPSK_HIP(fpsk::launch_rms(a, u, st));
@@ -1113,7 +1121,7 @@ fpsketch_status recheck_coords(fpsketch_ctx* c, const void* A, const void* B, co
 }
 
 // Enqueues the exact scan's entries (Sec. III-I: the first `keep` in row-major order, counted by
-// launch_scan_count), their recomputation and the patch list for the sketches; coordinates and
+// rms_hat_device), their recomputation and the patch list for the sketches; coordinates and
 // recomputed values reach host_abs (keep pairs, then keep doubles) with the next wait.
 fpsketch_status abs_list(fpsketch_ctx* c, const void* A, const void* B, const float* C, int32_t keep,
                          hipStream_t st) {
@@ -1853,8 +1861,7 @@ fpsketch_status fpsketch_calibrate_noise(fpsketch_ctx* c, const void* C, fpsketc
   FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
-  FPSK_TRY(rms_hat_device(c, static_cast<const float*>(C), nullptr, as<double>(c->sigma_acc),
-                          st));
+  FPSK_TRY(rms_hat_device(c, static_cast<const float*>(C), false, as<double>(c->sigma_acc), st));
   FPSK_HIP(hipStreamSynchronize(st));
   const double acc[2] = {head(c)->sigma, head(c)->extra};
   const double sigma_bar = acc[1] > 0 ? acc[0] / acc[1] : std::nan("");
@@ -1902,11 +1909,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
 
   // 1. Exact scan and absolute recompute (Sec. III-I; Algorithm 2).
   // rms-hat(C) and the last probe's noise are read with the scan's total: one wait.
-  FPSK_TRY(dev_alloc(c->scan_counts, static_cast<size_t>(c->n1) * sizeof(int32_t)));
-  FPSK_TRY(dev_alloc_zero(c->scan_total, sizeof(unsigned long long)));
-  FPSK_HIP(fpsk::launch_scan_count(Cf, c->n1, c->n3, as<int32_t>(c->scan_counts),
-                                   as<unsigned long long>(c->scan_total), st));
-  FPSK_TRY(rms_hat_device(c, Cf, as<unsigned long long>(c->scan_total), as<double>(c->stats), st));
+  FPSK_TRY(rms_hat_device(c, Cf, true, as<double>(c->stats), st));
   FPSK_HIP(hipStreamSynchronize(st));
   const double rms = head(c)->rms;
   double sigma = head(c)->sigma;

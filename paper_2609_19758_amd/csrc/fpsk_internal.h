@@ -183,8 +183,6 @@ hipError_t launch_stream(const StreamArgs& s, int dt, bool moments, int rb, int 
 // ts, kw: product tile edge and whether its k-range is split over the 4 waves
 hipError_t launch_product(const ProductArgs& a, int ts, bool kw, bool moments, hipStream_t st,
                           hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr);
-hipError_t launch_scan_count(const float* C, int64_t n1, int64_t n3, int32_t* counts,
-                             unsigned long long* total, hipStream_t st);
 // Entries of the exact scan as a patch list (at most keep of them), device memory except host_*.
 struct AbsArgs {
   int64_t n1;
@@ -234,6 +232,7 @@ struct SelArgs {
   uint32_t* hist;        // 2 x 4096
   uint64_t* cand;        // kSelGather
   int dev;               // 1: |S - state->med| in place of S
+  unsigned long long* clear;   // samples: a total that the first pass sets to zero (may be null)
 };
 // Figures of a localize step in host memory (written by a kernel, read after the stream is
 // waited for).
@@ -266,7 +265,11 @@ struct RoundArgs {
   HostHead* head;        // may be null
 };
 struct SetupArgs {
-  unsigned long long* found;   // exact scan's total (may be null), cleared once published
+  // exact scan of C (n1 x n3): entries of each row, and their total (null: no scan)
+  const float* C;
+  int64_t n1, n3;
+  int32_t* counts;
+  unsigned long long* found;
   const double* sigma;   // two doubles to publish (may be null)
   HostHead* head;
 };
@@ -314,7 +317,7 @@ hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipSt
 // A round's decisions on its grid S[0 .. n): the peel, the median and MAD (even counts: the mean
 // of the two middle order statistics; NaN orders above +inf), the cut, and the buckets above it.
 hipError_t launch_round_cut(const SelArgs& a, const RoundArgs& r, hipStream_t st);
-// rms-hat of C from its n samples, and what else the host reads with it.
+// rms-hat of C from its n samples, the exact scan's counts, and what else the host reads with them.
 hipError_t launch_rms(const SelArgs& a, const SetupArgs& u, hipStream_t st);
 // The recheck of n search windows of radius r <= kMaxWinR around centers (i, j): outputs
 // [center][di][dj], those outside C left alone.  part: window_slices(n2, n) n (2r + 1)^2 pairs.

@@ -517,7 +517,8 @@ __device__ __forceinline__ bool is_absolute_entry(float x) {
   return !(fabsf(x) <= static_cast<float>(kHugeLimit));
 }
 
-// Entries of the exact scan in each row of C, one work-group per row, added to *total.  Bound by
+// Entries of the exact scan in each row of C, one work-group per row, added to *total (set to zero
+// by an earlier launch of the same call: a call that fails part way leaves nothing for the next).  Bound by
 // the read of C: 16-byte loads at any alignment, four in flight a thread (4-byte loads read
 // 16384^2 at 3.7 TB/s, 290 us; now 6.9 TB/s, 155 us).
 __global__ __launch_bounds__(kThreads) void scan_count_kernel(const float* C, int64_t n3,
@@ -848,6 +849,7 @@ __device__ __forceinline__ void sel_flush(const SelLds& l, uint32_t* hist) {
 template <int MODE>
 __global__ __launch_bounds__(kSelThreads) void sel_hist1_kernel(SelArgs a) {
   __shared__ SelLds l;
+  if (MODE == kSelAbs && a.clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0;
   sel_zero(l);
   const double med = a.st->med;
 #pragma unroll 4
@@ -1138,7 +1140,6 @@ __global__ __launch_bounds__(kSelThreads) void rms_kernel(SelArgs a, SetupArgs u
     u.head->found = f < 0xffffffffull ? static_cast<uint32_t>(f) : 0xffffffffu;
     u.head->sigma = u.sigma != nullptr ? u.sigma[0] : 0.0;
     u.head->extra = u.sigma != nullptr ? u.sigma[1] : 0.0;
-    if (u.found != nullptr) *u.found = 0;       // zero again for the next scan
   }
 }
 
@@ -1441,13 +1442,6 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_scan_count(const float* C, int64_t n1, int64_t n3, int32_t* counts,
-                             unsigned long long* total, hipStream_t st) {
-  hipLaunchKernelGGL(scan_count_kernel, dim3(static_cast<unsigned>(n1)), dim3(kThreads), 0, st,
-                     C, n3, counts, total);
-  return hipGetLastError();
-}
-
 hipError_t launch_abs_list(const AbsArgs& g, const uint16_t* A, const uint16_t* B, int64_t bsk,
                            int64_t bsj, const float* C, int64_t n2, int64_t n3, int dt,
                            hipStream_t st) {
@@ -1504,9 +1498,15 @@ hipError_t launch_round_cut(const SelArgs& a0, const RoundArgs& r, hipStream_t s
   return hipGetLastError();
 }
 
-hipError_t launch_rms(const SelArgs& a, const SetupArgs& u, hipStream_t st) {
+hipError_t launch_rms(const SelArgs& a0, const SetupArgs& u, hipStream_t st) {
+  SelArgs a = a0;
   if (a.n <= 0) return hipErrorInvalidValue;
+  a.clear = u.found;
   sel_passes<kSelAbs>(a, st);
+  if (u.found != nullptr) {
+    hipLaunchKernelGGL(scan_count_kernel, dim3(static_cast<unsigned>(u.n1)), dim3(kThreads), 0, st,
+                       u.C, u.n3, u.counts, u.found);
+  }
   hipLaunchKernelGGL(rms_kernel, dim3(1), dim3(kSelThreads), 0, st, a, u);
   return hipGetLastError();
 }

@@ -69,7 +69,9 @@ void emulate(const std::string& k, void** args) {
   if (k.find("scan_count_kernel") != std::string::npos) {
     *arg<unsigned long long*>(args, 3) += g_scan_total;
   } else if (k.find("sel_hist1_kernel") != std::string::npos) {
-    selection(arg<fpsk::SelArgs>(args, 0), true);
+    const auto& a = arg<fpsk::SelArgs>(args, 0);
+    selection(a, true);
+    if (a.clear != nullptr) *a.clear = 0;
   } else if (k.find("sel_median_kernel") != std::string::npos) {
     selection(arg<fpsk::SelArgs>(args, 0), false);
   } else if (k.find("rms_kernel") != std::string::npos) {

@@ -87,6 +87,56 @@ class Host:
         assert self.rt.rt_faults() == b"", self.rt.rt_faults().decode()
 
 
+def _failing(h, call, each):
+    """Runs `call` with its 1st, 2nd, ... allocation failing until none fails, a new context each;
+    `each(status)` after every failed call."""
+    n = 0
+    while True:
+        n += 1
+        h.rt.rt_reset()
+        assert h.create() == fk.OK
+        h.rt.rt_fail_alloc(n)
+        s = call()
+        failed = h.rt.rt_alloc_pending() == 0
+        h.rt.rt_fail_alloc(0)
+        if failed:
+            assert s == fk.ENOMEM
+            each(s)
+        else:
+            assert s == fk.OK
+        h.lib.fpsketch_destroy(h.c)
+        if not failed:
+            return n - 1
+
+
+def _kernels(log):
+    return [ln.split()[0] for ln in log.splitlines()]
+
+
+def scan_total(h):
+    """A retry after a localization that failed part way extracts the entries that C holds."""
+    h.rt.rt_scan_total(3)
+
+    def again(_):
+        h.rt.rt_reset()
+        assert h.localize() == fk.OK
+        assert h.grid("scan_extract_kernel") == 3
+    assert _failing(h, h.localize, again) >= 5
+    # and after any one launch of it that failed
+    assert h.create() == fk.OK and h.localize() == fk.OK
+    h.rt.rt_reset()
+    assert h.localize() == fk.OK
+    names = _kernels(h.log())
+    assert len(names) > 20
+    for k in sorted(set(names)):
+        h.rt.rt_reset()
+        h.rt.rt_fail_kernel(k.encode())
+        s = h.localize()
+        assert s == fk.ENOMEM, (k, s)
+        again(s)
+    h.lib.fpsketch_destroy(h.c)
+
+
 def fills(h):
     """Kernels on a stream of the caller's run after the zero fills of the buffers they use."""
     h.rt.rt_scan_total(3)
@@ -101,7 +151,7 @@ def fills(h):
     h.lib.fpsketch_destroy(h.c)
 
 
-SCENARIOS = {"fills": (fills, {})}
+SCENARIOS = {"fills": (fills, {}), "scan_total": (scan_total, {})}
 
 
 # ---- the tests -------------------------------------------------------------------------------
