@@ -1053,6 +1053,15 @@ fpsketch_status ensure_selection(fpsketch_ctx* c) {
   return host_alloc(c->host_head, sizeof(fpsk::HostHead) + kPublish * sizeof(fpsk::Cand));
 }
 
+// A selection leaves its histograms empty for the next one.  After a launch of it that failed they
+// may hold counts: they are given back (which waits for the device), and the next call gets new ones.
+fpsketch_status selection_enqueued(fpsketch_ctx* c, hipError_t e) {
+  if (e == hipSuccess) return FPSK_OK;
+  dev_free(c->sel_hist);
+  return fail(e == hipErrorOutOfMemory ? FPSK_ENOMEM : FPSK_EHIP,
+              std::string("selection failed: ") + hipGetErrorString(e));
+}
+
 fpsk::SelArgs sel_args(fpsketch_ctx* c) {
   fpsk::SelArgs a{};
   a.st = as<fpsk::SelState>(c->sel_state);
@@ -1087,8 +1096,7 @@ fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, bool scan, const
   }
   u.sigma = sigma;
   u.head = head(c);
-  FPSK_HIP(fpsk::launch_rms(a, u, st));
-  return FPSK_OK;
+  return selection_enqueued(c, fpsk::launch_rms(a, u, st));
 }
 
 // Recheck a list of coordinates: gamma, sum |A||B| and C_ij, for coords (n pairs at the start of
@@ -1232,8 +1240,7 @@ fpsketch_status round_cut_device(fpsketch_ctx* c, int r, const fpsk::PeelEntry* 
   g.cap = kCandCap;
   g.count = as<uint32_t>(c->cand_count);
   g.head = head(c);
-  FPSK_HIP(fpsk::launch_round_cut(a, g, st));
-  return FPSK_OK;
+  return selection_enqueued(c, fpsk::launch_round_cut(a, g, st));
 }
 
 struct Found {

@@ -137,6 +137,21 @@ def scan_total(h):
     h.lib.fpsketch_destroy(h.c)
 
 
+def selection_state(h):
+    """The noise selection's histograms are empty again after any launch that failed (a grid above
+    one work-group's size, noise of its own)."""
+    h.rt.rt_scan_total(0)
+    assert h.create() == fk.OK and h.localize(0) == fk.OK
+    for k in sorted(set(_kernels(h.log()))):
+        h.rt.rt_reset()
+        h.rt.rt_fail_kernel(k.encode())
+        h.localize(0)
+        h.rt.rt_reset()
+        assert h.localize(0) == fk.OK
+        h.check()
+    h.lib.fpsketch_destroy(h.c)
+
+
 def fills(h):
     """Kernels on a stream of the caller's run after the zero fills of the buffers they use."""
     h.rt.rt_scan_total(3)
@@ -151,7 +166,8 @@ def fills(h):
     h.lib.fpsketch_destroy(h.c)
 
 
-SCENARIOS = {"fills": (fills, {}), "scan_total": (scan_total, {})}
+SCENARIOS = {"fills": (fills, {}), "scan_total": (scan_total, {}),
+             "selection_state": (selection_state, {"m": 200})}
 
 
 # ---- the tests -------------------------------------------------------------------------------
