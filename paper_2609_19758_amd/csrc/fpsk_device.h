@@ -204,15 +204,29 @@ __device__ float block_absmax_half(uint32_t mx, uint32_t* ldsu) {
 // A launch whose dispatch packet, when e0 / e1 are given, records its own start / end time in
 // them (no extra queue packets, so the events bracket exactly the kernel).
 template <typename K, typename... Args>
-static void launch_k(K kernel, dim3 grid, dim3 block, size_t shmem, hipStream_t st, hipEvent_t e0,
-                     hipEvent_t e1, Args... args) {
+static hipError_t launch_k(K kernel, dim3 grid, dim3 block, size_t shmem, hipStream_t st,
+                           hipEvent_t e0, hipEvent_t e1, Args... args) {
   if (e0 != nullptr || e1 != nullptr) {
     hipExtLaunchKernelGGL(kernel, grid, block, static_cast<uint32_t>(shmem), st, e0, e1, 0u,
                           args...);
   } else {
     hipLaunchKernelGGL(kernel, grid, block, shmem, st, args...);
   }
+  return hipGetLastError();
 }
+
+// One launch of a sequence: the launcher returns at the first that fails, since the kernels after
+// it take indices and counts from what it writes.
+#define FPSK_LAUNCH(kernel, grid, block, shmem, st, ...)                                        \
+  do {                                                                                          \
+    const hipError_t e_ = launch_k(kernel, grid, block, shmem, st, nullptr, nullptr, __VA_ARGS__); \
+    if (e_ != hipSuccess) return e_;                                                            \
+  } while (0)
+#define FPSK_LAUNCH_TIMED(kernel, grid, block, shmem, st, e0, e1, ...)                          \
+  do {                                                                                          \
+    const hipError_t e_ = launch_k(kernel, grid, block, shmem, st, e0, e1, __VA_ARGS__);        \
+    if (e_ != hipSuccess) return e_;                                                            \
+  } while (0)
 
 // ----------------------------------------------------------------------------------------
 // Work-group timeline, compiled only with FPSK_WG_TIMELINE (a diagnostic build of the library;

@@ -300,13 +300,11 @@ hipError_t launch_digit_product(const ProductArgs& a, hipStream_t st, hipEvent_t
   if (a.ts != 64 || a.ksl % 32 != 0 || a.ksl > kDigitMaxK) return hipErrorInvalidValue;
   const int nbP = (a.m + 127) / 128 * 4, nbQ = (a.m + 63) / 64 * 2;
   const int KS = (a.n2 + 31) / 32;
-  launch_k(row_scale_kernel, dim3(2 * a.m), dim3(kThreads), 0, st, e0, nullptr, a);
-  launch_k(digits_kernel, dim3((KS + 3) / 4, nbP + nbQ), dim3(kThreads), 0, st, nullptr, nullptr, a,
-           nbP);
+  FPSK_LAUNCH_TIMED(row_scale_kernel, dim3(2 * a.m), dim3(kThreads), 0, st, e0, nullptr, a);
+  FPSK_LAUNCH(digits_kernel, dim3((KS + 3) / 4, nbP + nbQ), dim3(kThreads), 0, st, a, nbP);
   const int wgs = (a.m + 127) / 128 * ((a.m + 63) / 64) * a.NS;
-  launch_k(digit_product_kernel, dim3((wgs + 7) / 8 * 8), dim3(kThreads), 0, st, nullptr, nullptr, a,
-           a.zero);
-  return hipGetLastError();
+  FPSK_LAUNCH(digit_product_kernel, dim3((wgs + 7) / 8 * 8), dim3(kThreads), 0, st, a, a.zero);
+  return hipSuccess;
 }
 
 }  // namespace fpsk

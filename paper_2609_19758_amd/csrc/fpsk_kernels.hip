@@ -1402,13 +1402,12 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
   if (a.mode == 1 && !moments && a.nX > 0) {
     const dim3 g(a.nX), b(kThreads);
     switch (a.xb) {
-      case 1: launch_k(block_product_kernel<1>, g, b, 0, st, e0, nullptr, a); break;
-      case 2: launch_k(block_product_kernel<2>, g, b, 0, st, e0, nullptr, a); break;
-      case 3: launch_k(block_product_kernel<3>, g, b, 0, st, e0, nullptr, a); break;
-      default: launch_k(block_product_kernel<4>, g, b, 0, st, e0, nullptr, a); break;
+      case 1: FPSK_LAUNCH_TIMED(block_product_kernel<1>, g, b, 0, st, e0, nullptr, a); break;
+      case 2: FPSK_LAUNCH_TIMED(block_product_kernel<2>, g, b, 0, st, e0, nullptr, a); break;
+      case 3: FPSK_LAUNCH_TIMED(block_product_kernel<3>, g, b, 0, st, e0, nullptr, a); break;
+      default: FPSK_LAUNCH_TIMED(block_product_kernel<4>, g, b, 0, st, e0, nullptr, a); break;
     }
-    launch_k(block_decide_kernel, dim3(1), dim3(kDecideThreads), 0, st, nullptr, e1, a);
-    return hipGetLastError();
+    return launch_k(block_decide_kernel, dim3(1), dim3(kDecideThreads), 0, st, nullptr, e1, a);
   }
   const dim3 grid((a.nt * a.nt * a.NS + 7) / 8 * 8);     // whole rounds of the 8 XCDs
   const dim3 rgrid(a.nt * a.nt);
@@ -1422,17 +1421,17 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
   }
 #define FPSK_PRODUCT_CASE(TS_, WB_, KW_, MOM_)                                              \
   if (ts == TS_ && kw == KW_ && moments == MOM_) {                                          \
-    launch_k(mfma_product_kernel<WB_, KW_, MOM_>, grid, dim3(kThreads), 0, st, e0,          \
-             (red || dec) ? nullptr : e1, a);                                               \
+    FPSK_LAUNCH_TIMED((mfma_product_kernel<WB_, KW_, MOM_>), grid, dim3(kThreads), 0, st, e0, \
+                      (red || dec) ? nullptr : e1, a);                                      \
     if (red) {                                                                              \
-      launch_k(reduce_kernel<TS_, MOM_>, rgrid, dim3(kThreads), 0, st, nullptr,             \
-               dec ? nullptr : e1, a);                                                      \
+      FPSK_LAUNCH_TIMED((reduce_kernel<TS_, MOM_>), rgrid, dim3(kThreads), 0, st, nullptr,  \
+                        dec ? nullptr : e1, a);                                             \
     }                                                                                       \
-    if (dec && a.clip_tiles) {                                                              \
-      launch_k(clip_kernel, rgrid, dim3(kThreads), 0, st, nullptr, nullptr, a);             \
+    if (dec && a.clip_tiles) FPSK_LAUNCH(clip_kernel, rgrid, dim3(kThreads), 0, st, a);     \
+    if (dec) {                                                                              \
+      FPSK_LAUNCH_TIMED(tile_decide_kernel, dim3(1), dim3(kDecideThreads), 0, st, nullptr, e1, a); \
     }                                                                                       \
-    if (dec) launch_k(tile_decide_kernel, dim3(1), dim3(kDecideThreads), 0, st, nullptr, e1, a); \
-    return hipGetLastError();                                                               \
+    return hipSuccess;                                                                      \
   }
   FPSK_PRODUCT_CASE(16, 1, true, false)
   FPSK_PRODUCT_CASE(64, 2, false, false)
@@ -1445,14 +1444,14 @@ hipError_t launch_product(const ProductArgs& a0, int ts, bool kw, bool moments, 
 hipError_t launch_abs_list(const AbsArgs& g, const uint16_t* A, const uint16_t* B, int64_t bsk,
                            int64_t bsj, const float* C, int64_t n2, int64_t n3, int dt,
                            hipStream_t st) {
-  hipLaunchKernelGGL(scan_rows_kernel, dim3(1), dim3(1024), 0, st, g);
-  hipLaunchKernelGGL(scan_extract_kernel, dim3(g.keep), dim3(kThreads), 0, st, C, n3, g.rows, g.base,
+  FPSK_LAUNCH(scan_rows_kernel, dim3(1), dim3(1024), 0, st, g);
+  FPSK_LAUNCH(scan_extract_kernel, dim3(g.keep), dim3(kThreads), 0, st, C, n3, g.rows, g.base,
                      g.nrows, g.keep, g.coords);
   const hipError_t e = launch_recheck(A, B, bsk, bsj, nullptr, n2, n3, dt, g.coords, g.keep, g.gamma,
                                       g.abssum, nullptr, st);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(patch_kernel, dim3((g.keep + kThreads - 1) / kThreads), dim3(kThreads), 0, st, g);
-  return hipGetLastError();
+  FPSK_LAUNCH(patch_kernel, dim3((g.keep + kThreads - 1) / kThreads), dim3(kThreads), 0, st, g);
+  return hipSuccess;
 }
 
 namespace {
@@ -1469,11 +1468,12 @@ unsigned sel_grid(int64_t n) {
 }
 
 template <int MODE>
-void sel_passes(const SelArgs& a, hipStream_t st) {
+hipError_t sel_passes(const SelArgs& a, hipStream_t st) {
   const dim3 g(sel_grid(a.n)), b(kSelThreads);
-  hipLaunchKernelGGL(sel_hist1_kernel<MODE>, g, b, 0, st, a);
-  hipLaunchKernelGGL(sel_hist2_kernel<MODE>, g, b, 0, st, a);
-  hipLaunchKernelGGL(sel_gather_kernel<MODE>, g, b, 0, st, a);
+  FPSK_LAUNCH(sel_hist1_kernel<MODE>, g, b, 0, st, a);
+  FPSK_LAUNCH(sel_hist2_kernel<MODE>, g, b, 0, st, a);
+  FPSK_LAUNCH(sel_gather_kernel<MODE>, g, b, 0, st, a);
+  return hipSuccess;
 }
 }  // namespace
 
@@ -1481,34 +1481,37 @@ hipError_t launch_round_cut(const SelArgs& a0, const RoundArgs& r, hipStream_t s
   SelArgs a = a0;
   if (a.n <= 0) return hipErrorInvalidValue;
   if (a.n <= kSelSmall) {
-    hipLaunchKernelGGL(sel_small_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
-    return hipGetLastError();
+    FPSK_LAUNCH(sel_small_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
+    return hipSuccess;
   }
   if (r.npeel > 0) {
-    hipLaunchKernelGGL(peel_kernel, dim3(1), dim3(kPeelChunk), 0, st, const_cast<double*>(a.S), r.peel,
+    FPSK_LAUNCH(peel_kernel, dim3(1), dim3(kPeelChunk), 0, st, const_cast<double*>(a.S), r.peel,
                        r.npeel);
   }
-  sel_passes<kSelGrid>(a, st);
-  hipLaunchKernelGGL(sel_median_kernel, dim3(1), dim3(kSelThreads), 0, st, a);
+  hipError_t e = sel_passes<kSelGrid>(a, st);
+  if (e != hipSuccess) return e;
+  FPSK_LAUNCH(sel_median_kernel, dim3(1), dim3(kSelThreads), 0, st, a);
   a.dev = 1;
-  sel_passes<kSelGrid>(a, st);
-  hipLaunchKernelGGL(sel_mad_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
-  hipLaunchKernelGGL(above_kernel, dim3(grid_for(a.n)), dim3(kThreads), 0, st, a.S, a.n, a.st,
+  e = sel_passes<kSelGrid>(a, st);
+  if (e != hipSuccess) return e;
+  FPSK_LAUNCH(sel_mad_kernel, dim3(1), dim3(kSelThreads), 0, st, a, r);
+  FPSK_LAUNCH(above_kernel, dim3(grid_for(a.n)), dim3(kThreads), 0, st, a.S, a.n, a.st,
                      r.cands, r.cap, r.count);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_rms(const SelArgs& a0, const SetupArgs& u, hipStream_t st) {
   SelArgs a = a0;
   if (a.n <= 0) return hipErrorInvalidValue;
   a.clear = u.found;
-  sel_passes<kSelAbs>(a, st);
+  const hipError_t e = sel_passes<kSelAbs>(a, st);
+  if (e != hipSuccess) return e;
   if (u.found != nullptr) {
-    hipLaunchKernelGGL(scan_count_kernel, dim3(static_cast<unsigned>(u.n1)), dim3(kThreads), 0, st,
+    FPSK_LAUNCH(scan_count_kernel, dim3(static_cast<unsigned>(u.n1)), dim3(kThreads), 0, st,
                        u.C, u.n3, u.counts, u.found);
   }
-  hipLaunchKernelGGL(rms_kernel, dim3(1), dim3(kSelThreads), 0, st, a, u);
-  return hipGetLastError();
+  FPSK_LAUNCH(rms_kernel, dim3(1), dim3(kSelThreads), 0, st, a, u);
+  return hipSuccess;
 }
 
 // Zeroes columns [c0, c1) of `rows` rows of a row-major FP32 matrix whose rows are ld apart.
@@ -1528,8 +1531,8 @@ hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipSt
   if (c0 < 0 || c1 > ld) return hipErrorInvalidValue;
   const int64_t total = static_cast<int64_t>(rows) * (c1 - c0);
   const int grid = static_cast<int>(std::min<int64_t>(256, (total + kThreads - 1) / kThreads));
-  hipLaunchKernelGGL(zero_cols_kernel, dim3(grid), dim3(kThreads), 0, st, base, rows, ld, c0, c1);
-  return hipGetLastError();
+  FPSK_LAUNCH(zero_cols_kernel, dim3(grid), dim3(kThreads), 0, st, base, rows, ld, c0, c1);
+  return hipSuccess;
 }
 
 // The 8 probe statistics to host memory: a launch and the caller's wait, without the staging of
@@ -1539,8 +1542,8 @@ __global__ __launch_bounds__(64) void publish_stats_kernel(const double* stats, 
 }
 
 hipError_t launch_publish_stats(const double* stats, double* out, hipStream_t st) {
-  hipLaunchKernelGGL(publish_stats_kernel, dim3(1), dim3(64), 0, st, stats, out);
-  return hipGetLastError();
+  FPSK_LAUNCH(publish_stats_kernel, dim3(1), dim3(64), 0, st, stats, out);
+  return hipSuccess;
 }
 
 // Copies of matrices of fewer than 8 elements into 32-byte slots (zero past them): thread t of
@@ -1551,21 +1554,21 @@ __global__ __launch_bounds__(64) void pad_tiny_kernel(PadTinyArgs a) {
 }
 
 hipError_t launch_pad_tiny(const PadTinyArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(pad_tiny_kernel, dim3(3), dim3(64), 0, st, a);
-  return hipGetLastError();
+  FPSK_LAUNCH(pad_tiny_kernel, dim3(3), dim3(64), 0, st, a);
+  return hipSuccess;
 }
 
 hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(apply_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, st, C,
+  FPSK_LAUNCH(apply_kernel, dim3((n + kThreads - 1) / kThreads), dim3(kThreads), 0, st, C,
                      list, n);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_moments_at(const MomentsAtArgs& g, int n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(moments_at_kernel, dim3(static_cast<unsigned>(n)), dim3(kThreads), 0, st, g);
-  return hipGetLastError();
+  FPSK_LAUNCH(moments_at_kernel, dim3(static_cast<unsigned>(n)), dim3(kThreads), 0, st, g);
+  return hipSuccess;
 }
 
 hipError_t launch_recheck(const uint16_t* A, const uint16_t* B, int64_t bsk, int64_t bsj,
@@ -1574,13 +1577,13 @@ hipError_t launch_recheck(const uint16_t* A, const uint16_t* B, int64_t bsk, int
   if (n <= 0) return hipSuccess;
   const unsigned grid = static_cast<unsigned>((n + 3) / 4);
   if (dt == 1) {
-    hipLaunchKernelGGL(recheck_kernel<1>, dim3(grid), dim3(kThreads), 0, st, A, B, bsk, bsj, C,
+    FPSK_LAUNCH(recheck_kernel<1>, dim3(grid), dim3(kThreads), 0, st, A, B, bsk, bsj, C,
                        n2, n3, coords, n, gamma, abssum, cval);
   } else {
-    hipLaunchKernelGGL(recheck_kernel<0>, dim3(grid), dim3(kThreads), 0, st, A, B, bsk, bsj, C,
+    FPSK_LAUNCH(recheck_kernel<0>, dim3(grid), dim3(kThreads), 0, st, A, B, bsk, bsj, C,
                        n2, n3, coords, n, gamma, abssum, cval);
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 int window_slices(int64_t n2, int n) {
@@ -1601,26 +1604,26 @@ hipError_t launch_windows(const WindowArgs& g0, int dt, hipStream_t st) {
   slices = static_cast<int>((g.n2 + g.ks - 1) / g.ks);
   const dim3 grid(g.n, (wd + kWinRows - 1) / kWinRows, slices);
   if (dt == 1) {
-    hipLaunchKernelGGL(window_kernel<1>, grid, dim3(kThreads), 0, st, g);
+    FPSK_LAUNCH(window_kernel<1>, grid, dim3(kThreads), 0, st, g);
   } else {
-    hipLaunchKernelGGL(window_kernel<0>, grid, dim3(kThreads), 0, st, g);
+    FPSK_LAUNCH(window_kernel<0>, grid, dim3(kThreads), 0, st, g);
   }
   const int64_t total = static_cast<int64_t>(g.n) * wd * wd;
-  hipLaunchKernelGGL(window_sum_kernel, dim3(static_cast<unsigned>((total + kThreads - 1) / kThreads)),
+  FPSK_LAUNCH(window_sum_kernel, dim3(static_cast<unsigned>((total + kThreads - 1) / kThreads)),
                      dim3(kThreads), 0, st, g, slices);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_read(const void* src, int64_t bytes, uint32_t* out, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(read_kernel, dim3(grid), dim3(kThreads), 0, st,
+  FPSK_LAUNCH(read_kernel, dim3(grid), dim3(kThreads), 0, st,
                      static_cast<const u32x4*>(src), bytes / 16, out);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, int grid, hipStream_t st) {
-  hipLaunchKernelGGL(copy_kernel, dim3(grid), dim3(kThreads), 0, st,
+  FPSK_LAUNCH(copy_kernel, dim3(grid), dim3(kThreads), 0, st,
                      static_cast<const u32x4*>(src), static_cast<u32x4*>(dst), bytes / 16);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace fpsk

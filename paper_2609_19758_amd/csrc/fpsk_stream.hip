@@ -1361,12 +1361,12 @@ size_t probe_pipe_lds(int xb) {
 }
 
 template <int DT, bool VEC, int XB, bool WTC>
-static void pipe_launch(const StreamArgs& s, const ProductArgs& prod, const ProductArgs& dec,
-                        int nprod, int has_dec, size_t lds, hipStream_t st, hipEvent_t e0,
-                        hipEvent_t e1) {
+static hipError_t pipe_launch(const StreamArgs& s, const ProductArgs& prod, const ProductArgs& dec,
+                              int nprod, int has_dec, size_t lds, hipStream_t st, hipEvent_t e0,
+                              hipEvent_t e1) {
   const dim3 grid(8 + (s.nC + s.nB + s.nA + 7) / 8 * 8 + nprod);
-  launch_k(probe_pipe_kernel<DT, VEC, XB, WTC>, grid, dim3(kThreads), lds, st, e0, e1, s, prod,
-           dec, nprod, has_dec);
+  return launch_k(probe_pipe_kernel<DT, VEC, XB, WTC>, grid, dim3(kThreads), lds, st, e0, e1, s,
+                  prod, dec, nprod, has_dec);
 }
 
 template <int DT, bool VEC, bool WTC>
@@ -1374,12 +1374,11 @@ static hipError_t pipe_dispatch(const StreamArgs& s, const ProductArgs& prod,
                                 const ProductArgs& dec, int nprod, int has_dec, int xb,
                                 size_t lds, hipStream_t st, hipEvent_t e0, hipEvent_t e1) {
   switch (xb) {
-    case 1: pipe_launch<DT, VEC, 1, WTC>(s, prod, dec, nprod, has_dec, lds, st, e0, e1); break;
-    case 2: pipe_launch<DT, VEC, 2, WTC>(s, prod, dec, nprod, has_dec, lds, st, e0, e1); break;
-    case 3: pipe_launch<DT, VEC, 3, WTC>(s, prod, dec, nprod, has_dec, lds, st, e0, e1); break;
+    case 1: return pipe_launch<DT, VEC, 1, WTC>(s, prod, dec, nprod, has_dec, lds, st, e0, e1);
+    case 2: return pipe_launch<DT, VEC, 2, WTC>(s, prod, dec, nprod, has_dec, lds, st, e0, e1);
+    case 3: return pipe_launch<DT, VEC, 3, WTC>(s, prod, dec, nprod, has_dec, lds, st, e0, e1);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 hipError_t launch_probe_pipe(const StreamArgs& s, const ProductArgs& prod, const ProductArgs& dec,
@@ -1411,25 +1410,17 @@ static hipError_t stream_dispatch(const StreamArgs& s, int rb, int g, int ng, si
   // one-tile-per-wave C work-groups: their own instances (at G = 1 only the probe's)
   const bool wtc = s.wt_c && !(g == 1 && MOM);
 #define FPSK_STREAM_LAUNCH(RB_, G_, NG_, VEC_, WTC_)                                          \
-  launch_k(stream_kernel<DT, MOM, RB_, G_, NG_, VEC_, WTC_>, dim3(grid), dim3(kThreads), lds, st, \
-           e0, e1, s)
+  launch_k(stream_kernel<DT, MOM, RB_, G_, NG_, VEC_, WTC_>, dim3(grid), dim3(kThreads), lds, \
+           st, e0, e1, s)
 #define FPSK_STREAM_CASE(RB_, G_, NG_)                                                        \
   if (rb == RB_ && g == G_ && ng == NG_) {                                                    \
-    if (vec) {                                                                                \
-      FPSK_STREAM_LAUNCH(RB_, G_, NG_, true, false);                                          \
-    } else {                                                                                  \
-      FPSK_STREAM_LAUNCH(RB_, G_, NG_, false, false);                                         \
-    }                                                                                         \
-    return hipGetLastError();                                                                 \
+    return vec ? FPSK_STREAM_LAUNCH(RB_, G_, NG_, true, false)                                \
+               : FPSK_STREAM_LAUNCH(RB_, G_, NG_, false, false);                              \
   }
 #define FPSK_STREAM_WTC_CASE(RB_, G_, NG_)                                                    \
   if (wtc && rb == RB_ && g == G_ && ng == NG_) {                                             \
-    if (vec) {                                                                                \
-      FPSK_STREAM_LAUNCH(RB_, G_, NG_, true, true);                                           \
-    } else {                                                                                  \
-      FPSK_STREAM_LAUNCH(RB_, G_, NG_, false, true);                                          \
-    }                                                                                         \
-    return hipGetLastError();                                                                 \
+    return vec ? FPSK_STREAM_LAUNCH(RB_, G_, NG_, true, true)                                 \
+               : FPSK_STREAM_LAUNCH(RB_, G_, NG_, false, true);                               \
   }
   if constexpr (!MOM) {
     FPSK_STREAM_WTC_CASE(4, 1, 1)

@@ -242,18 +242,18 @@ hipError_t launch_tables(const TableArgs& a, hipStream_t st) {
   const int64_t g1 = a.pad1 / 8, g3 = a.pad3 / 8;
   const int nb1 = static_cast<int>((g1 + kThreads - 1) / kThreads);
   const int nb3 = static_cast<int>((g3 + kThreads - 1) / kThreads);
-  hipLaunchKernelGGL(hash_kernel, dim3(nb1 + nb3), dim3(kThreads), 0, st, a, nb1);
+  FPSK_LAUNCH(hash_kernel, dim3(nb1 + nb3), dim3(kThreads), 0, st, a, nb1);
   if (a.slot != nullptr) {
-    hipLaunchKernelGGL(order_kernel, dim3((a.m + 1023) / 1024), dim3(1024), 0, st, a);
+    FPSK_LAUNCH(order_kernel, dim3((a.m + 1023) / 1024), dim3(1024), 0, st, a);
   }
   const int kWaves = kTableThreads / 64;
   const int np = (a.m + kWaves - 1) / kWaves, np2 = a.perm2 != nullptr ? np : 0;
   const int stride = a.c.stride > a.b.stride ? a.c.stride : a.b.stride;
   const size_t lds = static_cast<size_t>((a.m + 3) / 4 * 4) * 4 +
                      static_cast<size_t>((a.m + 1 + 7) / 8 * 8) * 2 + static_cast<size_t>(stride) * 2;
-  hipLaunchKernelGGL(tables_kernel, dim3(a.c.tiles + a.b.tiles + np + np2),
+  FPSK_LAUNCH(tables_kernel, dim3(a.c.tiles + a.b.tiles + np + np2),
                      dim3(kTableThreads), lds, st, a, np, np2);
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 }  // namespace fpsk

@@ -320,8 +320,7 @@ static hipError_t wide_launch(K kernel, int grid, size_t lds, hipStream_t st, hi
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            static_cast<int>(lds));
   if (e != hipSuccess) return e;
-  launch_k(kernel, dim3(grid), dim3(kWideThreads), lds, st, e0, e1, s);
-  return hipGetLastError();
+  return launch_k(kernel, dim3(grid), dim3(kWideThreads), lds, st, e0, e1, s);
 }
 
 hipError_t launch_wide_c(const StreamArgs& s, bool mom, hipStream_t st, hipEvent_t e0,

@@ -166,7 +166,29 @@ def fills(h):
     h.lib.fpsketch_destroy(h.c)
 
 
-SCENARIOS = {"fills": (fills, {}), "scan_total": (scan_total, {}),
+def sequence(h):
+    """After a launch that failed none of the kernels that take its results runs: the call ends with
+    it.  Probes on every product path and m above 1024, a localization with noise of its own."""
+    h.rt.rt_scan_total(3)
+    buf = ctypes.addressof(h.p)
+    calls = {"probe": lambda: h.lib.fpsketch_probe(h.c, buf, buf, buf, fk.F32, None, STREAM),
+             "localize": lambda: h.localize(0)}
+    for m, n2 in [(48, 96), (200, 96), (300, 4096), (1100, 96)]:
+        h.p.m, h.n2 = m, n2
+        assert h.create() == fk.OK
+        for call in calls.values():
+            h.rt.rt_reset()
+            assert call() == fk.OK
+            for k in dict.fromkeys(_kernels(h.log())):
+                h.rt.rt_reset()
+                h.rt.rt_fail_kernel(k.encode())
+                assert call() == fk.ENOMEM, (m, k)
+                assert _kernels(h.log())[-1] == k, (m, k, h.log())
+        h.rt.rt_reset()
+        h.lib.fpsketch_destroy(h.c)
+
+
+SCENARIOS = {"sequence": (sequence, {}), "fills": (fills, {}), "scan_total": (scan_total, {}),
              "selection_state": (selection_state, {"m": 200})}
 
 
