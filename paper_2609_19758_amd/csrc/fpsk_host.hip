@@ -778,6 +778,21 @@ fpsketch_status set_device(const fpsketch_ctx* c) {
   return FPSK_OK;
 }
 
+// A synchronous call that returns early waits for what it has enqueued: its kernels read the
+// caller's matrices and use host memory that the next call writes.
+class WaitOnReturn {
+ public:
+  explicit WaitOnReturn(hipStream_t st) : st_(st) {}
+  ~WaitOnReturn() {
+    if (!waited_) (void)hipStreamSynchronize(st_);
+  }
+  void waited() { waited_ = true; }      // nothing has been enqueued since the last wait
+
+ private:
+  hipStream_t st_;
+  bool waited_ = false;
+};
+
 // How a pass treats the B side: streamed, only filled into the context's cache (no product),
 // or taken from that cache (A and C streamed).
 enum class BSide { kStream, kFillCache, kUseCache };
@@ -1767,8 +1782,10 @@ fpsketch_status fpsketch_sketch(fpsketch_ctx* c, const void* A, const void* B, c
   FPSK_TRY(pipe_flush(c, st));
   std::vector<double> hS, hR, hT;
   double ma = 0, mb = 0;
+  WaitOnReturn wait(st);
   FPSK_TRY(sketch_round(c, seed, round, m, moments != 0, A, B, static_cast<const float*>(C),
                         nullptr, nullptr, nullptr, st, hS, hR, hT, &ma, &mb));
+  wait.waited();
   std::memcpy(S, hS.data(), hS.size() * sizeof(double));
   if (moments) {
     std::memcpy(R, hR.data(), hR.size() * sizeof(double));
@@ -1801,6 +1818,7 @@ fpsketch_status fpsketch_recheck(fpsketch_ctx* c, const void* A, const void* B,
   FPSK_TRY(pipe_flush(c, st));
   if (n == 0) return FPSK_OK;
   const size_t nn = static_cast<size_t>(n);
+  WaitOnReturn wait(st);
   FPSK_TRY(dev_alloc(c->rc_coords, 2 * nn * sizeof(int64_t)));
   FPSK_TRY(dev_alloc(c->rc_gamma, nn * sizeof(double)));
   FPSK_TRY(dev_alloc(c->rc_abs, nn * sizeof(double)));
@@ -1815,6 +1833,7 @@ fpsketch_status fpsketch_recheck(fpsketch_ctx* c, const void* A, const void* B,
   FPSK_HIP(hipMemcpyAsync(gamma, c->rc_gamma.p, nn * sizeof(double), hipMemcpyDeviceToHost, st));
   FPSK_HIP(hipMemcpyAsync(abssum, c->rc_abs.p, nn * sizeof(double), hipMemcpyDeviceToHost, st));
   FPSK_HIP(hipStreamSynchronize(st));
+  wait.waited();
   return FPSK_OK;
 }
 
@@ -1841,6 +1860,7 @@ fpsketch_status fpsketch_apply(fpsketch_ctx* c, const void* A, const void* B, vo
   }
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
+  WaitOnReturn wait(st);
   float* Cm = static_cast<float*>(C);
   // re-probe with a fresh round at the probe's m; its statistics go to host memory
   const int m = c->m;
@@ -1855,6 +1875,7 @@ fpsketch_status fpsketch_apply(fpsketch_ctx* c, const void* A, const void* B, vo
   FPSK_TRY(run_pass(c, c->aux_round, c->aux_ws, A, B, Cm, false, 1, nullptr, nullptr, nullptr,
                     nullptr, st, nullptr, stt, as<double>(c->reprobe_acc)));
   FPSK_HIP(hipStreamSynchronize(st));
+  wait.waited();
   *still_dirty = stt[5] != 0.0 ? 1 : 0;
   return FPSK_OK;
 }
@@ -1868,6 +1889,7 @@ fpsketch_status fpsketch_calibrate_noise(fpsketch_ctx* c, const void* C, fpsketc
   FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
+  WaitOnReturn wait(st);
   FPSK_TRY(rms_hat_device(c, static_cast<const float*>(C), false, as<double>(c->sigma_acc), st));
   FPSK_HIP(hipStreamSynchronize(st));
   const double acc[2] = {head(c)->sigma, head(c)->extra};
@@ -1893,6 +1915,7 @@ fpsketch_status fpsketch_calibrate_noise(fpsketch_ctx* c, const void* C, fpsketc
       FPSK_HIP(hipStreamSynchronize(st));
     }
   }
+  wait.waited();
   if (m_out) *m_out = c->m;
   if (sigma_bar_out) *sigma_bar_out = sigma_bar;
   if (rebuilt_out) *rebuilt_out = rebuilt;
@@ -1910,6 +1933,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
   FPSK_TRY(set_device(c));
   const hipStream_t st = static_cast<hipStream_t>(stream);
   FPSK_TRY(pipe_flush(c, st));
+  WaitOnReturn wait(st);
   const float* Cf = static_cast<const float*>(C);
   const int32_t K = cap_K(c->p);
   std::vector<Found> F;
@@ -2148,6 +2172,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     }
   }
 
+  wait.waited();           // (the last round ended with a wait, or none of its work is pending)
   c->last_plan.m = c->m;
   c->last_plan.m_loc = plan.m_loc;
   c->last_plan.r = plan.r;

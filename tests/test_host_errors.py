@@ -188,7 +188,47 @@ def sequence(h):
         h.lib.fpsketch_destroy(h.c)
 
 
-SCENARIOS = {"sequence": (sequence, {}), "fills": (fills, {}), "scan_total": (scan_total, {}),
+def waits(h):
+    """A synchronous call that fails leaves no work behind on its stream: the caller may free its
+    matrices, and the next call reuses the host memory that kernels read and write."""
+    h.rt.rt_scan_total(3)
+    buf = ctypes.addressof(h.p)
+    recs = (fk.Fault * 2)()
+    recs[1].i = 1
+    still, m_out = ctypes.c_int32(), ctypes.c_int32()
+    D = ctypes.c_double
+    grid, coord = (D * (48 * 48))(), (ctypes.c_int64 * 4)()
+    lib = h.lib
+    calls = [
+        lambda: h.localize(0), lambda: h.localize(1),
+        lambda: lib.fpsketch_apply(h.c, buf, buf, buf, fk.F32, recs, 2, 9, ctypes.byref(still), STREAM),
+        lambda: lib.fpsketch_sketch(h.c, buf, buf, buf, fk.F32, 4, 1, 48, 1, grid, grid, grid, None, STREAM),
+        lambda: lib.fpsketch_recheck(h.c, buf, buf, coord, 2, grid, grid, STREAM),
+        lambda: lib.fpsketch_calibrate_noise(h.c, buf, fk.F32, STREAM, ctypes.byref(m_out), None, None)]
+    for i, call in enumerate(calls):
+        def idle(what):
+            assert h.rt.rt_busy() == 0, (i, what)
+        assert _failing(h, call, idle) >= 1
+        assert h.create() == fk.OK
+        h.rt.rt_reset()
+        assert call() == fk.OK
+        for k in dict.fromkeys(_kernels(h.log())):
+            h.rt.rt_reset()
+            h.rt.rt_fail_kernel(k.encode())
+            assert call() == fk.ENOMEM
+            idle(k)
+        h.rt.rt_reset()
+        lib.fpsketch_destroy(h.c)
+    # a plan for more buckets than the kernels take, with the scan's entries being recomputed
+    h.n1 = h.n3 = 20000
+    h.rt.rt_noise(1.0, 1e6)
+    assert h.create() == fk.OK
+    assert h.localize(1) == fk.ESHAPE
+    assert h.rt.rt_busy() == 0
+
+
+SCENARIOS = {"waits": (waits, {"m": 48}),
+             "sequence": (sequence, {}), "fills": (fills, {}), "scan_total": (scan_total, {}),
              "selection_state": (selection_state, {"m": 200})}
 
 
