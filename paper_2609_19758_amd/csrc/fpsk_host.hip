@@ -1027,17 +1027,30 @@ fpsketch_status pipe_flush(fpsketch_ctx* c, hipStream_t next_st) {
   return FPSK_OK;
 }
 
+// The probe's tables and workspace for m buckets.  They are built beside the present ones and take
+// their place when all is there: a failure (memory, a launch) leaves the context as it was.
 fpsketch_status build_probe(fpsketch_ctx* c, int m, hipStream_t st) {
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, false, c->transb);
   const RoundCaps caps = round_caps(c->p.seed, 0, c->n1, c->n3, m, c->transb);
-  FPSK_TRY(build_round(c->p.seed, 0, caps, c->n1, c->n3, d, false, c->transb, true,
-                       c->probe_round, st));
-  // the probes that read the tables may run on other streams
-  FPSK_HIP(hipStreamSynchronize(st));
-  FPSK_TRY(ensure_workspace(c->probe_ws, c->n1, c->n2, c->n3, m, false, c->transb));
-  c->m = m;
-  c->qcache_m = 0;      // a cached B side belongs to the previous round
-  return FPSK_OK;
+  DevRound round;
+  Workspace ws;
+  auto build = [&]() -> fpsketch_status {
+    FPSK_TRY(ensure_workspace(ws, c->n1, c->n2, c->n3, m, false, c->transb));
+    FPSK_TRY(build_round(c->p.seed, 0, caps, c->n1, c->n3, d, false, c->transb, true, round, st));
+    // the probes that read the tables may run on other streams
+    FPSK_HIP(hipStreamSynchronize(st));
+    return FPSK_OK;
+  };
+  const fpsketch_status s = build();
+  if (s == FPSK_OK) {
+    std::swap(round, c->probe_round);
+    std::swap(ws, c->probe_ws);
+    c->m = m;
+    c->qcache_m = 0;      // a cached B side belongs to the previous round
+  }
+  free_round(round);
+  free_workspace(ws);
+  return s;
 }
 
 fpsketch_status check_matrices(const fpsketch_ctx* c, const void* A, const void* B,

@@ -19,6 +19,7 @@ namespace {
 
 std::map<const void*, std::string> g_names;      // host stub of a kernel -> its name
 std::map<void*, size_t> g_blocks;
+std::set<const void*> g_lists;                   // row lists that tables_kernel has written
 std::set<void*> g_busy;                          // streams with unfinished work
 std::string g_log, g_faults, g_unordered, g_fail_kernel;
 int g_fail_alloc = 0, g_scan_total = 0, g_candidates = 0;
@@ -51,6 +52,7 @@ hipError_t release(void* p) {
     return hipErrorInvalidValue;
   }
   munmap(p, it->second);
+  g_lists.erase(p);
   g_blocks.erase(it);
   return hipSuccess;
 }
@@ -58,6 +60,21 @@ hipError_t release(void* p) {
 template <typename T>
 const T& arg(void** args, int i) {
   return *static_cast<const T*>(args[i]);
+}
+
+// Pointers into allocations that exist (a probe's stream pass: lists, tables, factors).
+void check_pointers(const std::string& k, void** args) {
+  if (k.find("stream_kernel") == std::string::npos) return;
+  const auto& s = arg<fpsk::StreamArgs>(args, 0);
+  for (const void* p : {static_cast<const void*>(s.perm), static_cast<const void*>(s.ctab),
+                        static_cast<const void*>(s.coff), static_cast<const void*>(s.P),
+                        static_cast<const void*>(s.Q), static_cast<const void*>(s.partS),
+                        static_cast<const void*>(s.maxpart)}) {
+    if (g_blocks.find(const_cast<void*>(p)) == g_blocks.end()) {
+      g_faults += k + " got memory that is not allocated; ";
+    }
+  }
+  if (g_lists.count(s.perm) == 0) g_faults += k + " got row lists that no kernel has written; ";
 }
 
 // What a kernel would leave for the host or for the kernels after it.
@@ -112,6 +129,8 @@ hipError_t launch(const void* f, dim3 grid, dim3 block, void** args, size_t shme
     g_unordered += k + " does not wait for the null stream's fill; ";
   }
   g_busy.insert(st);
+  check_pointers(k, args);
+  if (k.find("tables_kernel") != std::string::npos) g_lists.insert(arg<fpsk::TableArgs>(args, 0).perm);
   emulate(k, args);
   return hipSuccess;
 }

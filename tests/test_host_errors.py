@@ -227,7 +227,51 @@ def waits(h):
     assert h.rt.rt_busy() == 0
 
 
-SCENARIOS = {"waits": (waits, {"m": 48}),
+def rebuild(h):
+    """A recalibration whose rebuild fails leaves the context as it was: the same probe as before it,
+    from buffers that are all there."""
+    buf = ctypes.addressof(h.p)
+    got = ctypes.c_int32()
+
+    def probe():
+        h.rt.rt_reset()
+        assert h.lib.fpsketch_probe(h.c, buf, buf, buf, fk.F32, None, STREAM) == fk.OK
+        h.check()                  # no kernel got a null or freed pointer
+        return h.log()
+
+    def recalibrate():
+        return h.lib.fpsketch_calibrate_noise(h.c, buf, fk.F32, STREAM, None, None, ctypes.byref(got))
+
+    # for more buckets and for fewer
+    for m, noise in [(48, 0.5), (300, 1e-9)]:
+        h.p.m = m
+        h.rt.rt_noise(1.0, noise)
+        assert h.create() == fk.OK
+        first = probe()
+        h.lib.fpsketch_destroy(h.c)
+
+        def same(_):
+            m_now = ctypes.c_int32()
+            h.lib.fpsketch_get_m(h.c, ctypes.byref(m_now))
+            assert m_now.value == m
+            assert probe() == first
+        assert _failing(h, recalibrate, same) >= 5
+        assert h.create() == fk.OK
+        h.rt.rt_reset()
+        assert recalibrate() == fk.OK and got.value == 1
+        names = dict.fromkeys(_kernels(h.log()))
+        h.lib.fpsketch_destroy(h.c)
+        for k in names:
+            assert h.create() == fk.OK
+            h.rt.rt_reset()
+            h.rt.rt_fail_kernel(k.encode())
+            assert recalibrate() == fk.ENOMEM
+            same(k)
+            h.lib.fpsketch_destroy(h.c)
+
+
+SCENARIOS = {"rebuild": (rebuild, {}),
+             "waits": (waits, {"m": 48}),
              "sequence": (sequence, {}), "fills": (fills, {}), "scan_total": (scan_total, {}),
              "selection_state": (selection_state, {"m": 200})}
 
