@@ -209,10 +209,11 @@ __device__ void column_tile(const TableArgs& a, const ColTable& t, int tile, cha
   for (int q = off[m] + tid; q < t.stride; q += NT) tab[q] = static_cast<uint16_t>(t.W);
 }
 
-__global__ __launch_bounds__(kTableThreads) void tables_kernel(TableArgs a, int nperm, int nperm2) {
+__global__ __launch_bounds__(kTableThreads) void tables_kernel(TableArgs a, int nperm, int nperm2,
+                                                                int first) {
   extern __shared__ char lds_tab[];
   constexpr int kWaves = kTableThreads / 64;
-  int u = blockIdx.x;
+  int u = first + static_cast<int>(blockIdx.x);
   const int nct = a.c.tiles + a.b.tiles;
   if (u < nct) {                    // the longer work first
     if (u < a.b.tiles) column_tile(a, a.b, u, lds_tab);
@@ -251,8 +252,13 @@ hipError_t launch_tables(const TableArgs& a, hipStream_t st) {
   const int stride = a.c.stride > a.b.stride ? a.c.stride : a.b.stride;
   const size_t lds = static_cast<size_t>((a.m + 3) / 4 * 4) * 4 +
                      static_cast<size_t>((a.m + 1 + 7) / 8 * 8) * 2 + static_cast<size_t>(stride) * 2;
-  FPSK_LAUNCH(tables_kernel, dim3(a.c.tiles + a.b.tiles + np + np2),
-                     dim3(kTableThreads), lds, st, a, np, np2);
+  // (a launch holds fewer than 2^32 threads: rows of 2^31 columns are more tiles than that)
+  const int total = a.c.tiles + a.b.tiles + np + np2;
+  constexpr int kMost = 1 << 21;
+  for (int first = 0; first < total; first += kMost) {
+    const int n = total - first < kMost ? total - first : kMost;
+    FPSK_LAUNCH(tables_kernel, dim3(n), dim3(kTableThreads), lds, st, a, np, np2, first);
+  }
   return hipSuccess;
 }
 

@@ -270,7 +270,19 @@ def rebuild(h):
             h.lib.fpsketch_destroy(h.c)
 
 
-SCENARIOS = {"rebuild": (rebuild, {}),
+def largest(h):
+    """Contexts of the longest rows and columns: every launch is within the runtime's limits."""
+    for n1, n3 in [(1, 2 ** 31 - 1), (2 ** 27, 3)]:
+        h.n1, h.n2, h.n3 = n1, 1, n3
+        assert h.create() == fk.OK
+        buf = ctypes.addressof(h.p)
+        assert h.lib.fpsketch_probe(h.c, buf, buf, buf, fk.F32, None, STREAM) == fk.OK
+        h.check()
+        h.lib.fpsketch_destroy(h.c)
+
+
+SCENARIOS = {"largest": (largest, {"m": 3}),
+             "rebuild": (rebuild, {}),
              "waits": (waits, {"m": 48}),
              "sequence": (sequence, {}), "fills": (fills, {}), "scan_total": (scan_total, {}),
              "selection_state": (selection_state, {"m": 200})}
