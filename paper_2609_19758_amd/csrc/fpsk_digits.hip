@@ -1,22 +1,41 @@
 // The bucket-space product S = P Q - S_C on the integer matrix cores (S alone, more than 240
-// buckets a side, n2 >= 512).
+// buckets a side, n2 >= 512, m^2 n2 >= 2^28).
 //
-// Each row of a factor is scaled by a power of two to 32-bit integers and split into four signed
-// 8-bit digits, x 2^e = d0 2^24 + d1 2^16 + d2 2^8 + d3.  All 16 digit products are formed, exact in
-// 32-bit sums over at most 16384 k (grouped by i + j into seven accumulators), and joined in 64-bit
-// integers, so P Q is exact but for entries with bits below 2^-31 of their row's largest.  A row
-// takes part when it is finite and its largest entry is at most 32 x its mean magnitude (5 x for a
-// Gaussian row): its typical entries then keep more bits than the FP32 factors hold.  Tiles with
-// another row are left to the FP64 matrix cores, whose kernel runs beside this one and takes only
-// those.  Error of S against 64 bits (rms over the noise), before and now: 4096^3 BF16, m = 1000
-// 1.283022712e-3 both; 16384^3 FP16, m = 698 4.676957421e-3 both; the two differ by 1e-12 to 1e-10.
+// A product of floating-point matrices as a sum of exact integer products is the scheme of Ozaki,
+// Ogita, Oishi and Rump (2012), here on 8-bit integers as in Ootomo, Ozaki and Yokota (2024).  Each
+// row of a factor is scaled by a power of two to 32-bit integers and split into four signed 8-bit
+// digits, x 2^e = d0 2^24 + d1 2^16 + d2 2^8 + d3.  All 16 digit products are formed, exact in 32-bit
+// sums over at most 16384 k (grouped by i + j into seven accumulators), and joined in 64-bit
+// integers, so P Q is exact but for entries with bits below 2^-31 of their row's largest.
+//
+// What those bits cost depends on both factors: an entry's quantum is its row's, and it is
+// multiplied by the other factor's entries at the same k.  Two measures keep it below the rounding
+// of the FP32 factors themselves:
+//   - channel k of P is multiplied by 2^t and of Q by 2^-t (exact, and nothing in the product), t
+//     half the difference of the channel's typical exponents in Q and in P, so that a channel which
+//     is small in one factor and large in the other is of middle size in both.  Channels scaled
+//     by 1e-6 in A (half of them) and in B (the others) gave S errors of 1855 times the noise without
+//     it, 0.0023 times with it, as the FP64 product does (2048 x 4096 x 2048, m = 260, BF16).
+//   - a row takes part when its quantum u adds at most about a quarter of the FP32 rounding to S:
+//     u^2 / 12 sum_k s_k^2 <= 1/15 2^-50.7 sum_k (x_k s_k)^2, s_k the channel's typical size in the
+//     other factor (equal for both after the scaling), 2^-50.7 the mean square of FP32 rounding
+//     relative to the values.  A Gaussian row has a 50 times smaller left side, one with a channel 30
+//     times the others' still a smaller one.  Rows that are not finite do not take part.
+// The typical sizes are means of the exponents over 64 buckets a factor, zeros left out: the
+// buckets are random sums of rows, and a mean of logarithms is not moved by a few rows of another
+// scale.  Tiles with a row that takes no part are left to the FP64 matrix cores, whose kernel runs
+// beside this one and takes only those.
+//
+// Error of S against 64 bits (rms over the noise), FP64 product and here: 2048 x 4096 x 2048,
+// m = 260, BF16 0.002402 both, FP16 0.004215 both; 4096^3 BF16, m = 1000 0.001302 both; channels scaled
+// by 1e-2 to 1e-6 as above likewise equal to four digits.
 // (13 pairs, i + j <= 4, in 64 x 32 wave tiles of five accumulators were as fast and raised FP16
 // errors by 0.1 %.)
 //
 // Bound by the integer matrix cores: 16 x 2 m^2 n2 operations at 1/64 of the FP64 cores' time each.
-// 16384^3 FP16, m = 4096: FP64 8400 us -> 3370 us with the row scales and the digits (the product
-// 3070 us, 2.9 x 10^15 operations a second of the 4.7 x 10^15 that registers alone reach); m = 698:
-// 275 -> 163 us; 4096^3, m = 432: 79 -> 37 us.
+// 16384^3 FP16, m = 4096: FP64 8400 us -> 3655 us (product 3340, digits 175, row scales 131, channels
+// 6), 2.6 x 10^15 operations a second of the 4.7 x 10^15 that registers alone reach; m = 698: 301 ->
+// 187 us; 4096^3, m = 432: 43 us and 15 us of slice sums -> 40 and 8 us.
 #include "fpsk_device.h"
 
 namespace fpsk {
@@ -24,54 +43,140 @@ namespace fpsk {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
-// Scale exponent e of each row (2m work-groups: rows of P, then of Q): x 2^e rounds to integers
-// whose four signed digits exist, |x 2^e| <= 2^31 - 2^24; kNoDigits for a row that is not taken.
-__global__ __launch_bounds__(kThreads) void row_scale_kernel(ProductArgs pa) {
-  __shared__ float smax[kThreads / 64];
-  __shared__ float ssum[kThreads / 64];
-  const int r = blockIdx.x;
-  const float* x = r < pa.m ? pa.P + static_cast<int64_t>(r) * pa.ldp
-                            : pa.Q + static_cast<int64_t>(r - pa.m) * pa.ldp;
-  float mx = 0.0f, sum = 0.0f;
-#pragma unroll 4
-  for (int k = 4 * threadIdx.x; k < pa.kact; k += 4 * kThreads) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(x + k);
+// Channel figures: the power of two t that balances channel k (low byte), and the binary logarithm
+// v of its typical size in both factors once balanced (high byte; kNoSize where a factor's sample
+// holds only zeros).  A work-group takes 128 channels; a thread 4 of them in 8 of the 64 sampled rows
+// of each factor.  A channel without a size in one factor is scaled out of the other: a row that
+// has an entry there after all is then too far from its typical size to take part.
+constexpr int kSampleRows = 64;
+constexpr int kNoSize = -128;
+
+__global__ __launch_bounds__(kThreads) void channel_kernel(ProductArgs pa) {
+  constexpr int G = kThreads / 32;                   // row groups
+  __shared__ uint32_t part[2][G][128];
+  const int t = threadIdx.x, g = t >> 5, c0 = 4 * (t & 31);
+  const int64_t k = static_cast<int64_t>(blockIdx.x) * 128 + c0;
+  f32x4 x[2][kSampleRows / G];
+#pragma unroll
+  for (int i = 0; i < kSampleRows / G; ++i) {
+    const int64_t row = static_cast<int64_t>(g + G * i) * pa.m / kSampleRows;
+    x[0][i] = *reinterpret_cast<const f32x4*>(pa.P + row * pa.ldp + k);
+    x[1][i] = *reinterpret_cast<const f32x4*>(pa.Q + row * pa.ldp + k);
+  }
+  // exponents of the normal numbers: their sum and count in one word
+#pragma unroll
+  for (int f = 0; f < 2; ++f)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      mx = fmaxf(mx, fabsf(v[e]));
-      sum += fabsf(v[e]);
+      uint32_t n = 0;
+#pragma unroll
+      for (int i = 0; i < kSampleRows / G; ++i) {
+        const uint32_t b = (__float_as_uint(x[f][i][e]) >> 23) & 255u;
+        n += b != 0 && b != 255 ? (1u << 16) + b : 0u;
+      }
+      part[f][g][c0 + e] = n;
+    }
+  __syncthreads();
+  if (t < 128) {
+    int ex[2];
+    bool none[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) {
+      uint32_t n = 0;
+#pragma unroll
+      for (int i = 0; i < G; ++i) n += part[f][i][t];
+      const int cnt = static_cast<int>(n >> 16);
+      none[f] = cnt == 0;
+      ex[f] = (static_cast<int>(n & 0xffffu) + cnt / 2) / (cnt > 0 ? cnt : 1) - 127;
+    }
+    int bal = (ex[1] - ex[0]) >> 1, v = (ex[0] + ex[1]) >> 1;
+    bal = bal < -100 ? -100 : (bal > 100 ? 100 : bal);
+    v = v < -127 ? -127 : v;
+    if (none[0] || none[1]) {
+      bal = none[0] == none[1] ? 0 : (none[0] ? 100 : -100);
+      v = kNoSize;
+    }
+    pa.chan[blockIdx.x * 128 + t] =
+        static_cast<uint16_t>((bal & 255) | (v & 255) << 8);
+  }
+  if (blockIdx.x == 0 && t == 0) pa.rexp[2 * pa.m] = pa.rexp[2 * pa.m + 1] = 0;
+}
+
+__device__ __forceinline__ int chan_bal(uint32_t c) { return static_cast<int8_t>(c & 255u); }
+__device__ __forceinline__ int chan_size(uint32_t c) { return static_cast<int8_t>((c >> 8) & 255u); }
+
+// Scale exponent e of each row (2m work-groups: rows of P, then of Q): the balanced row times 2^e
+// rounds to integers whose four signed digits exist, |x 2^e| <= 2^31 - 2^24; kNoDigits for a row
+// that takes no part.  rexp[2m], rexp[2m + 1]: whether any row of P, of Q does.
+__global__ __launch_bounds__(kThreads) void row_scale_kernel(ProductArgs pa) {
+  __shared__ uint32_t smax[kThreads / 64];
+  __shared__ double sen[kThreads / 64], sws[kThreads / 64];
+  const int r = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const bool second = r >= pa.m;
+  const float* x = second ? pa.Q + static_cast<int64_t>(r - pa.m) * pa.ldp
+                          : pa.P + static_cast<int64_t>(r) * pa.ldp;
+  const int sg = second ? -1 : 1;
+  uint32_t mx = 0;                          // bits of the largest magnitude (NaN above infinity)
+  double en = 0.0, ws = 0.0;                // sums of (x s)^2 and s^2
+#pragma unroll 4
+  for (int k = 4 * t; k < pa.kact; k += 4 * kThreads) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(x + k);
+    const u32x2 c = *reinterpret_cast<const u32x2*>(pa.chan + k);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const uint32_t ce = c[e >> 1] >> (16 * (e & 1));
+      const float xs = ldexpf(v[e], sg * chan_bal(ce));
+      const uint32_t b = __float_as_uint(xs) & 0x7fffffffu;
+      mx = b > mx ? b : mx;
+      // s^2 = 2^(2 size), zero for a channel without a size
+      const int size = chan_size(ce);
+      const uint32_t hi = size == kNoSize ? 0u : static_cast<uint32_t>(1023 + 2 * size) << 20;
+      const double s2 = __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32);
+      const double xd = static_cast<double>(xs);
+      en = fma(xd * xd, s2, en);
+      ws += s2;
     }
   }
+  mx = wave_max_u32(mx);
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {
-    mx = fmaxf(mx, __shfl_xor(mx, d, 64));
-    sum += __shfl_xor(sum, d, 64);
+    en += __shfl_xor(en, d, 64);
+    ws += __shfl_xor(ws, d, 64);
   }
-  if ((threadIdx.x & 63) == 0) {
-    smax[threadIdx.x >> 6] = mx;
-    ssum[threadIdx.x >> 6] = sum;
+  if (lane == 0) {
+    smax[w] = mx;
+    sen[w] = en;
+    sws[w] = ws;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
+  if (t != 0) return;
   for (int i = 1; i < kThreads / 64; ++i) {
-    mx = fmaxf(mx, smax[i]);
-    sum += ssum[i];
+    mx = smax[i] > mx ? smax[i] : mx;
+    en += sen[i];
+    ws += sws[i];
   }
   int e = kNoDigits;
-  if (mx == 0.0f && sum == 0.0f) {
+  const float big = __uint_as_float(mx);
+  if (mx == 0) {
     e = 0;
-  } else if (__builtin_isfinite(sum) && mx <= 32.0f * (sum / static_cast<float>(pa.n2)) &&
-             mx >= 0x1p-90f) {
+  } else if (mx < 0x7f800000u && big >= 0x1p-120f && ws > 0.0) {
     int ex;
-    const float f = frexpf(mx, &ex);               // mx = f 2^ex, 0.5 <= f < 1
-    e = f <= 1.0f - 0x1p-7f ? 31 - ex : 30 - ex;
+    const float f = frexpf(big, &ex);              // big = f 2^ex, 0.5 <= f < 1
+    const int q = f <= 1.0f - 0x1p-7f ? 31 - ex : 30 - ex;
+    // quantum 2^-q: ws 2^(-2q) / 12 <= en 2^-50.7 / 15 (a channel without a size has no part in en,
+    // so that a NaN or an infinity there is seen in mx only)
+    if (ldexp(en, 2 * q - 51) >= ws) e = q;
   }
   pa.rexp[r] = e;
+  // (every work-group that does stores the same word: no atomic, which cost 10 ns a row here)
+  if (e != kNoDigits) pa.rexp[2 * pa.m + (second ? 1 : 0)] = 1;
 }
 
 // Digit fragments.  For a block of 32 rows, 32 k and one digit the matrix instruction's operand
 // is 64 lanes of 16 bytes, lane (k / 16 mod 2) 32 + row holding 16 consecutive k: 1 KB in a row,
-// [row block][k block][digit].  A work-group converts 32 rows x 128 k, thread (row, k / 16).
+// [row block][k block][digit].  A work-group converts 32 rows x 128 k, thread (row, k / 16).  Blocks
+// that no tile of digits reads (no row of theirs takes part, or none of the other factor) stay as
+// they are.
 __global__ __launch_bounds__(kThreads) void digits_kernel(ProductArgs pa, int nbP) {
   const int t = threadIdx.x, row = t & 31;
   const bool second = static_cast<int>(blockIdx.y) >= nbP;
@@ -79,19 +184,23 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(ProductArgs pa, int nb
   const int r = rb * 32 + row;
   const int k = blockIdx.x * 128 + (t >> 5) * 16;
   const int KS = (pa.n2 + 31) / 32;
-  if (k >= KS * 32) return;
   const int e = r < pa.m ? pa.rexp[second ? pa.m + r : r] : kNoDigits;
+  if (__ballot(e != kNoDigits) == 0 || pa.rexp[2 * pa.m + (second ? 0 : 1)] == 0) return;
+  if (k >= KS * 32) return;
   const float* x = (second ? pa.Q : pa.P) + static_cast<int64_t>(r < pa.m ? r : 0) * pa.ldp + k;
+  const u32x4* ch = reinterpret_cast<const u32x4*>(pa.chan + k);
   f32x4 v[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) v[j] = reinterpret_cast<const f32x4*>(x)[j];
+  const u32x4 c[2] = {ch[0], ch[1]};
   u32x4 d[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t u[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int q = e != kNoDigits ? __float2int_rn(ldexpf(v[j][i], e)) : 0;
+      const int bal = chan_bal(c[j >> 1][2 * (j & 1) + (i >> 1)] >> (16 * (i & 1)));
+      const int q = e != kNoDigits ? __float2int_rn(ldexpf(v[j][i], second ? e - bal : e + bal)) : 0;
       // signed bytes: each of the lower three hands its carry up
       u[i] = (static_cast<uint32_t>(q) + 0x00808080u) ^ 0x00808080u;
     }
@@ -300,7 +409,8 @@ hipError_t launch_digit_product(const ProductArgs& a, hipStream_t st, hipEvent_t
   if (a.ts != 64 || a.ksl % 32 != 0 || a.ksl > kDigitMaxK) return hipErrorInvalidValue;
   const int nbP = (a.m + 127) / 128 * 4, nbQ = (a.m + 63) / 64 * 2;
   const int KS = (a.n2 + 31) / 32;
-  FPSK_LAUNCH_TIMED(row_scale_kernel, dim3(2 * a.m), dim3(kThreads), 0, st, e0, nullptr, a);
+  FPSK_LAUNCH_TIMED(channel_kernel, dim3((a.n2 + 127) / 128), dim3(kThreads), 0, st, e0, nullptr, a);
+  FPSK_LAUNCH(row_scale_kernel, dim3(2 * a.m), dim3(kThreads), 0, st, a);
   FPSK_LAUNCH(digits_kernel, dim3((KS + 3) / 4, nbP + nbQ), dim3(kThreads), 0, st, a, nbP);
   const int wgs = (a.m + 127) / 128 * ((a.m + 63) / 64) * a.NS;
   FPSK_LAUNCH(digit_product_kernel, dim3((wgs + 7) / 8 * 8), dim3(kThreads), 0, st, a, a.zero);

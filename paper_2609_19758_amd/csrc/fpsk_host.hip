@@ -619,6 +619,7 @@ struct Workspace {
   DevBuf P, Pw, Q, Qw, partS, partR, partT, scratch, S, R, T, maxpart, tilestat;
   DevBuf xpart;                // probe block-product partials
   DevBuf rexp, digP, digQ;     // digit product: row scales and digit fragments
+  DevBuf chan;                 // and channel figures
 };
 
 fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n3, int m,
@@ -653,7 +654,9 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
   if (d.nX > 0) FPSK_TRY(dev_alloc(W.xpart, static_cast<size_t>(d.xns) * mm));
   if (W.ds.i8) {
     const size_t row = static_cast<size_t>((n2 + 31) / 32) * 128;    // 4 digits of each k
-    FPSK_TRY(dev_alloc(W.rexp, static_cast<size_t>(m) * 2 * sizeof(int32_t)));
+    const size_t groups = static_cast<size_t>((n2 + 127) / 128);
+    FPSK_TRY(dev_alloc(W.rexp, (static_cast<size_t>(m) * 2 + 2) * sizeof(int32_t)));
+    FPSK_TRY(dev_alloc(W.chan, groups * 128 * sizeof(uint16_t)));
     FPSK_TRY(dev_alloc(W.digP, static_cast<size_t>((m + 127) / 128) * 128 * row));
     FPSK_TRY(dev_alloc(W.digQ, static_cast<size_t>((m + 63) / 64) * 64 * row));
   }
@@ -663,7 +666,7 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
 void free_workspace(Workspace& W) {
   for (DevBuf* b : {&W.P, &W.Pw, &W.Q, &W.Qw, &W.partS, &W.partR, &W.partT, &W.scratch, &W.S,
                     &W.R, &W.T, &W.maxpart, &W.tilestat, &W.xpart, &W.rexp, &W.digP,
-                    &W.digQ}) {
+                    &W.digQ, &W.chan}) {
     dev_free(*b);
   }
 }
@@ -907,6 +910,7 @@ fpsketch_status pass_args(fpsketch_ctx* c, const DevRound& R, Workspace& W, cons
   a.i8 = d.i8 ? 1 : 0;
   a.zero = c->zero.p;
   a.rexp = as<int32_t>(W.rexp);
+  a.chan = as<uint16_t>(W.chan);
   a.digP = as<uint32_t>(W.digP);
   a.digQ = as<uint32_t>(W.digQ);
   a.npc = d.npc;

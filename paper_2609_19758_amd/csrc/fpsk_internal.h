@@ -124,7 +124,10 @@ struct ProductArgs {
   // S alone on 64 x 64 tiles (i8): the factors as 8-bit digits on the integer matrix cores, tiles
   // with a row that does not fit them on the FP64 ones (fpsk_digits.hip)
   int i8;
-  int32_t* rexp;          // 2 m: scale exponent of every row of P, then of Q; kNoDigits where not
+  // 2 m + 2: scale exponent of every row of P, then of Q (kNoDigits where not), then for
+  // either whether any row has one
+  int32_t* rexp;
+  uint16_t* chan;         // per k, padded to 128: balancing exponent, size (fpsk_digits.hip)
   uint32_t* digP;         // digit fragments of P (rows padded to 128) and Q (to 64)
   uint32_t* digQ;
   const void* zero;       // >= 64 bytes of zeros

@@ -1,7 +1,8 @@
 """The bucket-space product on 8-bit digits: small-integer operands are exact in it, so sketches
 equal the oracle's bit for bit - at its smallest sizes, ragged tiles and k-steps, several and
-single slices - also where rows of the factors do not fit the digits (one entry far above the
-rest, infinities, NaN) and their tiles run on the FP64 matrix cores beside it."""
+single slices - also where rows of the factors do not fit the digits (an entry in a channel that is
+empty elsewhere, infinities, NaN) and their tiles run on the FP64 matrix cores beside it.  Operands
+with channels of different scale lose nothing against the FP64 product."""
 import numpy as np
 import pytest
 
@@ -57,8 +58,8 @@ def test_exact(fk, n1, n2, n3, m, layout):
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("side", ["A", "B", "both", "all rows"])
 def test_rows_without_digits(fk, side, layout):
-    """Some rows of A (columns of B) hold one entry of 30000 beside integers of at most 4: their
-    buckets' factor rows go to the FP64 tiles, the others stay."""
+    """Some rows of A (columns of B) hold one entry of 30000 beside integers of at most 4, or all of
+    them do in one channel."""
     n1, n2, n3, m = 300, 1040, 280, 520
     a_bits, b_bits, a64, b64, _ = int_case(n1, n2, n3, "fp16", 9)
     a, b = a64.copy(), b64.copy()
@@ -73,6 +74,112 @@ def test_rows_without_digits(fk, side, layout):
     bits = [wl.f32_to_f16_bits(x.astype(np.float32)) for x in (a, b)]
     S = _sketch(fk, bits[0], bits[1], c, m, layout)
     assert np.array_equal(S, _reference(a @ b - c.astype(np.float64), o.make_round(4, 1, n1, n3, m), m))
+
+
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("side", [0, 1])
+def test_rows_in_a_channel_without_a_size(fk, side, layout):
+    """Channels that hold zeros in every sampled bucket of one factor (i m / 64) and entries in a few
+    others: those rows take no part, their tiles run on the FP64 cores beside the digits'."""
+    n1, n2, n3, m = 300, 1040, 280, 520
+    a_bits, b_bits, a64, b64, _ = int_case(n1, n2, n3, "fp16", 9)
+    hr = o.make_round(4, 1, n1, n3, m)
+    sampled = {i * m // 64 for i in range(64)}
+    h = hr.h1 if side == 0 else hr.h2
+    free = [int(i) for i in range(len(h)) if int(h[i]) not in sampled]
+    x = a64.copy() if side == 0 else b64.T.copy()      # rows of the factor's side
+    x[:, [17, 600, 601, 1039]] = 0.0
+    for i, k, val in [(free[0], 17, 2048.0), (free[3], 600, -3.0), (free[-1], 1039, 1.0)]:
+        x[i, k] = val
+    a, b = (x, b64) if side == 0 else (a64, x.T)
+    c = (a @ b).astype(np.float32)
+    rng = np.random.default_rng(5)
+    c += rng.integers(-3, 4, size=c.shape).astype(np.float32)
+    bits = [wl.f32_to_f16_bits(np.ascontiguousarray(v, dtype=np.float32)) for v in (a, b)]
+    S = _sketch(fk, bits[0], bits[1], c, m, layout)
+    assert np.array_equal(S, _reference(a @ b - c.astype(np.float64), hr, m))
+
+
+def _scaled_case(n1, n2, n3, fmt, inverse, channels, outlier, seed):
+    """Normal operands; half of the channels scaled by `inverse` in A and the others in B, and
+    `channels` of A scaled by `outlier`.  On the GPU, with the black-box product."""
+    import torch
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("normal", 1.0), ("normal", 0.02), seed)
+    dt = torch.bfloat16 if fmt == "bf16" else torch.float16
+    A, B = to_dev_half(a_bits, fmt).float(), to_dev_half(b_bits, fmt).float()
+    order = torch.from_numpy(np.random.default_rng(seed).permutation(n2)).to(A.device)
+    A[:, order[:n2 // 2]] *= inverse
+    B[order[n2 // 2:]] *= inverse
+    A[:, order[:channels]] *= outlier
+    A, B = A.to(dt), B.to(dt)
+    return A, B, gemm_f32(A, B)
+
+
+def _signs(h, v, m):
+    """H1 or H2 in 64 bits on the GPU."""
+    import torch
+    H = torch.zeros(m, len(h), dtype=torch.float64, device="cuda")
+    H[torch.from_numpy(np.asarray(h, dtype=np.int64)).cuda(), torch.arange(len(h), device="cuda")] = \
+        torch.from_numpy(np.asarray(v, dtype=np.float64)).cuda()
+    return H
+
+
+def _exact_sums(hr, m, A, B, C):
+    """S in 64 bits."""
+    H1, H2 = _signs(hr.h1, hr.v1, m), _signs(hr.h2, hr.v2, m).T.contiguous()
+    return (H1 @ A.double()) @ (B.double() @ H2) - (H1 @ C.double()) @ H2
+
+
+SCALES = [("bf16", 1.0, 0, 1.0), ("bf16", 1e-2, 0, 1.0), ("bf16", 1e-3, 0, 1.0), ("bf16", 1e-4, 0, 1.0),
+          ("bf16", 1e-5, 0, 1.0), ("bf16", 1e-6, 0, 1.0), ("fp16", 1e-2, 0, 1.0), ("fp16", 1e-3, 0, 1.0),
+          ("bf16", 1.0, 1, 30.0), ("bf16", 1.0, 6, 30.0), ("fp16", 1.0, 6, 1000.0), ("bf16", 1e-3, 6, 1e4)]
+
+
+@pytest.mark.parametrize("m", [260, 1000])
+@pytest.mark.parametrize("fmt,inverse,channels,outlier", SCALES)
+def test_channel_scales(fk, fmt, inverse, channels, outlier, m):
+    """Channels of different scale: the digits add at most 1/15 of the mean square that rounding the
+    factors to FP32 costs (a relative 2^-25.35 of each product), so the error of S against 64 bits is
+    within 1.1 of that of the FP64 product, which the sketch with moments takes for its S.  Where a
+    few channels hold nearly all of the product their sums of a few half-precision values are exact
+    in FP32: the FP64 product's error is then far below that rounding, and the digits' share of the
+    rounding is the bound."""
+    n1, n2, n3 = 2048, 4096, 2048
+    A, B, C = _scaled_case(n1, n2, n3, fmt, inverse, channels, outlier, 8)
+    hr = o.make_round(4, 1, n1, n3, m)
+    ref = _exact_sums(hr, m, A, B, C).cpu().numpy()
+    v = fk.Verifier(n1, n2, n3, fmt, m=8)
+    err = [np.sqrt(np.mean((v.sketch(A, B, C, seed=4, rnd=1, m=m, moments=mom)[0] - ref) ** 2))
+           for mom in (False, True)]
+    v.close()
+    share = 0.0
+    if channels:
+        P, Q = _signs(hr.h1, hr.v1, m) @ A.double(), B.double() @ _signs(hr.h2, hr.v2, m).T.contiguous()
+        share = float((P.pow(2).mean(0) @ Q.pow(2).mean(1) / 15).sqrt()) * 2.0 ** -25.35
+    assert err[0] <= 1.1 * err[1] + share
+    assert err[1] <= 0.02 * np.std(ref)          # (it is a small share of the noise)
+
+
+@pytest.mark.parametrize("inverse", [1.0, 1e-3, 1e-6])
+def test_fault_in_scaled_channels(fk, inverse):
+    """The probe's noise is that of S in 64 bits, and an error of 0.02 rms(C) is found, as it is
+    there."""
+    n1, n2, n3, fmt, m = 2048, 4096, 2048, "bf16", 260
+    A, B, C = _scaled_case(n1, n2, n3, fmt, inverse, 0, 1.0, 8)
+    v = fk.Verifier(n1, n2, n3, fmt, m=m)
+    hr = o.make_round(v.params.seed, 0, n1, n3, m)
+    S = _exact_sums(hr, m, A, B, C).abs().cpu().numpy()
+    v.probe(A, B, C)
+    clean = v.probe_stats()
+    want = 1.2533 * np.mean(np.minimum(S, 5 * np.mean(S)))
+    assert not clean["dirty"] and abs(clean["sigma_hat"] - want) <= 1e-3 * want
+    C[700, 900] += 0.02 * float(C.double().pow(2).mean().sqrt())
+    v.probe(A, B, C)
+    stats = v.probe_stats()
+    v.close()
+    S = _exact_sums(hr, m, A, B, C).abs().cpu().numpy()
+    assert S.max() > 1.5 * stats["thr"] and stats["dirty"]
+    assert abs(stats["max_abs"] - S.max()) <= 1e-3 * S.max()
 
 
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
