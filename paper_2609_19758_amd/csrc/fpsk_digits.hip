@@ -175,8 +175,8 @@ __global__ __launch_bounds__(kThreads) void row_scale_kernel(ProductArgs pa) {
 // Digit fragments.  For a block of 32 rows, 32 k and one digit the matrix instruction's operand
 // is 64 lanes of 16 bytes, lane (k / 16 mod 2) 32 + row holding 16 consecutive k: 1 KB in a row,
 // [row block][k block][digit].  A work-group converts 32 rows x 128 k, thread (row, k / 16).  Blocks
-// that no tile of digits reads (no row of theirs takes part, or none of the other factor) stay as
-// they are.
+// that no tile of digits reads (one of their 64 rows takes no part, or none of the other factor's
+// does) stay as they are.
 __global__ __launch_bounds__(kThreads) void digits_kernel(ProductArgs pa, int nbP) {
   const int t = threadIdx.x, row = t & 31;
   const bool second = static_cast<int>(blockIdx.y) >= nbP;
@@ -185,7 +185,9 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(ProductArgs pa, int nb
   const int k = blockIdx.x * 128 + (t >> 5) * 16;
   const int KS = (pa.n2 + 31) / 32;
   const int e = r < pa.m ? pa.rexp[second ? pa.m + r : r] : kNoDigits;
-  if (__ballot(e != kNoDigits) == 0 || pa.rexp[2 * pa.m + (second ? 0 : 1)] == 0) return;
+  const int r64 = (rb >> 1) * 64 + (t & 63);
+  const bool bad = r64 < pa.m && pa.rexp[second ? pa.m + r64 : r64] == kNoDigits;
+  if (__ballot(bad) != 0 || pa.rexp[2 * pa.m + (second ? 0 : 1)] == 0) return;
   if (k >= KS * 32) return;
   const float* x = (second ? pa.Q : pa.P) + static_cast<int64_t>(r < pa.m ? r : 0) * pa.ldp + k;
   const u32x4* ch = reinterpret_cast<const u32x4*>(pa.chan + k);
@@ -247,8 +249,9 @@ __global__ __launch_bounds__(kThreads, 1) void digit_product_kernel(ProductArgs 
   const int ta = first + within % rows, tb = within / rows;
   const int t = threadIdx.x, lane = t & 63, w = t >> 6;
   if (w < 3) {
-    const int row = w < 2 ? ta * 128 + w * 64 + lane : tb * 64 + lane;
-    const bool bad = row < m && pa.rexp[w < 2 ? row : m + row] == kNoDigits;
+    // (a half past the last row has nothing to form either)
+    const int row0 = w < 2 ? ta * 128 + w * 64 : tb * 64, row = row0 + lane;
+    const bool bad = row0 >= m || (row < m && pa.rexp[w < 2 ? row : m + row] == kNoDigits);
     const bool any = __ballot(bad) != 0;
     if (lane == 0) none[w] = any;
   }

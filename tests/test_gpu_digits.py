@@ -115,6 +115,23 @@ def _scaled_case(n1, n2, n3, fmt, inverse, channels, outlier, seed):
     return A, B, gemm_f32(A, B)
 
 
+@pytest.mark.parametrize("layout", [0, 1])
+@pytest.mark.parametrize("side", [0, 1])
+def test_no_tile_of_digits(fk, side, layout):
+    """One factor's every 64 rows hold one that takes no part (a single entry of 30000 in a channel of
+    its own): no tile is on the digits, in a grid whose last 128 rows are less than half full."""
+    n1, n2, n3, m = 400, 4800, 400, 280
+    a_bits, b_bits, a64, b64, _ = int_case(n1, n2, n3, "fp16", 9)
+    x = a64.copy() if side == 0 else b64.T.copy()
+    x[np.arange(400), 11 * np.arange(400)] = 30000.0
+    a, b = (x, b64) if side == 0 else (a64, x.T)
+    c = (np.round(a @ b / 1024.0) * 1024.0).astype(np.float32)
+    bits = [wl.f32_to_f16_bits(np.ascontiguousarray(v, dtype=np.float32)) for v in (a, b)]
+    S = _sketch(fk, bits[0], bits[1], c, m, layout)
+    ref = _reference(a @ b - c.astype(np.float64), o.make_round(4, 1, n1, n3, m), m)
+    assert np.array_equal(S, ref)
+
+
 def _signs(h, v, m):
     """H1 or H2 in 64 bits on the GPU."""
     import torch
