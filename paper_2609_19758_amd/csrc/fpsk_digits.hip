@@ -1,5 +1,5 @@
-// The bucket-space product S = P Q - S_C on the integer matrix cores (S alone, more than 240
-// buckets a side, n2 >= 512, m^2 n2 >= 2^28).
+// The bucket-space product S = P Q - S_C on the integer matrix cores (S alone, more than 256
+// buckets a side, n2 >= 512, m^2 n2 >= 2^28, or 2.75 x 2^28 below n2 = 4096).
 //
 // A product of floating-point matrices as a sum of exact integer products is the scheme of Ozaki,
 // Ogita, Oishi and Rump (2012), here on 8-bit integers as in Ootomo, Ozaki and Yokota (2024).  Each

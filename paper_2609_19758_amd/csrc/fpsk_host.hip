@@ -448,14 +448,17 @@ Decomp decompose(int64_t n1, int64_t n2, int64_t n3, int m, bool mom, bool trans
   ns = std::max(1, std::min<int>({ns, 32, static_cast<int>((n2 + kstep - 1) / kstep)}));
   int64_t ksl = (n2 + ns - 1) / ns;
   ksl = (ksl + kstep - 1) / kstep * kstep;
-  // S alone on the quadrant tiles: the digit product, in 128 x 64 tiles, from m^2 n2 = 2^28 on.
-  // Its three extra launches cost about 16 us: at m = 260, n2 = 1030 (0.07 x 10^9) it takes 36 us
-  // against 15 us on the FP64 cores, at m = 279, n2 = 4096 (0.32 x 10^9) 42 against 53 with their
-  // reductions, at m = 698, n2 = 16384 163 against 275.  Slices for about 512 work-groups, of at
-  // least 512 k (a slice's epilogue and its share of the reduction cost as much as about 500 k) and
-  // at most what 32-bit sums hold.
-  d.i8 = !mom && !d.kw && n2 >= fpsk::kDigitMinK &&
-         static_cast<double>(m) * m * static_cast<double>(n2) >= 0x1p28;
+  // S alone on the quadrant tiles: the digit product, in 128 x 64 tiles, where it is faster than the
+  // FP64 product with its slice sums.  Its four extra launches cost about 22 us, and below 4096 k the
+  // slices are few.  Probes of 1024 x n2 x 1024, FP64 and digits (us a call): m = 280 n2 = 4096 72.2
+  // and 71.7, m = 300 n2 = 6000 84.0 and 81.5, m = 432 n2 = 4096 84.8 and 77.2; m = 600 n2 = 1500 71.9
+  // and 76.6, n2 = 2000 78.3 and 75.8, m = 1000 n2 = 512 68.4 and 74.1, n2 = 800 80.5 and 81.5,
+  // m = 2000 n2 = 512 130.6 and 125.2.  Up to m = 256 the FP64 tiles fill the grid evenly and stay
+  // ahead at every n2: m = 241 n2 = 4700 67.7 and 76.2, n2 = 16384 103.1 and 110.4.  Slices for about
+  // 512 work-groups, of at least 512 k (a slice's epilogue and its share of the reduction cost as
+  // much as about 500 k) and at most what 32-bit sums hold.
+  d.i8 = !mom && m > 256 && n2 >= fpsk::kDigitMinK &&
+         static_cast<double>(m) * m * static_cast<double>(n2) >= (n2 >= 4096 ? 0x1p28 : 0x1.6p29);
   if (d.i8) {
     const int64_t wg = static_cast<int64_t>((m + 127) / 128) * ((m + 63) / 64);
     int64_t want = std::max<int64_t>(1, std::min<int64_t>({512 / wg, 32, n2 / fpsk::kDigitMinK}));

@@ -39,9 +39,12 @@ def _sketch(fk, a_bits, b_bits, c, m, layout, fmt="fp16"):
     return S
 
 
-# m around tile edges with m^2 n2 >= 2^28; n2 off the 32-k steps, odd and even step counts, slices
+# m around tile edges with m^2 n2 >= 2^28 (some stay on the FP64 cores: below 2.75 x 2^28 at
+# n2 < 4096, and m <= 256); n2 off the 32-k steps, odd and even step counts, slices
 SIZES = [(400, 1700, 300, 400), (300, 1030, 520, 512), (260, 1025, 260, 513), (200, 800, 90, 641),
-         (500, 513, 333, 769), (90, 520, 700, 1100), (700, 4800, 300, 241), (64, 512, 64, 2050)]
+         (500, 513, 333, 769), (90, 520, 700, 1100), (700, 4800, 300, 241), (64, 512, 64, 2050),
+         (400, 1700, 300, 700), (300, 1030, 520, 896), (260, 1025, 260, 897), (200, 800, 90, 1025),
+         (500, 513, 333, 1281), (90, 4100, 700, 257), (700, 4800, 300, 385), (120, 4099, 300, 300)]
 
 
 @pytest.mark.parametrize("layout", [0, 1])
@@ -57,10 +60,11 @@ def test_exact(fk, n1, n2, n3, m, layout):
 
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("side", ["A", "B", "both", "all rows"])
-def test_rows_without_digits(fk, side, layout):
+@pytest.mark.parametrize("m", [520, 900])
+def test_rows_without_digits(fk, side, layout, m):
     """Some rows of A (columns of B) hold one entry of 30000 beside integers of at most 4, or all of
     them do in one channel."""
-    n1, n2, n3, m = 300, 1040, 280, 520
+    n1, n2, n3 = 300, 1040, 280
     a_bits, b_bits, a64, b64, _ = int_case(n1, n2, n3, "fp16", 9)
     a, b = a64.copy(), b64.copy()
     if side in ("A", "both"):
@@ -81,7 +85,7 @@ def test_rows_without_digits(fk, side, layout):
 def test_rows_in_a_channel_without_a_size(fk, side, layout):
     """Channels that hold zeros in every sampled bucket of one factor (i m / 64) and entries in a few
     others: those rows take no part, their tiles run on the FP64 cores beside the digits'."""
-    n1, n2, n3, m = 300, 1040, 280, 520
+    n1, n2, n3, m = 300, 1040, 280, 900
     a_bits, b_bits, a64, b64, _ = int_case(n1, n2, n3, "fp16", 9)
     hr = o.make_round(4, 1, n1, n3, m)
     sampled = {i * m // 64 for i in range(64)}
@@ -200,8 +204,9 @@ def test_fault_in_scaled_channels(fk, inverse):
 
 
 @pytest.mark.parametrize("bad", [np.inf, np.nan])
-def test_non_finite_rows(fk, bad):
-    n1, n2, n3, m = 300, 1040, 280, 520
+@pytest.mark.parametrize("m", [520, 900])
+def test_non_finite_rows(fk, bad, m):
+    n1, n2, n3 = 300, 1040, 280
     a_bits, b_bits, a64, b64, c = int_case(n1, n2, n3, "fp16", 9)
     a = a64.astype(np.float32)
     a[42, 77] = bad

@@ -281,7 +281,23 @@ def largest(h):
         h.lib.fpsketch_destroy(h.c)
 
 
-SCENARIOS = {"largest": (largest, {"m": 3}),
+def routes(h):
+    """Which product a probe of m buckets takes at n2, on both sides of each line."""
+    buf = ctypes.addressof(h.p)
+    cases = [(257, 4100, True), (256, 16384, False), (280, 4096, True), (279, 3400, False),
+             (700, 1700, True), (700, 1500, False), (896, 1030, True), (1281, 513, True),
+             (1300, 511, False), (2050, 512, True), (48, 4096, False)]
+    for m, n2, digits in cases:
+        h.p.m, h.n2 = m, n2
+        assert h.create() == fk.OK
+        h.rt.rt_reset()
+        assert h.lib.fpsketch_probe(h.c, buf, buf, buf, fk.F32, None, STREAM) == fk.OK
+        assert ("digit_product_kernel" in h.log()) == digits, (m, n2)
+        h.lib.fpsketch_destroy(h.c)
+
+
+SCENARIOS = {"routes": (routes, {}),
+             "largest": (largest, {"m": 3}),
              "rebuild": (rebuild, {}),
              "waits": (waits, {"m": 48}),
              "sequence": (sequence, {}), "fills": (fills, {}), "scan_total": (scan_total, {}),
