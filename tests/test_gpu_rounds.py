@@ -42,6 +42,34 @@ def test_tables_through_exact_sketches(fk, n1, n2, n3, m, layout):
     v.close()
 
 
+@pytest.mark.parametrize("n1,n3,m", [
+    (150000, 40, 1025), (80000, 40, 1025), (40000, 520, 1030), (30000, 1500, 1100), (6000, 2100, 1030), (3000, 4096, 1300),
+    (3000, 4097, 1025), (900, 8200, 1025)])
+def test_wide_rows_shared_by_waves(fk, n1, n3, m):
+    """More than 1024 buckets over few columns: 1, 2, 4, 8 and 16 column tiles a chunk (rounded up), so
+    that 16 to 1 waves share a bucket's rows, several groups of 64 rows a bucket, a short last chunk."""
+    n2, fmt = 3, "bf16"
+    a_bits, b_bits, a64, b64, c = int_case(n1, n2, n3, fmt, 5)
+    rng = np.random.default_rng(n1 + n3)
+    c += rng.integers(-2, 3, size=c.shape).astype(np.float32)
+    E = a64 @ b64 - c
+    v = fk.Verifier(n1, n2, n3, fmt, m=8)
+    hr = o.make_round(77, 2, n1, n3, m)
+    X = np.zeros((m, n3))
+    np.add.at(X, hr.h1, hr.v1[:, None] * E)
+    ref = np.zeros((m, m))
+    np.add.at(ref.T, hr.h2, (X * hr.v2).T)
+    args = to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt), to_dev_f32(c)
+    assert np.array_equal(v.sketch(*args, seed=77, rnd=2, m=m, moments=False)[0], ref)
+    S, R, _, _, _ = v.sketch(*args, seed=77, rnd=2, m=m, moments=True)
+    v.close()
+    Y = np.zeros((m, n3))
+    np.add.at(Y, hr.h1, (hr.v1 * ((np.arange(n1) + 1) / o.pow2_ceil(n1)))[:, None] * E)
+    refr = np.zeros((m, m))
+    np.add.at(refr.T, hr.h2, (Y * hr.v2).T)
+    assert np.array_equal(S, ref) and np.array_equal(R, refr)
+
+
 @pytest.mark.parametrize("layout", [0, 1])
 @pytest.mark.parametrize("n2", [5, 511, 1536])
 @pytest.mark.parametrize("sites", [
