@@ -729,7 +729,7 @@ struct fpsketch_ctx {
   DevBuf scan_counts, scan_total, scan_rows, scan_out, samples, patch_rowptr,
       patch_col, patch_val, rc_coords, rc_gamma, rc_abs, rc_part;
   // localize rounds on the device: selection state, histograms and kept keys, candidates
-  DevBuf sel_state, sel_hist, sel_cand, cands, cand_count;
+  DevBuf sel_state, sel_hist, sel_cand, cands, cand_count, peel_dev;
   // host memory the kernels read and write: figures and candidates of a step (HostHead, then up
   // to kPublish candidates), the peel list, the recheck's coordinates and results
   HostBuf host_head, host_peel, host_rc;
@@ -1269,7 +1269,12 @@ fpsketch_status round_cut_device(fpsketch_ctx* c, int r, const fpsk::PeelEntry* 
   g.c_n2 = c->p.c_valid * static_cast<double>(c->n2) * std::ldexp(1.0, -23);
   g.mx = static_cast<double>(std::max(c->n1, c->n3));
   g.radius = std::max(static_cast<double>(r), 0.5);
+  if (npeel > 0) {
+    const size_t bytes = static_cast<size_t>(npeel) * sizeof(fpsk::PeelEntry);
+    if (c->peel_dev.bytes < bytes) FPSK_TRY(dev_alloc(c->peel_dev, std::max<size_t>(2 * bytes, 4096)));
+  }
   g.peel = peel;
+  g.peel_dev = as<fpsk::PeelEntry>(c->peel_dev);
   g.npeel = npeel;
   g.cands = as<fpsk::Cand>(c->cands);
   g.cap = kCandCap;
@@ -1543,7 +1548,7 @@ void fpsketch_destroy(fpsketch_ctx* c) {
                     &c->scan_total, &c->scan_rows,
                     &c->scan_out, &c->samples, &c->patch_rowptr, &c->patch_col, &c->patch_val,
                     &c->rc_coords, &c->rc_gamma, &c->rc_abs, &c->rc_part, &c->sel_state,
-                    &c->sel_hist, &c->sel_cand, &c->cands, &c->cand_count, 
+                    &c->sel_hist, &c->sel_cand, &c->cands, &c->cand_count, &c->peel_dev,
                     &c->mo_list, &c->mo_rt,
                     &c->reprobe_acc, &c->qcache, &c->maxb_cache}) {
     dev_free(*b);
@@ -1942,18 +1947,10 @@ fpsketch_status fpsketch_calibrate_noise(fpsketch_ctx* c, const void* C, fpsketc
   return FPSK_OK;
 }
 
-fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B, const void* C,
-                                  fpsketch_dtype c_dtype, uint64_t seed, int32_t sigma_from_probe,
-                                  fpsketch_fault* out, int32_t cap, int32_t* n_out,
-                                  void* stream) {
-  FPSK_TRY(check_matrices(c, A, B, C, c_dtype));
-  if (n_out == nullptr || cap < 0 || (cap > 0 && out == nullptr)) {
-    return fail(FPSK_EINVAL, "bad output arguments");
-  }
-  FPSK_TRY(set_device(c));
-  const hipStream_t st = static_cast<hipStream_t>(stream);
-  FPSK_TRY(pipe_flush(c, st));
-  WaitOnReturn wait(st);
+// Localization after the checks, on the context's device (fpsketch_localize).
+static fpsketch_status localize(fpsketch_ctx* c, const void* A, const void* B, const void* C,
+                                uint64_t seed, int32_t sigma_from_probe, fpsketch_fault* out,
+                                int32_t cap, int32_t* n_out, hipStream_t st) {
   const float* Cf = static_cast<const float*>(C);
   const int32_t K = cap_K(c->p);
   std::vector<Found> F;
@@ -2052,7 +2049,7 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     ma.Qw = as<float>(c->aux_ws.Qw);
     ma.partR = as<double>(c->aux_ws.partR);
     ma.partT = as<double>(c->aux_ws.partT);
-    ma.peel = npeel > 0 ? peel : nullptr;
+    ma.peel = npeel > 0 ? as<fpsk::PeelEntry>(c->peel_dev) : nullptr;
     ma.npeel = npeel;
     ma.m = m;
     ma.ldp = c->aux_ws.d.ldp;
@@ -2192,7 +2189,6 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     }
   }
 
-  wait.waited();           // (the last round ended with a wait, or none of its work is pending)
   c->last_plan.m = c->m;
   c->last_plan.m_loc = plan.m_loc;
   c->last_plan.r = plan.r;
@@ -2217,6 +2213,23 @@ fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B,
     return fail(FPSK_ECAPACITY, "more fault records than capacity");
   }
   return FPSK_OK;
+}
+
+fpsketch_status fpsketch_localize(fpsketch_ctx* c, const void* A, const void* B, const void* C,
+                                  fpsketch_dtype c_dtype, uint64_t seed, int32_t sigma_from_probe,
+                                  fpsketch_fault* out, int32_t cap, int32_t* n_out,
+                                  void* stream) {
+  FPSK_TRY(check_matrices(c, A, B, C, c_dtype));
+  if (n_out == nullptr || cap < 0 || (cap > 0 && out == nullptr)) {
+    return fail(FPSK_EINVAL, "bad output arguments");
+  }
+  FPSK_TRY(set_device(c));
+  const hipStream_t st = static_cast<hipStream_t>(stream);
+  FPSK_TRY(pipe_flush(c, st));
+  WaitOnReturn wait(st);
+  const fpsketch_status s = localize(c, A, B, C, seed, sigma_from_probe, out, cap, n_out, st);
+  if (s == FPSK_OK || s == FPSK_ECAPACITY) wait.waited();     // (its last round ended with a wait)
+  return s;
 }
 
 fpsketch_status fpsketch_stream_read(const void* src, int64_t bytes, uint32_t* d_out,

@@ -246,7 +246,7 @@ struct HostHead {
   uint32_t found;        // buckets above the cut; for the setup entries of the exact scan
   uint32_t pad;
 };
-struct PeelEntry {     // S[o] -= ds, R[o] -= dr, T[o] -= dt (in host memory the device reads)
+struct PeelEntry {     // S[o] -= ds, R[o] -= dr, T[o] -= dt
   int64_t o;
   double ds, dr, dt;
 };
@@ -260,7 +260,8 @@ struct RoundArgs {
   double c_n2;           // c n2 2^-23
   double mx;             // max(n1, n3)
   double radius;         // max(r, 0.5)
-  const PeelEntry* peel; // subtracted first (may be null)
+  const PeelEntry* peel; // subtracted first (may be null), in host memory; copied to peel_dev
+  PeelEntry* peel_dev;
   int npeel;
   Cand* cands;           // buckets above the cut in any order, at most cap of them (at least
   uint32_t cap;          // kSelSmall fit)

@@ -103,3 +103,26 @@ def test_windows(fk, layout, n2, sites):
         union = {(i + a, j + b) for i, j in sites for a in range(-r, r + 1)
                  for b in range(-r, r + 1) if 0 <= i + a < n1 and 0 <= j + b < n3}
         assert plan["n_rechecked"] == len(union)
+
+
+def test_many_faults_peeled(fk):
+    """600 faults, more than the 512 entries that a peel takes at a time, several to a bucket: later
+    rounds peel them from S, R and T, and every one is recovered at its value."""
+    n1, n2, n3, fmt = 1024, 512, 1024, "bf16"
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("normal", 1.0), ("normal", 0.02), 4)
+    A, B = to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt)
+    c = gemm_f32(A, B).cpu().numpy()
+    rng = np.random.default_rng(8)
+    sites = rng.choice(n1 * n3, size=600, replace=False)
+    c.reshape(-1)[sites] += rng.uniform(50.0, 60.0, size=600).astype(np.float32)
+    v = fk.Verifier(n1, n2, n3, fmt, m=200, s_budget=600, k_cap=1024)
+    C = to_dev_f32(c)
+    v.probe(A, B, C)
+    recs, n, _ = v.localize(A, B, C, seed=3, sigma_from_probe=True, cap=2048)
+    v.close()
+    assert sorted(i * n3 + j for i, j, _, _, _ in recs) == sorted(sites.tolist())
+    assert max(r[4] for r in recs) > 1            # (some in a round that peeled others)
+    a64, b64 = o.decode(a_bits, fmt), o.decode(b_bits, fmt)
+    for i, j, d, _, _ in recs:
+        want = float(a64[i] @ b64[:, j]) - float(c[i, j])
+        assert abs(d - want) <= 1e-12 * (abs(want) + np.abs(a64[i]) @ np.abs(b64[:, j]))
