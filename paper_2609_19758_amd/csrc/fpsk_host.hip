@@ -1130,6 +1130,7 @@ fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, bool scan, const
     u.found = as<unsigned long long>(c->scan_total);
   }
   u.sigma = sigma;
+  u.need = scan ? 0 : 1;
   u.head = head(c);
   return selection_enqueued(c, fpsk::launch_rms(a, u, st));
 }

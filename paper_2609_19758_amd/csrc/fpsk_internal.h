@@ -236,6 +236,7 @@ struct SelArgs {
   uint64_t* cand;        // kSelGather
   int dev;               // 1: |S - state->med| in place of S
   unsigned long long* clear;   // samples: a total that the first pass sets to zero (may be null)
+  const double* need;          // samples: none counts when *need is zero (may be null)
 };
 // Figures of a localize step in host memory (written by a kernel, read after the stream is
 // waited for).
@@ -275,6 +276,7 @@ struct SetupArgs {
   int32_t* counts;
   unsigned long long* found;
   const double* sigma;   // two doubles to publish (may be null)
+  int need;              // 1: rms-hat only where the second of them is not zero
   HostHead* head;
 };
 // Moment sketches R, T at a list of n buckets o (launch_moments_at): the factors (rows ldp

@@ -850,7 +850,9 @@ template <int MODE>
 __global__ __launch_bounds__(kSelThreads) void sel_hist1_kernel(SelArgs a) {
   __shared__ SelLds l;
   if (MODE == kSelAbs && a.clear != nullptr && blockIdx.x == 0 && threadIdx.x == 0) *a.clear = 0;
+  const double need = MODE == kSelAbs && a.need != nullptr ? *a.need : 1.0;
   sel_zero(l);
+  if (need == 0.0) return;           // (the passes that follow find no counts and end as early)
   const double med = a.st->med;
 #pragma unroll 4
   for (int64_t i = static_cast<int64_t>(blockIdx.x) * kSelThreads + threadIdx.x; i < a.n;
@@ -894,6 +896,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_hist2_kernel(SelArgs a) {
     a.st->lo = ~0ull;
     a.st->not_hi = ~0ull;
   }
+  if (MODE == kSelAbs && n == 0) return;
   __syncthreads();
   sel_zero(l);
   const uint64_t hm = sel_mask(kSelBits);
@@ -923,6 +926,7 @@ __global__ __launch_bounds__(kSelThreads) void sel_gather_kernel(SelArgs a) {
     a.st->k2 = l.k;
     a.st->cnt2 = l.cnt;
   }
+  if (MODE == kSelAbs && l.total == 0) return;
   const uint64_t hm = sel_mask(2 * kSelBits);
   const uint64_t top = pref | ~hm;
   const double med = a.st->med;
@@ -1129,6 +1133,10 @@ __global__ __launch_bounds__(kSelThreads) void rms_kernel(SelArgs a, SetupArgs u
   __shared__ double red[lds_reduce_doubles<kSelThreads, 1>()];
   sel_finish<kSelAbs>(l, a, 0.0);
   const uint64_t nf = a.st->count;
+  if (a.need != nullptr && nf == 0) {       // nothing to take the median of, or nobody asks
+    if (threadIdx.x == 0) *u.head = HostHead{__builtin_nan(""), u.sigma[0], u.sigma[1], 0.0, 0.0, 0, 0};
+    return;
+  }
   const double clip = 64.0 * median_value(l.sel, l.next, nf);
   double acc[1] = {0.0};
 #pragma unroll 8
@@ -1508,6 +1516,7 @@ hipError_t launch_rms(const SelArgs& a0, const SetupArgs& u, hipStream_t st) {
   SelArgs a = a0;
   if (a.n <= 0) return hipErrorInvalidValue;
   a.clear = u.found;
+  a.need = u.need ? u.sigma + 1 : nullptr;
   const hipError_t e = sel_passes<kSelAbs>(a, st);
   if (e != hipSuccess) return e;
   if (u.found != nullptr) {

@@ -126,3 +126,27 @@ def test_scan_entries_in_row_major_order(fk, n1, n3, count, k_cap):
         assert all(r[4] == 0 and r[2] == a64[r[0]] @ b64[:, r[1]] for r in absolute)
         assert v.plan()["n_abs"] == len(want)
     v.close()
+
+
+@pytest.mark.parametrize("dirty", [False, True])
+def test_calibration_with_nothing_recorded(fk, dirty):
+    """No probe, or only dirty ones: nothing changes, and the selections that follow are as ever."""
+    n1, n2, n3, fmt, m = 300, 64, 500, "bf16", 40
+    a_bits, b_bits = wl.gen_operands(n1, n2, n3, fmt, ("normal", 1.0), ("normal", 1.0), 2)
+    A, B = to_dev_half(a_bits, fmt), to_dev_half(b_bits, fmt)
+    C = gemm_f32(A, B)
+    D = C.clone()
+    D[3, 4] += 100.0
+    v = fk.Verifier(n1, n2, n3, fmt, m=m)
+    if dirty:
+        v.probe(A, B, D)
+    for _ in range(2):
+        m_now, sigma, rebuilt = v.calibrate_noise(C)
+        assert (m_now, rebuilt) == (m, False) and math.isnan(sigma)
+    v.localize(A, B, C, seed=2, sigma_from_probe=False)
+    assert math.isclose(v.plan()["rms_hat"], o.rms_hat(C.cpu().numpy()), rel_tol=1e-11)
+    v.probe(A, B, C)
+    clean = v.probe_stats()
+    assert not clean["dirty"]
+    assert v.calibrate_noise(C)[1] == clean["sigma_hat"]
+    v.close()
