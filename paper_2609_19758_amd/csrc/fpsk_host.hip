@@ -291,18 +291,18 @@ void dev_free(DevBuf& b) {
   b.bytes = 0;
 }
 
-// As dev_alloc, and a new allocation is zero-filled.  The fill runs on the null stream, which the
-// caller's (possibly non-blocking) stream does not wait for, so it is waited for here; a buffer
-// that could not be filled is given back rather than kept with other contents.
-fpsketch_status dev_alloc_zero(DevBuf& b, size_t bytes) {
+// As dev_alloc, and a new allocation is zero-filled, by a kernel on the stream that will use it (a
+// memset on the null stream is not waited for by a non-blocking stream).  A buffer that could not be
+// filled is given back rather than kept with other contents.
+fpsketch_status dev_alloc_zero(DevBuf& b, size_t bytes, hipStream_t st) {
   if (b.p != nullptr && b.bytes >= bytes) return FPSK_OK;
   FPSK_TRY(dev_alloc(b, bytes));
   if (bytes == 0) return FPSK_OK;
-  hipError_t e = hipMemset(b.p, 0, bytes);
-  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  const hipError_t e = fpsk::launch_zero(b.p, bytes, st);
   if (e != hipSuccess) {
     dev_free(b);
-    return fail(FPSK_EHIP, std::string("zero fill failed: ") + hipGetErrorString(e));
+    return fail(e == hipErrorOutOfMemory ? FPSK_ENOMEM : FPSK_EHIP,
+                std::string("zero fill failed: ") + hipGetErrorString(e));
   }
   return FPSK_OK;
 }
@@ -626,20 +626,20 @@ struct Workspace {
 };
 
 fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n3, int m,
-                                 bool mom, bool transb, bool pipe = false) {
+                                 bool mom, bool transb, hipStream_t st, bool pipe = false) {
   const Decomp d = decompose(n1, n2, n3, m, mom, transb, pipe);
   W.d = d;
   W.mom = mom;
   // factor rows are ldp long; the padding past n2 is never written and stays zero
   const size_t fm = static_cast<size_t>(m) * static_cast<size_t>(d.ldp) * sizeof(float);
   const size_t mm = static_cast<size_t>(m) * static_cast<size_t>(m) * sizeof(double);
-  FPSK_TRY(dev_alloc_zero(W.P, fm));
-  FPSK_TRY(dev_alloc_zero(W.Q, fm));
+  FPSK_TRY(dev_alloc_zero(W.P, fm, st));
+  FPSK_TRY(dev_alloc_zero(W.Q, fm, st));
   FPSK_TRY(dev_alloc(W.partS, mm * d.npc));
   FPSK_TRY(dev_alloc(W.S, mm));
   if (mom) {
-    FPSK_TRY(dev_alloc_zero(W.Pw, fm));
-    FPSK_TRY(dev_alloc_zero(W.Qw, fm));
+    FPSK_TRY(dev_alloc_zero(W.Pw, fm, st));
+    FPSK_TRY(dev_alloc_zero(W.Qw, fm, st));
     FPSK_TRY(dev_alloc(W.partR, mm * d.npc));
     FPSK_TRY(dev_alloc(W.partT, mm * d.npc));
     FPSK_TRY(dev_alloc(W.R, mm));
@@ -785,7 +785,8 @@ fpsketch_status set_device(const fpsketch_ctx* c) {
 }
 
 // A synchronous call that returns early waits for what it has enqueued: its kernels read the
-// caller's matrices and use host memory that the next call writes.
+// caller's matrices and use host memory that the next call writes.  (Calls that only enqueue do so
+// after a failure: the next one may come on another stream, and fills of new buffers are on this.)
 class WaitOnReturn {
  public:
   explicit WaitOnReturn(hipStream_t st) : st_(st) {}
@@ -1042,7 +1043,7 @@ fpsketch_status build_probe(fpsketch_ctx* c, int m, hipStream_t st) {
   DevRound round;
   Workspace ws;
   auto build = [&]() -> fpsketch_status {
-    FPSK_TRY(ensure_workspace(ws, c->n1, c->n2, c->n3, m, false, c->transb));
+    FPSK_TRY(ensure_workspace(ws, c->n1, c->n2, c->n3, m, false, c->transb, st));
     FPSK_TRY(build_round(c->p.seed, 0, caps, c->n1, c->n3, d, false, c->transb, true, round, st));
     // the probes that read the tables may run on other streams
     FPSK_HIP(hipStreamSynchronize(st));
@@ -1080,9 +1081,9 @@ fpsk::Cand* published(fpsketch_ctx* c) {
                                        sizeof(fpsk::HostHead));
 }
 
-fpsketch_status ensure_selection(fpsketch_ctx* c) {
-  FPSK_TRY(dev_alloc_zero(c->sel_state, sizeof(fpsk::SelState)));
-  FPSK_TRY(dev_alloc_zero(c->sel_hist, 2 * 4096 * sizeof(uint32_t)));
+fpsketch_status ensure_selection(fpsketch_ctx* c, hipStream_t st) {
+  FPSK_TRY(dev_alloc_zero(c->sel_state, sizeof(fpsk::SelState), st));
+  FPSK_TRY(dev_alloc_zero(c->sel_hist, 2 * 4096 * sizeof(uint32_t), st));
   FPSK_TRY(dev_alloc(c->sel_cand, fpsk::kSelGather * sizeof(uint64_t)));
   FPSK_TRY(dev_alloc(c->cand_count, sizeof(uint32_t)));
   return host_alloc(c->host_head, sizeof(fpsk::HostHead) + kPublish * sizeof(fpsk::Cand));
@@ -1112,7 +1113,7 @@ fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, bool scan, const
   const int64_t total = c->n1 * c->n3;
   const int64_t stride = std::max<int64_t>(1, total / 65536);
   const int64_t count = (total + stride - 1) / stride;
-  FPSK_TRY(ensure_selection(c));
+  FPSK_TRY(ensure_selection(c, st));
   FPSK_TRY(dev_alloc(c->samples, static_cast<size_t>(count) * sizeof(float)));
   fpsk::SelArgs a = sel_args(c);
   a.samp = as<float>(c->samples);
@@ -1208,7 +1209,7 @@ fpsketch_status sketch_round(fpsketch_ctx* c, uint64_t seed, int round, int m, b
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, mom, c->transb);
   FPSK_TRY(build_round(seed, round, round_caps(seed, round, c->n1, c->n3, m, c->transb), c->n1,
                        c->n3, d, mom, c->transb, false, c->aux_round, st));
-  FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb));
+  FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb, st));
   FPSK_TRY(run_pass(c, c->aux_round, c->aux_ws, A, B, C, mom, 0, nullptr, prow, pcol, pval, st));
   const size_t mm = static_cast<size_t>(m) * static_cast<size_t>(m);
   S.resize(mm);
@@ -1244,7 +1245,7 @@ fpsketch_status sketch_round_device(fpsketch_ctx* c, uint64_t seed, int round, i
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, mom, c->transb);
   FPSK_TRY(build_round(seed, round, caps, c->n1, c->n3, d, mom, c->transb, false, c->aux_round,
                        st));
-  FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb));
+  FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, mom, c->transb, st));
   return run_pass(c, c->aux_round, c->aux_ws, A, B, C, mom, 0, nullptr, prow, pcol, pval, st,
                   nullptr, nullptr, nullptr, BSide::kStream, false);
 }
@@ -1257,7 +1258,7 @@ constexpr uint32_t kCandCap = 1u << 20;
 // middle order statistics), the thresholds and cut at search radius r, the buckets above it.
 fpsketch_status round_cut_device(fpsketch_ctx* c, int r, const fpsk::PeelEntry* peel, int npeel,
                                  hipStream_t st) {
-  FPSK_TRY(ensure_selection(c));
+  FPSK_TRY(ensure_selection(c, st));
   FPSK_TRY(dev_alloc(c->cands, static_cast<size_t>(kCandCap) * sizeof(fpsk::Cand)));
   const Decomp& d = c->aux_ws.d;
   fpsk::SelArgs a = sel_args(c);
@@ -1514,7 +1515,7 @@ fpsketch_status fpsketch_create(int64_t n1, int64_t n2, int64_t n3, fpsketch_dty
   fpsketch_status s = dev_alloc(c->stats, 8 * sizeof(double));
   if (s == FPSK_OK) s = dev_alloc(c->sigma_acc, 2 * sizeof(double));
   if (s == FPSK_OK) s = dev_alloc(c->zero, 64);
-  if (s == FPSK_OK) s = dev_alloc_zero(c->tiny, 96);
+  if (s == FPSK_OK) s = dev_alloc_zero(c->tiny, 96, nullptr);
   if (s == FPSK_OK) {
     hipError_t e = hipMemset(c->stats.p, 0, 8 * sizeof(double));
     if (e == hipSuccess) e = hipMemset(c->zero.p, 0, 64);
@@ -1636,11 +1637,13 @@ fpsketch_status fpsketch_cache_b(fpsketch_ctx* c, const void* B, void* stream) {
   FPSK_TRY(pipe_flush(c, st));
   const Decomp& d = c->probe_ws.d;
   const size_t fm = static_cast<size_t>(c->m) * static_cast<size_t>(d.ldp) * sizeof(float);
-  FPSK_TRY(dev_alloc_zero(c->qcache, fm));
+  WaitOnReturn wait(st);
+  FPSK_TRY(dev_alloc_zero(c->qcache, fm, st));
   FPSK_TRY(dev_alloc(c->maxb_cache, static_cast<size_t>(d.nB) * sizeof(float)));
   FPSK_TRY(run_pass(c, c->probe_round, c->probe_ws, c->zero.p, B, nullptr, false, 1, nullptr,
                     nullptr, nullptr, nullptr, st, nullptr, nullptr, nullptr,
                     BSide::kFillCache));
+  wait.waited();          // (enqueued whole: nothing to wait for)
   c->qcache_m = c->m;
   return FPSK_OK;
 }
@@ -1683,7 +1686,8 @@ fpsketch_status deferred_probe(fpsketch_ctx* c, const void* A, const void* B, co
                     nullptr, st, nullptr, nullptr, nullptr, bside);
   }
   Workspace& W = c->pipe_ws[c->pipe_next];
-  FPSK_TRY(ensure_workspace(W, c->n1, c->n2, c->n3, c->m, false, c->transb, true));
+  WaitOnReturn wait(st);
+  FPSK_TRY(ensure_workspace(W, c->n1, c->n2, c->n3, c->m, false, c->transb, st, true));
   const Decomp& d = W.d;
   fpsk::StreamArgs s;
   fpsk::ProductArgs a;
@@ -1695,6 +1699,7 @@ fpsketch_status deferred_probe(fpsketch_ctx* c, const void* A, const void* B, co
                                    c->pipe_has_prod ? c->pipe_nprod : 0,
                                    c->pipe_has_dec ? 1 : 0, c->dt == FPSK_BF16 ? 1 : 0, d.xb,
                                    lds, st));
+  wait.waited();          // (enqueued whole: nothing to wait for)
   c->pipe_dec = c->pipe_prod;
   c->pipe_has_dec = c->pipe_has_prod;
   c->pipe_prod = a;
@@ -1893,7 +1898,7 @@ fpsketch_status fpsketch_apply(fpsketch_ctx* c, const void* A, const void* B, vo
   const Decomp d = decompose(c->n1, c->n2, c->n3, m, false, c->transb);
   FPSK_TRY(build_round(seed, 0, round_caps(seed, 0, c->n1, c->n3, m, c->transb), c->n1, c->n3, d,
                        false, c->transb, true, c->aux_round, st));
-  FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, false, c->transb));
+  FPSK_TRY(ensure_workspace(c->aux_ws, c->n1, c->n2, c->n3, m, false, c->transb, st));
   FPSK_TRY(host_alloc(c->host_stats, 8 * sizeof(double)));
   double* stt = static_cast<double*>(c->host_stats.p);
   FPSK_TRY(dev_alloc(c->reprobe_acc, 2 * sizeof(double)));

@@ -318,6 +318,8 @@ struct PadTinyArgs {
 hipError_t launch_pad_tiny(const PadTinyArgs& a, hipStream_t st);
 hipError_t launch_publish_stats(const double* stats, double* out, hipStream_t st);
 hipError_t launch_apply(float* C, const ApplyEntry* list, int n, hipStream_t st);
+// Zeroes device memory: bytes at p, both multiples of 4.
+hipError_t launch_zero(void* p, size_t bytes, hipStream_t st);
 // Zeroes columns [c0, c1) of rows x ld FP32 rows (c1 <= ld).
 hipError_t launch_zero_cols(float* base, int rows, int ld, int c0, int c1, hipStream_t st);
 // A round's decisions on its grid S[0 .. n): the peel, the median and MAD (even counts: the mean

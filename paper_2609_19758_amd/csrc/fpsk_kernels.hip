@@ -1527,6 +1527,21 @@ hipError_t launch_rms(const SelArgs& a0, const SetupArgs& u, hipStream_t st) {
   return hipSuccess;
 }
 
+__global__ __launch_bounds__(kThreads) void zero_kernel(uint32_t* p, int64_t words) {
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kThreads;
+  const int64_t n4 = words / 4, t = static_cast<int64_t>(blockIdx.x) * kThreads + threadIdx.x;
+  for (int64_t i = t; i < n4; i += stride) reinterpret_cast<u32x4*>(p)[i] = u32x4{0u, 0u, 0u, 0u};
+  if (t < words - 4 * n4) p[4 * n4 + t] = 0u;
+}
+
+hipError_t launch_zero(void* p, size_t bytes, hipStream_t st) {
+  const int64_t words = static_cast<int64_t>(bytes / 4);
+  const int64_t g = std::max<int64_t>(1, std::min<int64_t>(2048, (words / 4 + kThreads - 1) / kThreads));
+  FPSK_LAUNCH(zero_kernel, dim3(static_cast<unsigned>(g)), dim3(kThreads), 0, st,
+              static_cast<uint32_t*>(p), words);
+  return hipSuccess;
+}
+
 // Zeroes columns [c0, c1) of `rows` rows of a row-major FP32 matrix whose rows are ld apart.
 __global__ __launch_bounds__(kThreads) void zero_cols_kernel(float* base, int rows, int ld,
                                                              int c0, int c1) {

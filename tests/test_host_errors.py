@@ -164,6 +164,15 @@ def fills(h):
         assert h.localize(0) == fk.OK and h.localize(1) == fk.OK
     assert h.rt.rt_unordered() == b"", h.rt.rt_unordered().decode()
     h.lib.fpsketch_destroy(h.c)
+    # a fill that fails: no context, and a call that needs it fails and the next one fills again
+    h.rt.rt_fail_kernel(b"zero_kernel")
+    assert h.create() == fk.ENOMEM
+    assert h.create() == fk.OK
+    h.rt.rt_fail_kernel(b"zero_kernel")
+    assert h.localize() == fk.ENOMEM
+    h.rt.rt_reset()
+    assert h.localize() == fk.OK and "zero_kernel" in h.log()
+    h.lib.fpsketch_destroy(h.c)
 
 
 def sequence(h):
@@ -177,6 +186,7 @@ def sequence(h):
         h.p.m, h.n2 = m, n2
         assert h.create() == fk.OK
         for call in calls.values():
+            assert call() == fk.OK           # (the first one also fills new buffers)
             h.rt.rt_reset()
             assert call() == fk.OK
             for k in dict.fromkeys(_kernels(h.log())):
@@ -209,7 +219,7 @@ def waits(h):
         def idle(what):
             assert h.rt.rt_busy() == 0, (i, what)
         assert _failing(h, call, idle) >= 1
-        assert h.create() == fk.OK
+        assert h.create() == fk.OK and call() == fk.OK
         h.rt.rt_reset()
         assert call() == fk.OK
         for k in dict.fromkeys(_kernels(h.log())):
