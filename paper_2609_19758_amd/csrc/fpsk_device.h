@@ -111,7 +111,7 @@ __device__ __forceinline__ void load8f_rag(const float* X, int64_t base, int off
 }
 
 // The rows rag_near picks: the final 8 elements of the matrix moved down to the lane's own
-// (zeros beyond the end), or the element loads of a matrix of fewer than 8.
+// (zeros beyond the end).
 __device__ __forceinline__ void rag_shift(u32x4& v, int64_t base, int off, int64_t last, bool ok) {
   const int s = ok ? off - rag_off(base, off, last) : 0;    // 0 .. 7 elements
   if (s & 1) {

@@ -11,7 +11,6 @@
 #include <cstdio>
 #include <cstring>
 #include <mutex>
-#include <numeric>
 #include <string>
 #include <unordered_map>
 #include <unordered_set>
@@ -1136,8 +1135,8 @@ fpsketch_status rms_hat_device(fpsketch_ctx* c, const float* C, bool scan, const
   return selection_enqueued(c, fpsk::launch_rms(a, u, st));
 }
 
-// Recheck a list of coordinates: gamma, sum |A||B| and C_ij, for coords (n pairs at the start of
-// host_rc, see recheck_coords_at) into the arrays after them.
+// Recheck of a list of coordinates: gamma, sum |A||B| and C_ij for the n pairs at the start of
+// host_rc, into the arrays after them (recheck_buffers).
 struct Recheck {
   int64_t* coords;
   double* gamma;
@@ -1360,7 +1359,7 @@ int64_t window_coords(const WindowCheck& wc, const std::vector<int64_t>& centers
     }
     return total;
   }
-  std::vector<int64_t> keys, found;
+  std::vector<int64_t> keys;
   for (size_t u = 0; u < n; ++u) {
     const int64_t ci = centers[2 * u], cj = centers[2 * u + 1];
     for (int64_t i = lo(ci); i <= hi(ci, n1); ++i)

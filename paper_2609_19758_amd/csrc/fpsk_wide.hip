@@ -338,7 +338,8 @@ __global__ __launch_bounds__(kWideThreads) void wide_b_kernel(StreamArgs s) {
   if (t == 0) s.maxpart[s.nA + blockIdx.x] = bmax;
 }
 
-// Dynamic LDS above 64 KB is asked for once per kernel and device.
+// Dynamic LDS above 64 KB has to be asked for; the attribute is set with every launch, since it is
+// the current device's (a host call without device work, taken under capture too).
 template <typename K>
 static hipError_t wide_launch(K kernel, int grid, size_t lds, hipStream_t st, hipEvent_t e0,
                               hipEvent_t e1, const StreamArgs& s) {
