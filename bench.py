@@ -25,6 +25,20 @@ METRIC = ("verify µs/call + HBM GB/s (A,B,C read) at 4096³ BF16; "
           "fault recovery rate")
 HBM_PEAK_GBS = 8000.0
 FP64_PEAK_TFLOPS = 78.6      # MI355X dense FP64, matrix and vector alike
+INT8_PEAK_TOPS = 5000.0      # MI355X dense 8-bit integer, matrix
+
+
+def product_figures(m: int, n2: int, p_us: float) -> dict:
+    """The bucket-space product S = P Q - S_C over the event-timed product and decision, against
+    the cores it runs on: FP64 FMAs on the block path (m <= 64), the FP64 matrix cores, or the
+    8-bit ones from the line the library draws (16 digit products of 2 m^2 n2 operations each)."""
+    digits = m > 256 and n2 >= 512 and m * m * n2 >= (2 ** 28 if n2 >= 4096 else 2.75 * 2 ** 28)
+    ops = 2 * m * m * n2 * (16 if digits else 1)
+    peak = INT8_PEAK_TOPS if digits else FP64_PEAK_TFLOPS
+    rate = ops / (p_us * 1e-6) / 1e12
+    return {"bound": "int8-matrix" if digits else ("fp64-matrix" if m > 64 else "fp64-vector"),
+            "flop": ops, "achieved": round(rate, 3), "peak": peak,
+            "unit": "TOP/s" if digits else "TFLOP/s", "frac": round(rate / peak, 4)}
 
 
 def log(msg: str):
@@ -819,12 +833,15 @@ def main() -> int:
 
     gbs = w.bytes_abc / (ms_per * 1e-3) / 1e9
     achieved = w.bytes_abc / (k_us * 1e-6) / 1e9
+    product = product_figures(v.m, w.n2, p_us)
     out = {
         "metric": METRIC, "value": round(gbs, 1), "unit": "GB/s", "n_gpus": 1,
         "steps": args.steps, "warmup": args.warmup, "ms_per_step": round(ms_per, 6),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "fp32+fp64",
         "arithmetic": "half inputs read exactly; FP32 sums of at most 8 terms and FP32 factors "
-                      "P = H1 A, Q = B H2^T; FP64 accumulation, bucket-space product and decision",
+                      "P = H1 A, Q = B H2^T; FP64 accumulation and decision; bucket-space product "
+                      + ("in 8-bit digits, exact sums" if product["bound"] == "int8-matrix"
+                         else "in FP64"),
         "data": "synthetic",
         "config": {"workload": w.name, "n1": w.n1, "n2": w.n2, "n3": w.n3, "operands": w.fmt,
                    "c": "fp32", "m": v.m, "m_law": m0,
@@ -861,15 +878,7 @@ def main() -> int:
                                "recomputed": recomputed, "delivered_correct": delivered_ok,
                                "apply_ms_median": round(float(np.median(apply_us)) / 1e3, 3)
                                if apply_us else None}},
-        # the bucket-space product S = P Q - S_C: 2 m^2 n2 FP64 FLOP per call against the FP64
-        # peak, over the event-timed product and decision (matrix cores above m = 64, FP64 FMAs
-        # on the block path below)
-        "product_roofline": {"bound": "fp64-matrix" if v.m > 64 else "fp64-vector",
-                             "flop": 2 * v.m * v.m * w.n2,
-                             "achieved": round(2 * v.m * v.m * w.n2 / (p_us * 1e-6) / 1e12, 3),
-                             "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                             "frac": round(2 * v.m * v.m * w.n2 / (p_us * 1e-6) / 1e12
-                                           / FP64_PEAK_TFLOPS, 4)},
+        "product_roofline": product,
         # the whole call (stream pass, product and decision) against the same roofline
         "call_roofline": {"bound": "hbm", "achieved": round(gbs, 1), "peak": HBM_PEAK_GBS,
                           "unit": "GB/s", "frac": round(gbs / HBM_PEAK_GBS, 4)},
