@@ -16,15 +16,20 @@
 //     is small in one factor and large in the other is of middle size in both.  Channels scaled
 //     by 1e-6 in A (half of them) and in B (the others) gave S errors of 1855 times the noise without
 //     it, 0.0023 times with it, as the FP64 product does (2048 x 4096 x 2048, m = 260, BF16).
-//   - a row takes part when its quantum u adds at most about a quarter of the FP32 rounding to S:
-//     u^2 / 12 sum_k s_k^2 <= 1/15 2^-50.7 sum_k (x_k s_k)^2, s_k the channel's typical size in the
-//     other factor (equal for both after the scaling), 2^-50.7 the mean square of FP32 rounding
-//     relative to the values.  A Gaussian row has a 50 times smaller left side, one with a channel 30
-//     times the others' still a smaller one.  Rows that are not finite do not take part.
-// The typical sizes are means of the exponents over 64 buckets a factor, zeros left out: the
-// buckets are random sums of rows, and a mean of logarithms is not moved by a few rows of another
-// scale.  Tiles with a row that takes no part are left to the FP64 matrix cores, whose kernel runs
-// beside this one and takes only those.
+//   - a row takes part when its quantum u adds at most about half of the FP32 rounding to S:
+//     u^2 / 12 sum_k w_k <= 4/15 2^-50.7 sum_k w_k x_k^2, w_k the channel's typical square in the
+//     other factor (equal for both after the scaling) and 2^-50.7 the mean square of FP32 rounding
+//     relative to the values; with T = 2^49 u^2, sum_k w_k T <= sum_k w_k x_k^2.  Every x_k^2 counts
+//     at most 16 T, so that at least 1/16 of the weight has to lie where the row is above the bound,
+//     and not in one entry that most of the other factor's rows may not meet (1e30 in a channel that
+//     a single column of B holds: with the uncapped sum the rest of the row was lost).  A Gaussian
+//     row has a 200 times smaller left side; rows with 40 channels at 30 times the others' scale
+//     still take part (with T four times larger most tiles of 6 such channels were refused: 4096^3,
+//     m = 432, 124 -> 147 us a probe).  Rows of one huge entry, or not finite, take no part.
+// The typical sizes are means of the exponents over 64 buckets a factor, zeros left out, and the
+// weights the share of the buckets that hold the channel: the buckets are random sums of rows, and a
+// mean of logarithms is not moved by a few rows of another scale.  Tiles with a row that takes no part
+// are left to the FP64 matrix cores, whose kernel runs beside this one and takes only those.
 //
 // Error of S against 64 bits (rms over the noise), FP64 product and here: 2048 x 4096 x 2048,
 // m = 260, BF16 0.002402 both, FP16 0.004215 both; 4096^3 BF16, m = 1000 0.001302 both; channels scaled
@@ -33,9 +38,9 @@
 // errors by 0.1 %.)
 //
 // Bound by the integer matrix cores: 16 x 2 m^2 n2 operations at 1/64 of the FP64 cores' time each.
-// 16384^3 FP16, m = 4096: FP64 8400 us -> 3655 us (product 3340, digits 175, row scales 131, channels
-// 6), 2.6 x 10^15 operations a second of the 4.7 x 10^15 that registers alone reach; m = 698: 301 ->
-// 187 us; 4096^3, m = 432: 43 us and 15 us of slice sums -> 40 and 8 us.
+// 16384^3 FP16, m = 4096: FP64 8400 us -> 3660 us (product 3340, digits 179, row scales 137, channels
+// 7), 2.6 x 10^15 operations a second of the 4.7 x 10^15 that registers alone reach; m = 698: 301 ->
+// 190 us; 4096^3, m = 432: 43 us and 15 us of slice sums -> 41 and 8 us.
 #include "fpsk_device.h"
 
 namespace fpsk {
@@ -43,17 +48,26 @@ namespace fpsk {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
 
-// Channel figures: the power of two t that balances channel k (low byte), and the binary logarithm
-// v of its typical size in both factors once balanced (high byte; kNoSize where a factor's sample
-// holds only zeros).  A work-group takes 128 channels; a thread 4 of them in 8 of the 64 sampled rows
-// of each factor.  A channel without a size in one factor is scaled out of the other: a row that
-// has an entry there after all is then too far from its typical size to take part.
+// Channel figures: the power of two t that balances channel k (bal), and the binary logarithm of the
+// channel's weight (weight), the product of its typical sizes in both factors times the
+// share of the sampled rows that hold it at all; kNoSize where a factor's sample holds only zeros.  A
+// work-group takes 128 channels; a thread 4 of them in 8 of the 64 sampled rows of each factor.  A
+// channel without a size in one factor is scaled out of the other: a row that has an entry there
+// after all is then too far from its typical size to take part.
 constexpr int kSampleRows = 64;
-constexpr int kNoSize = -128;
+constexpr int kNoSize = -32768;
+
+// 2^(lw - top), top the largest of the logarithms: zero below 2^-126.
+__device__ __forceinline__ float weight_of(int lw, int top) {
+  const int b = 127 + lw - top;
+  return lw == kNoSize || b < 0 ? 0.0f : __uint_as_float(static_cast<uint32_t>(b) << 23);
+}
 
 __global__ __launch_bounds__(kThreads) void channel_kernel(ProductArgs pa) {
   constexpr int G = kThreads / 32;                   // row groups
   __shared__ uint32_t part[2][G][128];
+  __shared__ int stop[2];
+  __shared__ float ssum[2];
   const int t = threadIdx.x, g = t >> 5, c0 = 4 * (t & 31);
   const int64_t k = static_cast<int64_t>(blockIdx.x) * 128 + c0;
   f32x4 x[2][kSampleRows / G];
@@ -77,8 +91,9 @@ __global__ __launch_bounds__(kThreads) void channel_kernel(ProductArgs pa) {
       part[f][g][c0 + e] = n;
     }
   __syncthreads();
+  int w = kNoSize;
   if (t < 128) {
-    int ex[2];
+    int ex[2], held = 0;
     bool none[2];
 #pragma unroll
     for (int f = 0; f < 2; ++f) {
@@ -88,88 +103,170 @@ __global__ __launch_bounds__(kThreads) void channel_kernel(ProductArgs pa) {
       const int cnt = static_cast<int>(n >> 16);
       none[f] = cnt == 0;
       ex[f] = (static_cast<int>(n & 0xffffu) + cnt / 2) / (cnt > 0 ? cnt : 1) - 127;
+      held += 31 - __clz(cnt > 0 ? cnt : 1);           // log2 of the rows that hold it
     }
-    int bal = (ex[1] - ex[0]) >> 1, v = (ex[0] + ex[1]) >> 1;
+    int bal = (ex[1] - ex[0]) >> 1;
+    w = ex[0] + ex[1] + held;
     bal = bal < -100 ? -100 : (bal > 100 ? 100 : bal);
-    v = v < -127 ? -127 : v;
     if (none[0] || none[1]) {
       bal = none[0] == none[1] ? 0 : (none[0] ? 100 : -100);
-      v = kNoSize;
+      w = kNoSize;
     }
-    pa.chan[blockIdx.x * 128 + t] =
-        static_cast<uint16_t>((bal & 255) | (v & 255) << 8);
+    pa.bal[blockIdx.x * 128 + t] = static_cast<int8_t>(bal);
+    pa.weight[blockIdx.x * 128 + t] = static_cast<int16_t>(w);
+    // the work-group's largest weight, and the sum of its weights relative to that
+    const int m64 = static_cast<int>(wave_max_u32(static_cast<uint32_t>(w - kNoSize))) + kNoSize;
+    if ((t & 63) == 0) stop[t >> 6] = m64;
+  }
+  __syncthreads();
+  const int top = stop[0] > stop[1] ? stop[0] : stop[1];
+  if (t < 128) {
+    float sum = weight_of(w, top);
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    if ((t & 63) == 0) ssum[t >> 6] = sum;
+  }
+  __syncthreads();
+  if (t == 0) {
+    pa.wtop[blockIdx.x] = top;
+    pa.wsum[blockIdx.x] = ssum[0] + ssum[1];
   }
   if (blockIdx.x == 0 && t == 0) pa.rexp[2 * pa.m] = pa.rexp[2 * pa.m + 1] = 0;
 }
 
-__device__ __forceinline__ int chan_bal(uint32_t c) { return static_cast<int8_t>(c & 255u); }
-__device__ __forceinline__ int chan_size(uint32_t c) { return static_cast<int8_t>((c >> 8) & 255u); }
+// Byte i of a word of four balancing exponents.
+__device__ __forceinline__ int bal_of(uint32_t c, int i) {
+  return static_cast<int>(c << (24 - 8 * i)) >> 24;
+}
 
 // Scale exponent e of each row (2m work-groups: rows of P, then of Q): the balanced row times 2^e
 // rounds to integers whose four signed digits exist, |x 2^e| <= 2^31 - 2^24; kNoDigits for a row
-// that takes no part.  rexp[2m], rexp[2m + 1]: whether any row of P, of Q does.
+// that takes no part.  rexp[2m], rexp[2m + 1]: whether any row of P, of Q does.  The balanced row
+// stays in registers between the search for its largest entry and the sum over it (NV 16-byte pieces a
+// thread; NV = 0, longer rows, reads it again).  16384^3, m = 698, 92 MB of factors: read twice 28.8 us,
+// kept 19.1 us (loads behind branches, one piece at a time: 28 us).
+template <int NV>
 __global__ __launch_bounds__(kThreads) void row_scale_kernel(ProductArgs pa) {
   __shared__ uint32_t smax[kThreads / 64];
-  __shared__ double sen[kThreads / 64], sws[kThreads / 64];
+  __shared__ int stop[kThreads / 64];
+  __shared__ float sen[kThreads / 64], sws[kThreads / 64];
   const int r = blockIdx.x, t = threadIdx.x, lane = t & 63, w = t >> 6;
   const bool second = r >= pa.m;
   const float* x = second ? pa.Q + static_cast<int64_t>(r - pa.m) * pa.ldp
                           : pa.P + static_cast<int64_t>(r) * pa.ldp;
   const int sg = second ? -1 : 1;
+  // the largest weight of all channels
+  const int groups = (pa.n2 + 127) / 128;
+  int top = kNoSize;
+  for (int i = t; i < groups; i += kThreads) top = pa.wtop[i] > top ? pa.wtop[i] : top;
   uint32_t mx = 0;                          // bits of the largest magnitude (NaN above infinity)
-  double en = 0.0, ws = 0.0;                // sums of (x s)^2 and s^2
-#pragma unroll 4
-  for (int k = 4 * t; k < pa.kact; k += 4 * kThreads) {
-    const f32x4 v = *reinterpret_cast<const f32x4*>(x + k);
-    const u32x2 c = *reinterpret_cast<const u32x2*>(pa.chan + k);
+  auto row_at = [&](int k) { return *reinterpret_cast<const f32x4*>(x + k); };
+  auto bal_at = [&](int k) { return *reinterpret_cast<const uint32_t*>(pa.bal + k); };
+  auto weight_at = [&](int k) { return *reinterpret_cast<const u32x2*>(pa.weight + k); };
+  auto balanced = [&](f32x4 v, uint32_t c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = ldexpf(v[e], sg * bal_of(c, e));
+    return v;
+  };
+  auto largest = [&](const f32x4& v) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const uint32_t ce = c[e >> 1] >> (16 * (e & 1));
-      const float xs = ldexpf(v[e], sg * chan_bal(ce));
-      const uint32_t b = __float_as_uint(xs) & 0x7fffffffu;
+      const uint32_t b = __float_as_uint(v[e]) & 0x7fffffffu;
       mx = b > mx ? b : mx;
-      // s^2 = 2^(2 size), zero for a channel without a size
-      const int size = chan_size(ce);
-      const uint32_t hi = size == kNoSize ? 0u : static_cast<uint32_t>(1023 + 2 * size) << 20;
-      const double s2 = __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32);
-      const double xd = static_cast<double>(xs);
-      en = fma(xd * xd, s2, en);
-      ws += s2;
     }
+  };
+  // (pieces past the row read its first ones and count as zeros: loads without branches go out
+  // together)
+  f32x4 kept[NV > 0 ? NV : 1];
+  u32x2 wt[NV > 0 ? NV : 1];
+  if constexpr (NV > 0) {
+    uint32_t c[NV];
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = 4 * t + 4 * kThreads * i, at = k < pa.kact ? k : 0;
+      kept[i] = row_at(at);
+      c[i] = bal_at(at);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const bool in = 4 * t + 4 * kThreads * i < pa.kact;
+      kept[i] = balanced(kept[i], c[i]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) kept[i][e] = in ? kept[i][e] : 0.0f;
+      largest(kept[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int k = 4 * t + 4 * kThreads * i;
+      wt[i] = weight_at(k < pa.kact ? k : 0);
+    }
+  } else {
+#pragma unroll 4
+    for (int k = 4 * t; k < pa.kact; k += 4 * kThreads) largest(balanced(row_at(k), bal_at(k)));
   }
   mx = wave_max_u32(mx);
+  top = static_cast<int>(wave_max_u32(static_cast<uint32_t>(top - kNoSize))) + kNoSize;
+  if (lane == 0) {
+    smax[w] = mx;
+    stop[w] = top;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kThreads / 64; ++i) {
+    mx = smax[i] > mx ? smax[i] : mx;
+    top = stop[i] > top ? stop[i] : top;
+  }
+  const float big = __uint_as_float(mx);
+  int q = 0;                                // quantum 2^-q
+  if (mx < 0x7f800000u && big >= 0x1p-120f) {
+    int ex;
+    const float f = frexpf(big, &ex);       // big = f 2^ex, 0.5 <= f < 1
+    q = f <= 1.0f - 0x1p-7f ? 31 - ex : 30 - ex;
+  } else if (mx != 0) {
+    if (t == 0) pa.rexp[r] = kNoDigits;
+    return;
+  }
+  // sums of the weights times min(2 x^2 / T, 32), and of the weights
+  float en = 0.0f, ws = 0.0f;
+  for (int i = t; i < groups; i += kThreads) ws += ldexpf(pa.wsum[i], pa.wtop[i] - top);
+  auto weigh = [&](const f32x4& v, const u32x2& c) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float y = ldexpf(v[e], q - 24);           // at most 2^7
+      const int lw = static_cast<int>(c[e >> 1] << (16 - 16 * (e & 1))) >> 16;
+      int b = 127 + lw - top;                         // (a channel without a size is far below 0)
+      b = b > 0 ? b : 0;
+      en = fmaf(fminf(y * y, 32.0f), __uint_as_float(static_cast<uint32_t>(b) << 23), en);
+    }
+  };
+  if constexpr (NV > 0) {
+#pragma unroll
+    for (int i = 0; i < NV; ++i) weigh(kept[i], wt[i]);
+  } else {
+#pragma unroll 4
+    for (int k = 4 * t; k < pa.kact; k += 4 * kThreads) {
+      weigh(balanced(row_at(k), bal_at(k)), weight_at(k));
+    }
+  }
 #pragma unroll
   for (int d = 32; d > 0; d >>= 1) {
     en += __shfl_xor(en, d, 64);
     ws += __shfl_xor(ws, d, 64);
   }
   if (lane == 0) {
-    smax[w] = mx;
     sen[w] = en;
     sws[w] = ws;
   }
   __syncthreads();
   if (t != 0) return;
   for (int i = 1; i < kThreads / 64; ++i) {
-    mx = smax[i] > mx ? smax[i] : mx;
     en += sen[i];
     ws += sws[i];
   }
-  int e = kNoDigits;
-  const float big = __uint_as_float(mx);
-  if (mx == 0) {
-    e = 0;
-  } else if (mx < 0x7f800000u && big >= 0x1p-120f && ws > 0.0) {
-    int ex;
-    const float f = frexpf(big, &ex);              // big = f 2^ex, 0.5 <= f < 1
-    const int q = f <= 1.0f - 0x1p-7f ? 31 - ex : 30 - ex;
-    // quantum 2^-q: ws 2^(-2q) / 12 <= en 2^-50.7 / 15 (a channel without a size has no part in en,
-    // so that a NaN or an infinity there is seen in mx only)
-    if (ldexp(en, 2 * q - 51) >= ws) e = q;
-  }
-  pa.rexp[r] = e;
+  const bool takes = mx == 0 || (ws > 0.0f && en >= 2.0f * ws);
+  pa.rexp[r] = takes ? q : kNoDigits;
   // (every work-group that does stores the same word: no atomic, which cost 10 ns a row here)
-  if (e != kNoDigits) pa.rexp[2 * pa.m + (second ? 1 : 0)] = 1;
+  if (takes) pa.rexp[2 * pa.m + (second ? 1 : 0)] = 1;
 }
 
 // Digit fragments.  For a block of 32 rows, 32 k and one digit the matrix instruction's operand
@@ -190,18 +287,17 @@ __global__ __launch_bounds__(kThreads) void digits_kernel(ProductArgs pa, int nb
   if (__ballot(bad) != 0 || pa.rexp[2 * pa.m + (second ? 0 : 1)] == 0) return;
   if (k >= KS * 32) return;
   const float* x = (second ? pa.Q : pa.P) + static_cast<int64_t>(r < pa.m ? r : 0) * pa.ldp + k;
-  const u32x4* ch = reinterpret_cast<const u32x4*>(pa.chan + k);
+  const u32x4 ch = *reinterpret_cast<const u32x4*>(pa.bal + k);
   f32x4 v[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) v[j] = reinterpret_cast<const f32x4*>(x)[j];
-  const u32x4 c[2] = {ch[0], ch[1]};
   u32x4 d[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     uint32_t u[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      const int bal = chan_bal(c[j >> 1][2 * (j & 1) + (i >> 1)] >> (16 * (i & 1)));
+      const int bal = bal_of(ch[j], i);
       const int q = e != kNoDigits ? __float2int_rn(ldexpf(v[j][i], second ? e - bal : e + bal)) : 0;
       // signed bytes: each of the lower three hands its carry up
       u[i] = (static_cast<uint32_t>(q) + 0x00808080u) ^ 0x00808080u;
@@ -413,7 +509,14 @@ hipError_t launch_digit_product(const ProductArgs& a, hipStream_t st, hipEvent_t
   const int nbP = (a.m + 127) / 128 * 4, nbQ = (a.m + 63) / 64 * 2;
   const int KS = (a.n2 + 31) / 32;
   FPSK_LAUNCH_TIMED(channel_kernel, dim3((a.n2 + 127) / 128), dim3(kThreads), 0, st, e0, nullptr, a);
-  FPSK_LAUNCH(row_scale_kernel, dim3(2 * a.m), dim3(kThreads), 0, st, a);
+  const dim3 rows(2 * a.m), block(kThreads);
+  if (a.kact <= 4 * 4 * kThreads) {
+    FPSK_LAUNCH(row_scale_kernel<4>, rows, block, 0, st, a);
+  } else if (a.kact <= 16 * 4 * kThreads) {
+    FPSK_LAUNCH(row_scale_kernel<16>, rows, block, 0, st, a);
+  } else {
+    FPSK_LAUNCH(row_scale_kernel<0>, rows, block, 0, st, a);
+  }
   FPSK_LAUNCH(digits_kernel, dim3((KS + 3) / 4, nbP + nbQ), dim3(kThreads), 0, st, a, nbP);
   const int wgs = (a.m + 127) / 128 * ((a.m + 63) / 64) * a.NS;
   FPSK_LAUNCH(digit_product_kernel, dim3((wgs + 7) / 8 * 8), dim3(kThreads), 0, st, a, a.zero);

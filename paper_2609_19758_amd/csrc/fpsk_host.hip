@@ -621,7 +621,7 @@ struct Workspace {
   DevBuf P, Pw, Q, Qw, partS, partR, partT, scratch, S, R, T, maxpart, tilestat;
   DevBuf xpart;                // probe block-product partials
   DevBuf rexp, digP, digQ;     // digit product: row scales and digit fragments
-  DevBuf chan;                 // and channel figures
+  DevBuf bal, weight, wtop, wsum;   // and channel figures
 };
 
 fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n3, int m,
@@ -658,7 +658,10 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
     const size_t row = static_cast<size_t>((n2 + 31) / 32) * 128;    // 4 digits of each k
     const size_t groups = static_cast<size_t>((n2 + 127) / 128);
     FPSK_TRY(dev_alloc(W.rexp, (static_cast<size_t>(m) * 2 + 2) * sizeof(int32_t)));
-    FPSK_TRY(dev_alloc(W.chan, groups * 128 * sizeof(uint16_t)));
+    FPSK_TRY(dev_alloc(W.bal, groups * 128 * sizeof(int8_t)));
+    FPSK_TRY(dev_alloc(W.weight, groups * 128 * sizeof(int16_t)));
+    FPSK_TRY(dev_alloc(W.wtop, groups * sizeof(int32_t)));
+    FPSK_TRY(dev_alloc(W.wsum, groups * sizeof(float)));
     FPSK_TRY(dev_alloc(W.digP, static_cast<size_t>((m + 127) / 128) * 128 * row));
     FPSK_TRY(dev_alloc(W.digQ, static_cast<size_t>((m + 63) / 64) * 64 * row));
   }
@@ -668,7 +671,8 @@ fpsketch_status ensure_workspace(Workspace& W, int64_t n1, int64_t n2, int64_t n
 void free_workspace(Workspace& W) {
   for (DevBuf* b : {&W.P, &W.Pw, &W.Q, &W.Qw, &W.partS, &W.partR, &W.partT, &W.scratch, &W.S,
                     &W.R, &W.T, &W.maxpart, &W.tilestat, &W.xpart, &W.rexp, &W.digP,
-                    &W.digQ, &W.chan}) {
+                    &W.digQ, &W.bal, &W.weight,
+                    &W.wtop, &W.wsum}) {
     dev_free(*b);
   }
 }
@@ -913,7 +917,10 @@ fpsketch_status pass_args(fpsketch_ctx* c, const DevRound& R, Workspace& W, cons
   a.i8 = d.i8 ? 1 : 0;
   a.zero = c->zero.p;
   a.rexp = as<int32_t>(W.rexp);
-  a.chan = as<uint16_t>(W.chan);
+  a.bal = as<int8_t>(W.bal);
+  a.weight = as<int16_t>(W.weight);
+  a.wtop = as<int32_t>(W.wtop);
+  a.wsum = as<float>(W.wsum);
   a.digP = as<uint32_t>(W.digP);
   a.digQ = as<uint32_t>(W.digQ);
   a.npc = d.npc;

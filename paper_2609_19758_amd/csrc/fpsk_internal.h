@@ -127,7 +127,10 @@ struct ProductArgs {
   // 2 m + 2: scale exponent of every row of P, then of Q (kNoDigits where not), then for
   // either whether any row has one
   int32_t* rexp;
-  uint16_t* chan;         // per k, padded to 128: balancing exponent, size (fpsk_digits.hip)
+  int8_t* bal;            // per k, padded to 128: balancing exponent and weight (fpsk_digits.hip)
+  int16_t* weight;
+  int32_t* wtop;          // per 128 k: largest weight, sum relative to it
+  float* wsum;
   uint32_t* digP;         // digit fragments of P (rows padded to 128) and Q (to 64)
   uint32_t* digQ;
   const void* zero;       // >= 64 bytes of zeros
